@@ -10,88 +10,78 @@ namespace ls {
 namespace {
 
 // One workgroup per sequence; a thread takes nodes tid, tid + blockDim.x, ...
-//   match[i]   node i carries the token the target predicts after its parent
-//   chosen[i]  match[i] and no earlier sibling matches (lowest index wins among equal tokens)
-//   node i is on the accepted path iff every node from i up to, not including, node 0 is
-//   chosen and that walk ends at node 0.  At most one child of a node is chosen, so the
-//   accepted nodes form one root path and a node's position on it is its depth.
+//   match[i]    node i carries the token the target predicts after its parent
+//   child_of[p] the lowest matching child of p (lowest index wins among equal tokens)
+// The accepted path starts at node 0 and follows child_of until a node has no matching child;
+// children come after their parents, so the walk ends after at most n_tree steps.
+//
+// Bound by latency: one round trip for the three token arrays, two LDS passes, and the walk, one
+// LDS read per accepted node.  Siblings compete with an LDS minimum per parent; the form before
+// compared every matching node with all earlier ones and let every node walk up to the root, one
+// LDS read after the other (128 nodes, 4 sequences: 12.9 us, this form 2.4 us).
 __global__ void __launch_bounds__(256)
 tree_accept_kernel(const int32_t *__restrict__ parents, const int32_t *__restrict__ draft,
                    const int32_t *__restrict__ target, int32_t n_tree, int32_t *__restrict__ path,
                    int32_t *__restrict__ accept_len, int32_t *__restrict__ next_token,
                    int32_t *__restrict__ err_flag)
 {
-    __shared__ int32_t par[LS_MAX_TREE];
+    constexpr int NPT = LS_MAX_TREE / 256;  // nodes per thread, for the smallest workgroup that may see LS_MAX_TREE nodes
     __shared__ int32_t tgt[LS_MAX_TREE];
-    __shared__ uint8_t match[LS_MAX_TREE];
-    __shared__ uint8_t chosen[LS_MAX_TREE];
-    __shared__ int32_t len_sh;
-    __shared__ int32_t last_sh;
+    __shared__ int32_t child_of[LS_MAX_TREE];
+    __shared__ int32_t path_sh[LS_MAX_TREE];
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
-    const int step = blockDim.x;
+    const int step = blockDim.x;  // n_tree <= NPT * step
     parents += (size_t)b * n_tree;
     draft += (size_t)b * n_tree;
     target += (size_t)b * n_tree;
     path += (size_t)b * n_tree;
 
     int bad = 0;
-    for (int i = tid; i < n_tree; i += step) {
-        int32_t p = parents[i];
-        if (p < -1 || p >= i) {  // not a forest in topological order: treat the node as a root
-            bad = 1;
-            p = -1;
-        }
-        par[i] = p;
+    int32_t par[NPT], own[NPT];
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+        const int i = tid + k * step;
+        par[k] = -1;
+        own[k] = 0;
+        if (i >= n_tree) continue;
+        par[k] = parents[i];
+        own[k] = draft[i];
         tgt[i] = target[i];
-        path[i] = -1;
-    }
-    if (tid == 0) {
-        len_sh = 0;
-        last_sh = 0;
-    }
-    __syncthreads();
-    for (int i = tid; i < n_tree; i += step) match[i] = i > 0 && par[i] >= 0 && draft[i] == tgt[par[i]];
-    __syncthreads();
-    for (int i = tid; i < n_tree; i += step) {
-        bool first = match[i];
-        for (int j = 1; j < i && first; ++j)
-            if (par[j] == par[i] && match[j]) first = false;
-        chosen[i] = first;
-    }
-    __syncthreads();
-    for (int i = tid; i < n_tree; i += step) {
-        int cur = i, depth = 0;
-        bool on_path = true;
-        while (cur > 0) {  // par[cur] < cur, so this ends after at most i steps
-            if (!chosen[cur]) {
-                on_path = false;
-                break;
-            }
-            cur = par[cur];
-            ++depth;
-        }
-        on_path = on_path && cur == 0;  // a walk that ends at another root is off the path
-        if (on_path) {
-            path[depth] = i;
-            // depth in the high bits, node in the low ones: the maximum names the deepest accepted node
-            atomicMax(&last_sh, (depth << 16) | i);
-            atomicMax(&len_sh, depth + 1);
+        child_of[i] = LS_MAX_TREE;
+        path_sh[i] = -1;
+        if (par[k] < -1 || par[k] >= i) {  // not a forest in topological order: treat the node as a root
+            bad = 1;
+            par[k] = -1;
         }
     }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NPT; ++k)
+        if (par[k] >= 0 && own[k] == tgt[par[k]]) atomicMin(&child_of[par[k]], tid + k * step);
     const int any_bad = __syncthreads_or(bad);
     if (tid == 0) {
-        // the deepest accepted node reports the token the target adds itself
-        next_token[b] = tgt[last_sh & 0xffff];
-        accept_len[b] = len_sh;
+        int cur = 0, len = 0;
+        while (true) {
+            path_sh[len++] = cur;
+            const int next = child_of[cur];
+            if (next >= n_tree) break;
+            cur = next;
+        }
+        next_token[b] = tgt[cur];  // the token the target adds itself after the deepest accepted node
+        accept_len[b] = len;
         if (err_flag) err_flag[b] = any_bad ? 1 : 0;
     }
+    __syncthreads();
+    for (int i = tid; i < n_tree; i += step) path[i] = path_sh[i];
 }
 
 // One workgroup per (sequence, KV head): 16-byte pieces of the accepted rows of K and V are
 // copied from the tree buffers to cache rows prefix_len, prefix_len + 1, ...  The number of
 // rows moved is the longest prefix of the path whose entries are nodes and whose target rows
 // exist; anything shorter than accept_len is reported in err_flag.
+//
+// Bound by latency as well: lengths and path, then the rows, then the stores.
 __global__ void __launch_bounds__(256)
 kv_commit_kernel(Problem p, int elem_bytes, const int32_t *__restrict__ accept_path,
                  const int32_t *__restrict__ accept_len, uint8_t *__restrict__ k_cache,
@@ -104,6 +94,14 @@ kv_commit_kernel(Problem p, int elem_bytes, const int32_t *__restrict__ accept_p
     const int g = blockIdx.x % p.n_kv_heads;
     const int tid = threadIdx.x;
 
+    // the whole path, together with the lengths that say how much of it counts: one round trip
+    constexpr int NPT = LS_MAX_TREE / 256;
+    int32_t node[NPT];
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+        const int t = tid + k * 256;
+        node[k] = t < p.n_tree ? accept_path[(size_t)b * p.n_tree + t] : -1;
+    }
     int plen = p.prefix_lens[b];
     plen = plen < 0 ? 0 : (plen > p.max_prefix_len ? p.max_prefix_len : plen);
     int want = accept_len[b];
@@ -112,22 +110,25 @@ kv_commit_kernel(Problem p, int elem_bytes, const int32_t *__restrict__ accept_p
     int n = want < room ? want : room;
     if (tid == 0) n_sh = n;
     __syncthreads();
-    for (int t = tid; t < n; t += blockDim.x) {
-        const int32_t node = accept_path[(size_t)b * p.n_tree + t];
-        path[t] = node;
-        if (node < 0 || node >= p.n_tree) atomicMin(&n_sh, t);  // stop before the first bad entry
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+        const int t = tid + k * 256;
+        if (t >= n) continue;
+        path[t] = node[k];
+        if (node[k] < 0 || node[k] >= p.n_tree) atomicMin(&n_sh, t);  // stop before the first bad entry
     }
     __syncthreads();
     n = n_sh;
 
-    const int chunks = p.head_dim * elem_bytes / 16;  // 16-byte pieces per row
+    // 16-byte pieces per row: 8, 16 or 32 (head_dim 64 or 128, elements of 2 or 4 bytes)
+    const int chunk_shift = __builtin_ctz((uint32_t)(p.head_dim * elem_bytes / 16));
     const uint8_t *kt = (const uint8_t *)p.k_tree + (b * p.kt_stride[0] + g * p.kt_stride[1]) * elem_bytes;
     const uint8_t *vt = (const uint8_t *)p.v_tree + (b * p.vt_stride[0] + g * p.vt_stride[1]) * elem_bytes;
     // contiguous cache: first index = sequence; paged cache: first index = page, found per row
     const int32_t *tab = p.block_table ? p.block_table + (size_t)b * p.bt_stride : nullptr;
     const int page_rows_mask = (1 << p.page_shift) - 1;
-    for (int e = tid; e < n * chunks; e += blockDim.x) {
-        const int j = e / chunks, c = e % chunks;
+    for (int e = tid; e < n << chunk_shift; e += blockDim.x) {
+        const int j = e >> chunk_shift, c = e & ((1 << chunk_shift) - 1);
         const int64_t node = path[j];
         const int row = plen + j;  // < max_prefix_len <= bt_stride * page size
         const int64_t first = tab ? (int64_t)tab[row >> p.page_shift] : (int64_t)b;

@@ -258,6 +258,41 @@ SplitPlan plan_call(const ls_desc &d)
     return plan;
 }
 
+// Which kernels a whole-path call on 16-bit inputs runs (the float path has one form).
+struct WholePlan {
+    int32_t row_tiles;  // > 0: the kernel whose waves split the keys, this many 32-row tiles per workgroup
+    int32_t n_splits;   // its key splits; 1: its output is final
+};
+
+WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree)
+{
+    WholePlan w{0, 0};
+    const int rows_kv = d.n_q_heads / d.n_kv_heads * d.n_tree;
+    const int tiles = (d.max_prefix_len + 31) / 32 + (with_tree ? (d.n_tree + 31) / 32 : 0);
+    // the ranges in which the kernels' divisions by multiplication are exact
+    const int64_t heads = (int64_t)d.batch * d.n_q_heads;
+    if (heads * d.n_tree * d.n_tree >= (1ll << 32) || heads * d.n_q_heads >= (1ll << 32) ||
+        ((int64_t)tiles + plan.n_splits) * plan.n_splits >= (1ll << 32) ||
+        (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 31) / 32) * plan.n_splits * ((rows_kv + 31) / 32 + plan.n_splits) >= (1ll << 32))
+        return w;
+    // rows of the tree are addressed with 32-bit offsets inside a tile
+    if (with_tree && (d.kt_stride[2] >= (1 << 24) || d.vt_stride[2] >= (1 << 24))) return w;
+    // A cache of some 1500 keys is worked through by one workgroup per row tile in less time than the merge
+    // of a split call takes (64 rows per KV head, 8 KV heads: 700 keys 11.0 us in one split against 12.9 in
+    // two and 18.6 on the kernel that shares tiles between waves; 1600 keys 14.9, 16.3, 19.8).
+    constexpr int kDirectTiles = 48;
+    if (rows_kv <= 64) {
+        // every wave of a workgroup holds all the query rows of the KV head (32 rows per KV head, 16k keys: 52.7
+        // against 57.3 us; 64 rows, 32k keys: 34.6 against 35.4; 32 rows, 8k keys: 14.2 against 20.6)
+        w.row_tiles = rows_kv <= 32 ? 1 : 2;
+        w.n_splits = tiles <= kDirectTiles ? 1 : plan.n_splits;
+    } else if (tiles <= kDirectTiles) {
+        w.row_tiles = 1;
+        w.n_splits = 1;
+    }
+    return w;
+}
+
 }  // namespace ls
 
 using namespace ls;
@@ -398,6 +433,17 @@ int ls_lse_merge(const ls_desc *desc, int32_t n_parts, int32_t part_dtype, const
 }  // extern "C"
 
 namespace {
+// Whole-path call on the kernel whose waves split the keys, and the merge if there is more than one split.
+int run_wave_split(const ls_desc &d, const Problem &p, const WholePlan &plan, const int32_t *parents, int32_t *err,
+                   void *out, float *lse, void *o_parts, float *lse_parts, hipStream_t s)
+{
+    WholeCall w{parents, err, out, {d.o_stride[0], d.o_stride[1], d.o_stride[2]}, lse, o_parts, lse_parts, plan.n_splits,
+                FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads)};
+    if (launch_wave_split(p, d.dtype, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
+    if (plan.n_splits > 1 && launch_merge_parts(p, d.dtype, w, s) != hipSuccess) return LS_ERR_HIP;
+    return LS_OK;
+}
+
 // The whole path for a contiguous cache.  prefix_lens: device array, or nullptr with every
 // sequence holding prefix_len_all cached rows.
 int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, const void *v_cache,
@@ -424,6 +470,10 @@ int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, c
     hipStream_t s = (hipStream_t)stream;
     Problem p = make_problem(*desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree);
     p.prefix_len_all = prefix_len_all;
+    if (prefix_mfma_supports(p, desc->dtype) && !single_launch) {
+        const WholePlan whole = plan_whole(*desc, plan, true);
+        if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, parents, err, out, lse, o_parts, lse_parts, s);
+    }
 
     // (b) cached keys -> parts [0, n_splits), stored in the problem's dtype; on the MFMA path
     // the same launch carries the workgroups of (a), the tree mask
@@ -547,6 +597,10 @@ int ls_cache_attn(const ls_desc *desc, const void *q, const void *k_cache, const
     const Problem p = make_problem(*desc, q, k_cache, v_cache, prefix_lens, nullptr, nullptr);
     const bool mfma = prefix_mfma_supports(p, desc->dtype);
     if (!mfma && is_16bit(desc->dtype)) return LS_ERR_UNSUPPORTED;
+    if (mfma) {
+        const WholePlan whole = plan_whole(*desc, plan, false);
+        if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, s);
+    }
     const Partials parts{o_parts, lse_parts, w.n_parts, 0, is_16bit(desc->dtype), 1};
     const hipError_t e = mfma ? launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s)
                               : launch_prefix_valu(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, s);
@@ -637,6 +691,8 @@ int ls_hybrid_tree_attn_paged(const ls_desc *desc, const void *q, const void *k_
     if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
+    const WholePlan whole = plan_whole(*desc, plan, true);
+    if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, parents, err, out, lse, parts.o, parts.lse, s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{parents, mask, err}, FusedTail{}, s) != hipSuccess) return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, mask, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)
         return LS_ERR_HIP;
@@ -665,6 +721,8 @@ int ls_cache_attn_paged(const ls_desc *desc, const void *q, const void *k_pages,
     if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
+    const WholePlan whole = plan_whole(*desc, plan, false);
+    if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, nullptr, nullptr, out, lse, parts.o, parts.lse, s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s) != hipSuccess)
         return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, nullptr, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)

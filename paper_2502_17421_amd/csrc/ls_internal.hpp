@@ -99,6 +99,32 @@ struct SplitPlan {
     int32_t reserved;
 };
 
+// n / d for wave-uniform or per-lane n by one multiplication, exact while n * d < 2^32 (the multiplier is
+// ceil(2^32 / d), so the error n * (mul - 2^32/d) / 2^32 stays below 1/d).  d = 1 has no 32-bit
+// multiplier and is a case of its own.  A 32-bit division costs some forty dependent instructions,
+// and the kernels of the small calls did five before their first request (0.8 us).
+struct FastDiv {
+    uint32_t mul, d;
+    static FastDiv of(uint32_t d) { return {d > 1 ? (uint32_t)((0x100000000ull + d - 1) / d) : 0u, d}; }
+    __device__ __forceinline__ uint32_t div(uint32_t n) const { return d > 1 ? __umulhi(n, mul) : n; }
+};
+
+// Outputs of a whole-path call whose kernels take the tree keys as further key tiles (16-bit inputs).
+// n_splits == 1: out and lse are final.  More: partial rows [b, head, tree row, split] in the problem's
+// type with float LSEs; the last split holds the tree keys (parents != nullptr) and writes what
+// rounding took off its rows into the rows of `out`, for merge_parts_kernel to add.
+struct WholeCall {
+    const int32_t *parents;  // nullptr: cached keys only
+    int32_t *err_flag;       // one word per sequence, or nullptr
+    void *out;
+    int64_t o_stride[3];
+    float *lse;
+    void *o_parts;
+    float *lse_parts;
+    int32_t n_splits;
+    FastDiv by_splits, by_tree, by_kv_heads, by_q_heads;  // divisors n_splits, n_tree, n_kv_heads, n_q_heads
+};
+
 // bf16 <-> float on raw 16-bit patterns (round to nearest even, NaN kept quiet).
 __device__ __forceinline__ float bf16_to_float(uint16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 __device__ __forceinline__ uint16_t float_to_bf16(float f)
@@ -193,6 +219,11 @@ hipError_t launch_merge(int32_t batch, int32_t n_q_heads, int32_t n_tree, int32_
 hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, const Partials &cache_parts,
                              int32_t n_cache_parts, void *out, const int64_t o_stride[3], float *lse,
                              hipStream_t stream);
+
+// Whole-path kernel whose waves split the keys (32 * row_tiles query rows per workgroup, 1 or 2).
+hipError_t launch_wave_split(const Problem &p, int dtype, int row_tiles, const WholeCall &w, hipStream_t stream);
+// Merge of the parts of a whole-path call (w.n_splits > 1) into out / lse.
+hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream);
 
 hipError_t launch_tree_accept(const int32_t *parents, const int32_t *draft_tokens, const int32_t *target_tokens,
                               int32_t batch, int32_t n_tree, int32_t *accept_path, int32_t *accept_len,

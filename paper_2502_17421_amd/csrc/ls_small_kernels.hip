@@ -308,4 +308,115 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
     return hipGetLastError();
 }
 
+// --------------------------------------------------------------------- (d), whole path ----
+// Merge of the split rows of a whole-path call whose kernels took the tree keys along (WholeCall): per
+// query row n 16-bit rows side by side, their LSEs, and, when the call has a tree, what rounding took
+// off the last one, in the row of `out` that the merged row replaces.
+//
+// LG = D / 8 lanes hold a row in 16-byte pieces.  WIDE: a wavefront per query row, 64 / LG parts per
+// load instruction; else LG lanes per query row (at most 8 parts).  Every load of a row is issued before
+// the first is used; LSEs and rows come together, so a row costs one round trip.
+template <typename T, int D, bool WIDE>
+__global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w, int rows_total)
+{
+    constexpr int LG = D / 8;
+    constexpr int GROUPS = kWave / LG;                    // parts (WIDE) or query rows per load instruction
+    constexpr int NL = WIDE ? 64 / GROUPS : 8;            // load instructions per pass of at most 64 (8) parts
+    typedef Lanes<T, 8> L8;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    const int group = lane / LG, sl = lane % LG;
+    int r = WIDE ? wave : wave * GROUPS + group;
+    if (WIDE && r >= rows_total) return;
+    const bool live = r < rows_total;
+    r = live ? r : rows_total - 1;
+    const int bh = (int)w.by_tree.div((uint32_t)r), i = r - bh * p.n_tree;
+    const int b = (int)w.by_q_heads.div((uint32_t)bh), h = bh - b * p.n_q_heads;
+    T *orow = (T *)w.out + b * w.o_stride[0] + h * w.o_stride[1] + i * w.o_stride[2] + sl * 8;
+    const T *rows = (const T *)w.o_parts + (size_t)r * w.n_splits * D + sl * 8;
+    const float *lses = w.lse_parts + (size_t)r * w.n_splits;
+
+    float o[8], top = -INFINITY, wsum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = 0.f;
+    RawVec<16> rest{};
+    const int tree_part = w.parents ? w.n_splits - 1 : -1;
+    if (w.parents) rest = load_raw<16>(orow);
+    for (int k0 = 0; k0 < w.n_splits; k0 += WIDE ? 64 : 8) {  // one pass up to 64 (8) parts
+        const int n = w.n_splits - k0 < (WIDE ? 64 : 8) ? w.n_splits - k0 : (WIDE ? 64 : 8);
+        const int mine = WIDE ? lane : sl;                // the part whose LSE this lane holds
+        const float l = mine < n ? lses[k0 + mine] : -INFINITY;
+        RawVec<16> raw[NL];
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            const int part = WIDE ? k * GROUPS + group : k;
+            if (WIDE ? k * GROUPS < n : k < n)            // wave-uniform; past the last part: a valid row, weight 0
+                raw[k] = load_raw<16>(rows + (size_t)(k0 + (part < n ? part : n - 1)) * D);
+        }
+        float t = l;
+#pragma unroll
+        for (int off = WIDE ? 32 : LG / 2; off > 0; off >>= 1) t = fmaxf(t, __shfl_xor(t, off, kWave));
+        const float top_new = fmaxf(top, t);
+        const float scale = top == -INFINITY ? 0.f : exp2f((top - top_new) * kLog2e);
+        wsum *= scale;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] *= scale;
+        top = top_new;
+        const float weight = l == -INFINITY ? 0.f : exp2f((l - top) * kLog2e);
+        wsum += weight;                                   // summed over the lanes at the end
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            if (WIDE ? k * GROUPS < n : k < n) {
+                const int part = WIDE ? k * GROUPS + group : k;
+                const float wk = __shfl(weight, WIDE ? part : group * LG + k, kWave);
+                float v[8];
+                L8::unpack(raw[k], v);
+                if (k0 + part == tree_part) {
+                    float d[8];
+                    L8::unpack(rest, d);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] += d[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] += wk > 0.f ? wk * v[e] : 0.f;  // empty parts may hold anything
+            }
+        }
+    }
+#pragma unroll
+    for (int off = WIDE ? 32 : LG / 2; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off, kWave);
+    if constexpr (WIDE) {
+#pragma unroll
+        for (int off = 32; off >= LG; off >>= 1)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off, kWave);
+    }
+    const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] *= inv;
+    if (live && (!WIDE || group == 0)) {
+        store_raw<16>(orow, L8::pack(o));
+        if (sl == 0) w.lse[r] = wsum > 0.f ? top + log2f(wsum) * kLn2 : -INFINITY;
+    }
+}
+
+hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream)
+{
+    const int rows = p.batch * p.n_q_heads * p.n_tree;
+    const bool wide = w.n_splits > 8;
+    const int rows_per_block = 4 * (wide ? 1 : kWave / (p.head_dim / 8));
+    const dim3 block(256), grid((rows + rows_per_block - 1) / rows_per_block);
+#define LS_MP_CASE(T, DD)                                                                                   \
+    do {                                                                                                    \
+        if (wide) hipLaunchKernelGGL((merge_parts_kernel<T, DD, true>), grid, block, 0, stream, p, w, rows); \
+        else hipLaunchKernelGGL((merge_parts_kernel<T, DD, false>), grid, block, 0, stream, p, w, rows);     \
+    } while (0)
+    if (dtype == LS_BF16 && p.head_dim == 128) LS_MP_CASE(uint16_t, 128);
+    else if (dtype == LS_BF16 && p.head_dim == 64) LS_MP_CASE(uint16_t, 64);
+    else if (dtype == LS_F16 && p.head_dim == 128) LS_MP_CASE(half_t, 128);
+    else if (dtype == LS_F16 && p.head_dim == 64) LS_MP_CASE(half_t, 64);
+    else return hipErrorInvalidValue;
+#undef LS_MP_CASE
+    return hipGetLastError();
+}
+
 }  // namespace ls

@@ -262,11 +262,25 @@ SplitPlan plan_call(const ls_desc &d)
 struct WholePlan {
     int32_t row_tiles;  // > 0: the kernel whose waves split the keys, this many 32-row tiles per workgroup
     int32_t n_splits;   // its key splits; 1: its output is final
+    // the kernel for the cached keys takes the tree keys along and a merge without a tree part follows, if
+    // any (else: the tail kernel does the tree keys and the merge)
+    bool ride;
 };
 
-WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree)
+// Whether q and out share memory (in-place calls: `out` cannot hold remainders while q is still read).
+bool q_overlaps_out(const ls_desc &d, const void *q, const void *out)
 {
-    WholePlan w{0, 0};
+    auto extent = [&](const int64_t s[3]) {
+        return (((int64_t)d.batch - 1) * s[0] + ((int64_t)d.n_q_heads - 1) * s[1] + ((int64_t)d.n_tree - 1) * s[2] + d.head_dim) *
+               (int64_t)elem_size(d.dtype);
+    };
+    const uintptr_t q0 = (uintptr_t)q, o0 = (uintptr_t)out;
+    return q0 < o0 + (uintptr_t)extent(d.o_stride) && o0 < q0 + (uintptr_t)extent(d.q_stride);
+}
+
+WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, const void *q, const void *out)
+{
+    WholePlan w{0, 0, false};
     const int rows_kv = d.n_q_heads / d.n_kv_heads * d.n_tree;
     const int tiles = (d.max_prefix_len + 31) / 32 + (with_tree ? (d.n_tree + 31) / 32 : 0);
     // the ranges in which the kernels' divisions by multiplication are exact
@@ -277,6 +291,15 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree)
         return w;
     // rows of the tree are addressed with 32-bit offsets inside a tile
     if (with_tree && (d.kt_stride[2] >= (1 << 24) || d.vt_stride[2] >= (1 << 24))) return w;
+    if (q_overlaps_out(d, q, out)) return w;
+    // With tree keys on its last split the cached-key kernel of a 64-node tree takes 6 us longer there (two tiles
+    // that nothing overlaps, against 0.6 us per cached tile), which re-cutting the cached keys hides only
+    // where a split is long; the tail kernel takes 3 to 9 us longer than the merge.  Measured, tail kernel against
+    // tree split: 32k keys, 32 tiles per split 53.7 / 50.6 us, 69 nodes x 12k keys, 26 tiles 36.7 / 33.5,
+    // 256 nodes x 32k keys, 128 tiles 138.8 / 136.6; below, splits keep the cut of the stand-alone call.
+    constexpr int kRideSplitLen = 768;
+    w.ride = !with_tree || plan.split_len >= kRideSplitLen;
+    w.n_splits = plan.n_splits;
     // A cache of some 1500 keys is worked through by one workgroup per row tile in less time than the merge
     // of a split call takes (64 rows per KV head, 8 KV heads: 700 keys 11.0 us in one split against 12.9 in
     // two and 18.6 on the kernel that shares tiles between waves; 1600 keys 14.9, 16.3, 19.8).
@@ -286,9 +309,11 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree)
         // against 57.3 us; 64 rows, 32k keys: 34.6 against 35.4; 32 rows, 8k keys: 14.2 against 20.6)
         w.row_tiles = rows_kv <= 32 ? 1 : 2;
         w.n_splits = tiles <= kDirectTiles ? 1 : plan.n_splits;
+        w.ride = true;
     } else if (tiles <= kDirectTiles) {
         w.row_tiles = 1;
         w.n_splits = 1;
+        w.ride = true;
     }
     return w;
 }
@@ -433,15 +458,27 @@ int ls_lse_merge(const ls_desc *desc, int32_t n_parts, int32_t part_dtype, const
 }  // extern "C"
 
 namespace {
-// Whole-path call on the kernel whose waves split the keys, and the merge if there is more than one split.
-int run_wave_split(const ls_desc &d, const Problem &p, const WholePlan &plan, const int32_t *parents, int32_t *err,
-                   void *out, float *lse, void *o_parts, float *lse_parts, hipStream_t s)
+// Whole-path call whose tree keys are taken along by the kernel for the cached keys, and the merge of the
+// parts unless a single split's output is final.
+int run_whole(const ls_desc &d, const Problem &p, const SplitPlan &splits, const WholePlan &plan, const int32_t *parents,
+              int32_t *err, void *out, float *lse, void *o_parts, float *lse_parts, hipStream_t s)
 {
     WholeCall w{parents, err, out, {d.o_stride[0], d.o_stride[1], d.o_stride[2]}, lse, o_parts, lse_parts, plan.n_splits,
                 FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads)};
-    if (launch_wave_split(p, d.dtype, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
-    if (plan.n_splits > 1 && launch_merge_parts(p, d.dtype, w, s) != hipSuccess) return LS_ERR_HIP;
-    return LS_OK;
+    if (plan.row_tiles > 0) {
+        if (launch_wave_split(p, d.dtype, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
+        if (plan.n_splits == 1) return LS_OK;
+    } else {
+        const Partials parts{o_parts, lse_parts, plan.n_splits, 0, 1, 1};
+        FusedTail tail{};
+        tail.parents = parents;
+        tail.out = out;
+        for (int i = 0; i < 3; ++i) tail.o_stride[i] = d.o_stride[i];
+        tail.err_flag = err;
+        if (launch_prefix_mfma(p, d.dtype, splits, parts, MaskJob{nullptr, nullptr, nullptr}, tail, s) != hipSuccess)
+            return LS_ERR_HIP;
+    }
+    return launch_merge_parts(p, d.dtype, w, s) == hipSuccess ? LS_OK : LS_ERR_HIP;
 }
 
 // The whole path for a contiguous cache.  prefix_lens: device array, or nullptr with every
@@ -471,8 +508,8 @@ int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, c
     Problem p = make_problem(*desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree);
     p.prefix_len_all = prefix_len_all;
     if (prefix_mfma_supports(p, desc->dtype) && !single_launch) {
-        const WholePlan whole = plan_whole(*desc, plan, true);
-        if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, parents, err, out, lse, o_parts, lse_parts, s);
+        const WholePlan whole = plan_whole(*desc, plan, true, q, out);
+        if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, o_parts, lse_parts, s);
     }
 
     // (b) cached keys -> parts [0, n_splits), stored in the problem's dtype; on the MFMA path
@@ -598,8 +635,8 @@ int ls_cache_attn(const ls_desc *desc, const void *q, const void *k_cache, const
     const bool mfma = prefix_mfma_supports(p, desc->dtype);
     if (!mfma && is_16bit(desc->dtype)) return LS_ERR_UNSUPPORTED;
     if (mfma) {
-        const WholePlan whole = plan_whole(*desc, plan, false);
-        if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, s);
+        const WholePlan whole = plan_whole(*desc, plan, false, q, out);
+        if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, s);
     }
     const Partials parts{o_parts, lse_parts, w.n_parts, 0, is_16bit(desc->dtype), 1};
     const hipError_t e = mfma ? launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s)
@@ -691,8 +728,8 @@ int ls_hybrid_tree_attn_paged(const ls_desc *desc, const void *q, const void *k_
     if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
-    const WholePlan whole = plan_whole(*desc, plan, true);
-    if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, parents, err, out, lse, parts.o, parts.lse, s);
+    const WholePlan whole = plan_whole(*desc, plan, true, q, out);
+    if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, parts.o, parts.lse, s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{parents, mask, err}, FusedTail{}, s) != hipSuccess) return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, mask, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)
         return LS_ERR_HIP;
@@ -721,8 +758,8 @@ int ls_cache_attn_paged(const ls_desc *desc, const void *q, const void *k_pages,
     if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
-    const WholePlan whole = plan_whole(*desc, plan, false);
-    if (whole.row_tiles > 0) return run_wave_split(*desc, p, whole, nullptr, nullptr, out, lse, parts.o, parts.lse, s);
+    const WholePlan whole = plan_whole(*desc, plan, false, q, out);
+    if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, parts.o, parts.lse, s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s) != hipSuccess)
         return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, nullptr, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)

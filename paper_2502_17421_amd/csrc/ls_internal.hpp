@@ -76,7 +76,8 @@ struct MaskJob {
 // the merge for them; the workgroup that completed the count then claims every slice still free
 // (workgroups that gave up, or all of them when spin_limit is 0) and does those too.  So every
 // row is written exactly once, by the same code whoever writes it, and no wait is unbounded.
-// counters == nullptr: the kernel only writes its partial rows.
+// counters == nullptr: the kernel only writes its partial rows; those of the last split include the
+// tree keys if parents != nullptr (see WholeCall; out takes what rounding took off them).
 struct FusedTail {
     uint64_t *counters;  // three words per (sequence, KV head, query block); zero before the first call
     const int32_t *parents;
@@ -84,6 +85,7 @@ struct FusedTail {
     int64_t o_stride[3];
     float *lse;
     int32_t spin_limit;  // polls (about half a microsecond apart) before a workgroup leaves its slice to the last one
+    int32_t *err_flag;   // (tree keys of the last split) one word per sequence, or nullptr
 };
 constexpr int kMaxArrivalCounters = 4096;  // (sequence, KV head, query block) triples one single-launch call may have
 constexpr int kCounterWords = 3;           // 64-bit words per triple

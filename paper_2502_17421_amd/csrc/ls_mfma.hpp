@@ -113,6 +113,125 @@ __device__ __forceinline__ int vswz(int row)
     return (((k >> 1) << 2) | ((k & 1) << 1) | (k >> 1)) << 1;
 }
 
+// the two values of a packed pair
+template <bool F16> __device__ __forceinline__ float low16(uint32_t u)
+{
+    return F16 ? half_to_float((uint16_t)u) : __uint_as_float(u << 16);
+}
+template <bool F16> __device__ __forceinline__ float high16(uint32_t u)
+{
+    return F16 ? half_to_float((uint16_t)(u >> 16)) : __uint_as_float(u & 0xffff0000u);
+}
+
+// what rounding x to `rounded` took off (nothing if the result is not finite)
+__device__ __forceinline__ float rounding_rest(float x, float rounded)
+{
+    const float r = x - rounded;
+    return fabsf(r) < INFINITY ? r : 0.f;
+}
+
+// ---- tree keys on the matrix cores ------------------------------------------------------------
+// A tree tile holds 32 nodes; a row sees a node when it is an ancestor of the row's own node or that
+// node itself.  Numerators of tree keys keep twice the operand type's significant bits (a second
+// output product with the rounding remainders): the few tree keys may carry most of a row's weight.
+
+// Ancestors of node `lane` (itself included) as a 64-bit mask, for trees of at most 64 nodes: every
+// round doubles the reach of every node.  anc: the node's parent, valid or -1; all 64 lanes active.
+__device__ __forceinline__ uint2 ancestor_mask(int anc, int lane)
+{
+    uint32_t lo = lane < 32 ? 1u << lane : 0u, hi = lane < 32 ? 0u : 1u << (lane - 32);
+    while (__any(anc >= 0)) {
+        const int src = (anc < 0 ? lane : anc) * 4;
+        const uint32_t lo2 = __builtin_amdgcn_ds_bpermute(src, lo), hi2 = __builtin_amdgcn_ds_bpermute(src, hi);
+        const int anc2 = __builtin_amdgcn_ds_bpermute(src, anc);
+        if (anc >= 0) {
+            lo |= lo2;
+            hi |= hi2;
+            anc = anc2;
+        }
+    }
+    return make_uint2(lo, hi);
+}
+
+// The mask word of tree tile `tt` (bit k: node 32*tt + k) of a chain walked in LDS (entries -1 or
+// smaller than their index): takes the nodes of that tile off the chain.  Tiles are visited from the
+// last one down, as the chain does.
+__device__ __forceinline__ uint32_t take_chain_word(const int32_t *par, int &node, int tt)
+{
+    uint32_t bits = 0;
+    while (node >= tt * 32) {
+        bits |= 1u << (node & 31);
+        node = par[node];
+    }
+    return bits;
+}
+
+// Numerators of a tree tile: rounded to the operand type (hi), and what the rounding took off (lo).
+// m_run: the reference exponent, -inf while the row has seen no key (all scores are -inf then).
+template <bool F16>
+__device__ __forceinline__ float tree_numerators(const floatx16 &s, float c, float m_run, uint32_t (&hi)[8],
+                                                 uint32_t (&lo)[8])
+{
+    const float mc = m_run == -INFINITY ? 0.f : m_run * c;
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -mc));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], c, -mc));
+        sum += p0 + p1;
+        const uint32_t u = pack16<F16>(p0, p1);
+        hi[e >> 1] = u;
+        lo[e >> 1] = pack16<F16>(p0 - low16<F16>(u), p1 - high16<F16>(u));
+    }
+    return sum;
+}
+
+// Infinite and NaN values of a node must not reach rows that do not see it, but a matrix product carries
+// them there (0 * inf).  drop_not_finite replaces them by zeros in the fragments and says whether there were
+// any (wave-uniform); if so, add_not_finite puts those of a visible node into the row at the end.
+template <bool F16, int N> __device__ __forceinline__ bool drop_not_finite(bf16x8 (&frag)[N])
+{
+    typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+    constexpr uint32_t kMagnitude = 0x7fff7fffu, kInf = F16 ? 0x7c00u : 0x7f80u;
+    ushortx2 top = {0, 0};
+#pragma unroll
+    for (int f = 0; f < N; ++f) {
+        const uint4 v = __builtin_bit_cast(uint4, frag[f]);
+        top = __builtin_elementwise_max(top, __builtin_bit_cast(ushortx2, v.x & kMagnitude));
+        top = __builtin_elementwise_max(top, __builtin_bit_cast(ushortx2, v.y & kMagnitude));
+        top = __builtin_elementwise_max(top, __builtin_bit_cast(ushortx2, v.z & kMagnitude));
+        top = __builtin_elementwise_max(top, __builtin_bit_cast(ushortx2, v.w & kMagnitude));
+    }
+    if (!__any(top.x >= kInf || top.y >= kInf)) return false;
+    auto drop = [](uint32_t x) __attribute__((always_inline)) {
+        return ((x & 0x7fffu) >= kInf ? 0u : x & 0xffffu) | ((x >> 16 & 0x7fffu) >= kInf ? 0u : x & 0xffff0000u);
+    };
+#pragma unroll
+    for (int f = 0; f < N; ++f) {
+        const uint4 v = __builtin_bit_cast(uint4, frag[f]);
+        frag[f] = __builtin_bit_cast(bf16x8, make_uint4(drop(v.x), drop(v.y), drop(v.z), drop(v.w)));
+        __builtin_amdgcn_sched_barrier(0);  // few temporaries: the kernels have no registers to spare
+    }
+    return true;
+}
+
+// v_row: the node's value row in global memory; o: the output columns of a lane in half-wave lh.
+template <bool F16, int MT>
+__device__ __forceinline__ void add_not_finite(floatx16 (&o)[MT], const uint8_t *v_row, int lh)
+{
+    constexpr uint32_t kInf = F16 ? 0x7c00u : 0x7f80u;
+#pragma unroll
+    for (int n = 0; n < 4 * MT; ++n) {  // 16-byte chunk n of the row, this half-wave's four elements
+        const uint2 x = *(const uint2 *)(v_row + n * 16 + lh * 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t pair = i < 2 ? x.x : x.y;
+            const bool bad = ((i & 1 ? pair >> 16 : pair) & 0x7fffu) >= kInf;
+            o[n / 4][4 * (n % 4) + i] += bad ? (i & 1 ? high16<F16>(pair) : low16<F16>(pair)) : 0.f;
+        }
+    }
+}
+
 }  // namespace
 
 }  // namespace ls

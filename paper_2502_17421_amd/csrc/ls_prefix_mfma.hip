@@ -51,6 +51,13 @@
 // a larger sum (scores far above everything before) redoes that step on the general path,
 // which raises m and rescales O and l.
 //
+// Tree keys.  In a whole-path call whose splits are long the last split takes the keys of the tree along,
+// before its cached keys, in LDS stages that the first window of cached tiles leaves free, and the call ends
+// with a merge alone instead of the tail kernel (32k keys, 64 nodes: tail 11.7 us, merge 7.6; 640 rows per KV
+// head in four sequences: 20.8 and 11.9).  A tree tile is not pipelined (about 2 us against 0.6 for a cached one:
+// mask, score product, softmax, output product of the numerators and of their rounding remainders, one
+// after the other in all waves), so that split gets fewer cached tiles.
+//
 // MFMA operand layouts: ls_mfma.hpp.
 #include <type_traits>
 
@@ -71,6 +78,10 @@ constexpr int TK = 32;              // keys per tile = keys per pipeline step (o
 // compute unit holds anyway.
 constexpr int kDeepRequests = 6, kShallowRequests = 3;
 constexpr int kDeepMaxTiles = 16;   // splits of at most this many tiles take the deep window
+constexpr int kTreeRound = 3;       // tree tiles in LDS at a time (the stages the first window leaves free)
+// Cached tiles the last split gets less per tree tile (measured with 0, 1 and 3: 256 nodes x 32k keys, eight
+// splits, 145.8 / 141.3 / 137.0 us).
+constexpr int kTreeTileCost = 3;
 constexpr float kLazy = 8.f;        // general path: m is raised only when a score exceeds it by 2^8
 // common path: largest row-sum increment taken without raising m; the numerators are stored in
 // the operand type, and a half holds nothing above 65504
@@ -78,7 +89,9 @@ template <bool F16> constexpr float kSumCap = F16 ? 0x1p15f : 0x1p40f;
 
 }  // namespace
 
-template <int D, int NW, bool F16, bool PAGED, int PD>
+// FUSED: the single-launch call (contiguous caches only).  A form of its own: what it needs at the end would
+// otherwise be kept over the key loop (180 scalar registers spilled to vector lanes, against 20).
+template <int D, int NW, bool F16, bool PAGED, int PD, bool FUSED>
 __global__ void __launch_bounds__(NW * 64, 2048 / (NW * 64) / 4)  // at most 256 registers per lane: no AGPR copies
 prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, FusedTail tail, int32_t n_qblocks)
 {
@@ -136,10 +149,22 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     int plen = p.prefix_lens ? p.prefix_lens[b] : p.prefix_len_all;
     plen = plen < 0 ? 0 : (plen > p.max_prefix_len ? p.max_prefix_len : plen);
     int split_len = plan.split_len;
-    if (plan.per_sequence) split_len = ((plen + plan.n_splits - 1) / plan.n_splits + TK - 1) / TK * TK;
-    const int k_lo = split * split_len;
-    int k_hi = k_lo + split_len;
+    // Whole-path call: the last split also takes the tree keys, and as many cached tiles less as they
+    // cost (a tree tile has the output product of the rounding remainders as well and is not pipelined).
+    const bool with_tree = !FUSED && tail.parents != nullptr;
+    const bool tree_split = with_tree && split == plan.n_splits - 1;
+    const int tree_tiles = tree_split ? (p.n_tree + TK - 1) / TK : 0;
+    if (plan.per_sequence) {
+        const int cost = with_tree ? kTreeTileCost * ((p.n_tree + TK - 1) / TK) : 0;
+        int per_split = ((plen + TK - 1) / TK + cost + plan.n_splits - 1) / plan.n_splits;
+        if (with_tree) per_split += per_split & 1;  // tiles go in pairs: 17 take as long as 18
+        per_split = per_split < kMaxSplitLen / TK ? per_split : kMaxSplitLen / TK;
+        split_len = per_split * TK;
+    }
+    int k_lo = split * split_len;
+    int k_hi = tree_split ? plen : k_lo + split_len;
     k_hi = k_hi > plen ? plen : k_hi;
+    k_lo = k_lo < k_hi ? k_lo : k_hi;
 
     // The query row of this lane.
     const int wave_row0 = (qblock * NW + wave) * 32;
@@ -149,9 +174,9 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     const int ti = q_ok ? m_row % p.n_tree : 0;
     const size_t part_row = out.row((size_t)b * p.n_q_heads + hq, split, p.n_tree, ti);
 
-    if (k_lo >= k_hi) {  // empty split: weight zero in the merge
+    if (k_lo >= k_hi && !tree_split) {  // empty split: weight zero in the merge
         if (lh == 0 && q_ok) {
-            if (tail.counters == nullptr) out.lse[part_row] = -INFINITY;
+            if constexpr (!FUSED) out.lse[part_row] = -INFINITY;
             else __hip_atomic_store(out.lse + part_row, -INFINITY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return;
@@ -166,6 +191,17 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk)
         asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(q_raw[kk]) : "v"(q_ptr + kk * 16 + lh * 8) : "memory");
+
+    // Parents of the tree, node 64 * (wave + NW * i) + lane in entry i, to LDS once they are here.  (Loaded on
+    // every path, from a valid address, so that the registers are written by one instruction.)
+    int32_t par_raw[LS_MAX_TREE / 64 / NW];
+#pragma unroll
+    for (int i = 0; i < LS_MAX_TREE / 64 / NW; ++i) {
+        const int node = (wave + NW * i) * 64 + lane;
+        const int32_t *src = tree_split ? tail.parents + (size_t)b * p.n_tree + (node < p.n_tree ? node : p.n_tree - 1)
+                                        : (const int32_t *)q_ptr;
+        asm volatile("global_load_dword %0, %1, off" : "=v"(par_raw[i]) : "v"(src) : "memory");
+    }
 
     // ---- HBM -> LDS tile loads ----------------------------------------------------------
     const uint8_t *kbase = uniform_ptr((const uint8_t *)p.k_cache + (b * p.kc_stride[0] + g * p.kc_stride[1]) * 2);
@@ -255,12 +291,35 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         }
     };
 
+    // Tree keys, up to kTreeRound tiles at a time, the last nodes first: tile j of a round has its K rows in
+    // stage 2j and its V rows in stage 2j + 1 of those that the first window of cached tiles leaves free
+    // (K stages PD+1, PD+2 and V stages PD .. PD+3: none is requested before advance0, below).
+    auto tree_stage = [&](int i) __attribute__((always_inline)) -> uint32_t {
+        return i < 2 ? (uint32_t)((PD + 1 + i) * TILEB) : V_RING + (uint32_t)((PD + i - 2) * TILEB);
+    };
+    auto request_tree = [&](int top) __attribute__((always_inline)) {  // tiles top - 1, top - 2, .. (every wave copies)
+        const int n = top < kTreeRound ? top : kTreeRound;
+        for (int i = wave; i < n * 2 * TPT; i += NW) {
+            const int j = i / (2 * TPT), is_v = (i / TPT) & 1, row0 = (i % TPT) * ROWS_PER_LOAD;
+            const int first = (top - 1 - j) * TK, last = p.n_tree - 1 - first;
+            const int row = row0 + ld_row;
+            const int64_t row_bytes = 2 * (is_v ? p.vt_stride[2] : p.kt_stride[2]);
+            const uint8_t *base = uniform_ptr((is_v ? (const uint8_t *)p.v_tree + (b * p.vt_stride[0] + g * p.vt_stride[1]) * 2
+                                                    : (const uint8_t *)p.k_tree + (b * p.kt_stride[0] + g * p.kt_stride[1]) * 2) +
+                                              first * row_bytes);
+            const int swz = (is_v ? vswz(row) : row) & (CH - 1);
+            copy_to_lds(base, (uint32_t)((row < last ? row : last) * (int)row_bytes) + (ld_pos ^ swz) * 16,
+                        __builtin_amdgcn_readfirstlane(smem_off + tree_stage(2 * j + is_v) + row0 * ROWB));
+        }
+    };
+    if (tree_split) request_tree(tree_tiles);
+
     const int n_tiles = (k_hi - k_lo + TK - 1) / TK;
     // Tile order: the softmax does not care in which order keys arrive, so split s starts at
     // its tile (s mod n_tiles) and wraps around.  All workgroups start together; with every
     // split reading from its first row their addresses would differ by multiples of the split
     // size only and crowd a few memory channels.
-    const int key_first = k_lo + (split % n_tiles) * TK;  // first key of tile 0
+    const int key_first = k_lo + (n_tiles > 0 ? split % n_tiles : 0) * TK;  // first key of tile 0
     const int key_wrap = k_lo + n_tiles * TK;
     auto next_key0 = [&](int k0) __attribute__((always_inline)) { return k0 + TK == key_wrap ? k_lo : k0 + TK; };
     auto next_k = [&](uint32_t off) __attribute__((always_inline)) { return off + TILEB == KS * TILEB ? 0u : off + TILEB; };
@@ -312,6 +371,28 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         const u32x4 v = q_ok ? q_raw[kk] : u32x4{0, 0, 0, 0};
         q_reg[kk] = __builtin_bit_cast(bf16x8, v);
     }
+    int32_t *par_lds = (int32_t *)(smem + PAGE_TAB + (PAGED ? kMaxSplitPages * 4 : 0));  // then two words per wave
+    bool bad_parent = false;
+#pragma unroll
+    for (int i = 0; i < LS_MAX_TREE / 64 / NW; ++i) {
+        asm volatile("" : "+v"(par_raw[i]));
+        const int node = (wave + NW * i) * 64 + lane;
+        if (tree_split && node < p.n_tree) {
+            int pa = par_raw[i];
+            if (pa < -1 || pa >= node) {  // not a forest in topological order: treat the node as a root
+                bad_parent = true;
+                pa = -1;
+            }
+            par_lds[node] = pa;
+        }
+    }
+    if (tree_split) {  // wave-uniform
+        const bool any_bad = __any(bad_parent);
+        if (lane == 0) par_lds[LS_MAX_TREE + wave] = any_bad;
+    }
+    // What the end of the kernel has to know (kept here, the loop has no scalar registers to spare): 0 no tree keys,
+    // 1 tree keys, 2 infinities or NaN among their values.
+    par_lds[LS_MAX_TREE + NW + wave] = tree_split ? 1 : 0;
 
     floatx16 o_acc[MT];
 #pragma unroll
@@ -398,12 +479,6 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     floatx16 s_sl[2];
     uint32_t p_sl[2][8];
     float mc = 0.f;
-#pragma unroll
-    for (int f = 0; f < FS; ++f) v_frag[f] = k_frag[f] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p_sl[x][e] = 0;  // an output product of zeros adds nothing
 
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
@@ -495,7 +570,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     using X0 = std::integral_constant<int, 0>;
     using X1 = std::integral_constant<int, 1>;
 
-    __syncthreads();  // the K rows of tile 0 are complete in LDS
+    __syncthreads();  // the K rows of tile 0 and the first tree tiles are complete in LDS
     // Before half-step 1 (which reads K rows of tile 1): request -PD has landed, for this wave and
     // then for everybody; request 0 follows.
     auto advance0 = [&]() __attribute__((always_inline)) {
@@ -559,16 +634,80 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
             request_v(true);
         }
     };
+    // Tree keys: attention of this wave's rows over the nodes they see, before the cached keys (whose first
+    // window arrives meanwhile).
+    const bool has_rows = wave_row0 < rows_kv;
+    if (tree_split) {
+        uint64_t vis = 0;                // up to 64 nodes: the nodes this lane's row sees
+        int chain = q_ok ? ti : -1;      // more: the rest of the chain
+        if (has_rows && p.n_tree <= 64) {
+            const uint2 mask = ancestor_mask(lane < p.n_tree ? par_lds[lane] : -1, lane);
+            vis = (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(ti * 4, mask.x) |
+                  ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(ti * 4, mask.y) << 32);
+        }
+        if (tid == 0 && g == 0 && qblock == 0 && tail.err_flag) {
+            int any_bad = 0;
+            for (int i = 0; i < NW; ++i) any_bad |= par_lds[LS_MAX_TREE + i];
+            tail.err_flag[b] = any_bad;
+        }
+        for (int top = tree_tiles; top > 0; top -= kTreeRound) {  // the tiles of this round: top - 1 and down
+            if (top < tree_tiles) {
+                ring_barrier();  // every wave is done with the previous round's stages
+                request_tree(top);
+                wait_vmem<0>();
+                ring_barrier();
+            }
+            for (int j = 0; has_rows && j < kTreeRound && j < top; ++j) {
+                const int tt = top - 1 - j;
+                const uint32_t word = p.n_tree <= 64 ? (uint32_t)(vis >> (32 * tt)) : take_chain_word(par_lds, chain, tt);
+                if (!__any(word != 0)) continue;
+                const uint32_t k_at = tree_stage(2 * j) + k_off0, v_at = tree_stage(2 * j + 1) + v_off0;
+                floatx16 s;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) s[e] = 0.f;
+                bf16x8 frag[KSTEPS];
+#pragma unroll
+                for (int kk = 0; kk < KSTEPS; ++kk) frag[kk] = read_k(k_at, kk);
+#pragma unroll
+                for (int kk = 0; kk < KSTEPS; ++kk) s = mfma32<F16>(frag[kk], q_reg[kk], s);
+                const uint32_t seen = word >> (4 * lh);
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (!((seen >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
+                raise_reference(s);
+                uint32_t hi[8], lo[8];
+                l_run += tree_numerators<F16>(s, c, m_run, hi, lo);
+#pragma unroll
+                for (int f = 0; f < KSTEPS; ++f) frag[f] = read_v(v_at, f);
+                if (drop_not_finite<F16>(frag)) par_lds[LS_MAX_TREE + NW + wave] = 2;
+#pragma unroll
+                for (int f = 0; f < KSTEPS; ++f)
+                    o_acc[f % MT] = mfma32<F16>(frag[f], __builtin_bit_cast(bf16x8, make_uint4(hi[4 * (f / MT)], hi[4 * (f / MT) + 1],
+                                                                                               hi[4 * (f / MT) + 2], hi[4 * (f / MT) + 3])), o_acc[f % MT]);
+#pragma unroll
+                for (int f = 0; f < KSTEPS; ++f)
+                    o_acc[f % MT] = mfma32<F16>(frag[f], __builtin_bit_cast(bf16x8, make_uint4(lo[4 * (f / MT)], lo[4 * (f / MT) + 1],
+                                                                                               lo[4 * (f / MT) + 2], lo[4 * (f / MT) + 3])), o_acc[f % MT]);
+            }
+        }
+    }
     // A wave whose rows all lie past the last query row of the KV head (the last query block of a
     // head whose row count is not a multiple of the block) only keeps feeding the rings: its
     // share of every tile, and every barrier of the code below.
-    if (wave_row0 >= rows_kv) {
+    if (!has_rows) {
         advance0();
         for (int h = 1; h + 1 < n_tiles; h += 2) advance_pair(h);
         __syncthreads();
         return;
     }
 
+    if (n_tiles > 0) {
+#pragma unroll
+    for (int f = 0; f < FS; ++f) v_frag[f] = k_frag[f] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p_sl[x][e] = 0;  // an output product of zeros adds nothing
     // scores of step 0 and the reference exponent
     {
         bf16x8 k0f[KSTEPS];
@@ -580,7 +719,9 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         for (int kk = 0; kk < KSTEPS; ++kk) s_sl[0] = mfma32<F16>(k0f[kk], q_reg[kk], s_sl[0]);
     }
     if (key_first + TK > k_hi) mask_tail(s_sl[0], key_first);
-    {  // the reference exponent: the largest of the first 32 scores (at least one key is valid)
+    if (tree_split) {
+        raise_reference(s_sl[0]);
+    } else {  // the reference exponent: the largest of the first 32 scores (at least one key is valid)
         float mx = s_sl[0][0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s_sl[0][e]);
@@ -628,6 +769,12 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     half_step(X0{}, no{}, yes{}, no{}, yes{}, 0, 0, v_cur, v_nxt);  // output h-1; softmax h
     step_on();
     half_step(X1{}, no{}, no{}, no{}, no{}, 0, 0, v_cur, 0);       // output h
+    }
+
+    const int tree_state = __builtin_amdgcn_readfirstlane(par_lds[LS_MAX_TREE + NW + wave]);
+    if (tree_state == 2)
+        for (int node = q_ok ? ti : -1; node >= 0; node = par_lds[node])
+            add_not_finite<F16>(o_acc, (const uint8_t *)p.v_tree + (b * p.vt_stride[0] + g * p.vt_stride[1] + node * p.vt_stride[2]) * 2, lh);
 
     // ---- epilogue: normalise and store this split's partial result -----------------------
     __syncthreads();  // every wave is done reading tiles: the rings are free
@@ -662,7 +809,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
             // streaming stores: whole rows that nobody on this compute unit reads again; they leave
             // the L2 as they are written instead of in one burst when the kernel ends
             uint16_t *dst = (uint16_t *)out.o + (size_t)prow * D + cpos * 8;
-            if (ok && tail.counters == nullptr) {
+            if (!FUSED && ok) {
                 __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, (u32x4 *)dst);
             } else if (ok) {
                 // single-launch call: device-scope stores, complete in the memory all XCDs share when
@@ -671,6 +818,32 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
                                    __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store((uint64_t *)dst + 1, (uint64_t)v.z | ((uint64_t)v.w << 32), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (tree_state) {
+            // what the rounding took off these rows: into the rows of `out`, the same way
+            const int64_t o_off = (int64_t)b * tail.o_stride[0] + hq * tail.o_stride[1] + ti * tail.o_stride[2];
+            auto rest = [&](float x) __attribute__((always_inline)) {
+                return rounding_rest(x, low16<F16>(pack16<F16>(x, x)));
+            };
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) {
+                    uint2 v;
+                    v.x = pack16<F16>(rest(o_acc[mt][4 * rg + 0] * inv), rest(o_acc[mt][4 * rg + 1] * inv));
+                    v.y = pack16<F16>(rest(o_acc[mt][4 * rg + 2] * inv), rest(o_acc[mt][4 * rg + 3] * inv));
+                    const int chunk = (4 * mt + rg) ^ (li & (CH - 1));
+                    *(uint2 *)(mine + li * ROWB + chunk * 16 + lh * 8) = v;
+                }
+#pragma unroll
+            for (int j = 0; j < 32 / ROWS_PER_STORE; ++j) {
+                const int row = j * ROWS_PER_STORE + lane / CH;
+                const int cpos = lane % CH;
+                const uint4 v = *(const uint4 *)(mine + row * ROWB + ((cpos ^ (row & (CH - 1))) * 16));
+                const uint32_t lo = __shfl((uint32_t)o_off, row), hi = __shfl((uint32_t)((uint64_t)o_off >> 32), row);
+                const int ok = __shfl((int)q_ok, row);
+                if (ok) *(uint4 *)((uint16_t *)tail.out + (int64_t)(((uint64_t)hi << 32) | lo) + cpos * 8) = v;
             }
         }
         if (!q_ok) return;
@@ -691,12 +864,12 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     }
     if (lh == 0) {
         const float lse_part = (m_run * c + log2f(l_tot)) * kLn2;
-        if (tail.counters == nullptr) out.lse[part_row] = lse_part;
+        if constexpr (!FUSED) out.lse[part_row] = lse_part;
         else __hip_atomic_store(out.lse + part_row, lse_part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     }();
 
-    if (tail.counters == nullptr) return;
+    if constexpr (!FUSED) return;
     // ---- single-launch call (protocol: see FusedTail).  Memory order: the partial rows and LSEs
     // were written with device-scope stores; once a wave's store counter is at zero they are in the
     // memory all XCDs share, so after the barrier a relaxed count says that this workgroup's rows
@@ -810,13 +983,13 @@ bool prefix_mfma_supports(const Problem &p, int dtype)
 
 namespace {
 
-template <int D, int NW, bool F16, bool PAGED, int PD>
-hipError_t launch_one(const Problem &p, const SplitPlan &plan, const Partials &out, const MaskJob &mask_job,
+template <int D, int NW, bool F16, bool PAGED, int PD, bool FUSED>
+hipError_t launch_form(const Problem &p, const SplitPlan &plan, const Partials &out, const MaskJob &mask_job,
                       const FusedTail &tail, hipStream_t stream)
 {
-    constexpr int lds_bytes = (2 * PD + 7) * TK * D * 2 + (PAGED ? kMaxSplitPages * 4 : 0);
+    constexpr int lds_bytes = (2 * PD + 7) * TK * D * 2 + (PAGED ? kMaxSplitPages * 4 : 0) + (LS_MAX_TREE + 2 * NW) * 4;
     static_assert(lds_bytes <= 160 * 1024, "the rings exceed the 160 KB of a compute unit");
-    auto kernel = prefix_mfma_kernel<D, NW, F16, PAGED, PD>;
+    auto kernel = prefix_mfma_kernel<D, NW, F16, PAGED, PD, FUSED>;
     static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  lds_bytes);
     if (attr != hipSuccess) return attr;
@@ -825,12 +998,21 @@ hipError_t launch_one(const Problem &p, const SplitPlan &plan, const Partials &o
     const int64_t n_main = (int64_t)plan.n_splits * n_qblocks * p.batch * p.n_kv_heads;
     const int64_t n_blocks = n_main + (mask_job.parents ? p.batch : 0);
     if (n_blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if (tail.counters && (!out.o_is_16bit || plan.n_splits > 64 ||
+    if (FUSED && (!out.o_is_16bit || plan.n_splits > 64 ||
                           (int64_t)n_qblocks * p.batch * p.n_kv_heads > kMaxArrivalCounters))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_blocks), dim3(NW * 64), lds_bytes, stream, p, plan, out, mask_job,
                        tail, n_qblocks);
     return hipGetLastError();
+}
+
+template <int D, int NW, bool F16, bool PAGED, int PD>
+hipError_t launch_one(const Problem &p, const SplitPlan &plan, const Partials &out, const MaskJob &mask_job,
+                      const FusedTail &tail, hipStream_t stream)
+{
+    if (!tail.counters) return launch_form<D, NW, F16, PAGED, PD, false>(p, plan, out, mask_job, tail, stream);
+    if constexpr (PAGED) return hipErrorInvalidValue;
+    else return launch_form<D, NW, F16, false, PD, true>(p, plan, out, mask_job, tail, stream);
 }
 
 }  // namespace

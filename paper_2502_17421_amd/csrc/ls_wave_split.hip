@@ -271,8 +271,7 @@ wave_split_kernel(WaveArgs a)
     asm volatile("" : "+v"(par_reg));
 
     // ---- tree mask ---------------------------------------------------------------------------------
-    int32_t *par_lds = (int32_t *)(smem + PAR_OFF);
-    uint64_t vis[RT];  // up to 64 nodes: the ancestors of this lane's query rows, themselves included
+    int32_t *par_lds = (int32_t *)(smem + PAR_OFF);  // parents; up to 64 nodes: the mask of every node instead
     bool bad_parent = false;
     const bool tree_wave = has_tree && busy && n_all > n_pref && wave + ((n_all - 1 - wave) / NW) * NW >= n_pref;
     if (tree_wave) {  // wave-uniform
@@ -286,24 +285,8 @@ wave_split_kernel(WaveArgs a)
             } else {
                 anc = -1;
             }
-            uint32_t lo = lane < 32 ? 1u << lane : 0u, hi = lane < 32 ? 0u : 1u << (lane - 32);
-            while (__any(anc >= 0)) {  // every round doubles the ancestors a node knows
-                const int src = (anc < 0 ? lane : anc) * 4;
-                const uint32_t lo2 = __builtin_amdgcn_ds_bpermute(src, lo), hi2 = __builtin_amdgcn_ds_bpermute(src, hi);
-                const int anc2 = __builtin_amdgcn_ds_bpermute(src, anc);
-                if (anc >= 0) {
-                    lo |= lo2;
-                    hi |= hi2;
-                    anc = anc2;
-                }
-            }
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const int m = row_of(row0 + rt * 32 + li);
-                const int ti = m - (int)a.by_tree.div((uint32_t)m) * a.n_tree;
-                vis[rt] = (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(ti * 4, lo) |
-                          ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(ti * 4, hi) << 32);
-            }
+            const uint2 mask = ancestor_mask(anc, lane);
+            ((uint2 *)par_lds)[lane] = mask;  // (every wave that needs it writes the same values)
         } else {
             // every wave that needs the array writes all of it: the waves write the same values
             for (int i = lane; i < a.n_tree; i += 64) {
@@ -352,17 +335,18 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) asm volatile("" : "+v"(frag[kk]));  // in registers: the stage is free
     };
+    auto read_v = [&](uint32_t off, int f) __attribute__((always_inline)) {  // f = 16-key half * MT + d tile
+        const uint32_t a = (off ^ (uint32_t)((f % MT) << 6)) + ((f / MT) * 16) * ROWB;
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)a);
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(a + 8 * ROWB));
+        const uint2 lo2 = __builtin_bit_cast(uint2, lo), hi2 = __builtin_bit_cast(uint2, hi);
+        return __builtin_bit_cast(bf16x8, make_uint4(lo2.x, lo2.y, hi2.x, hi2.y));
+    };
     auto read_v_tile = [&](bf16x8 (&frag)[KSTEPS]) __attribute__((always_inline)) {
         uint32_t off = v_off0;
         asm volatile("" : "+v"(off));
 #pragma unroll
-        for (int f = 0; f < KSTEPS; ++f) {  // f = 16-key half * MT + d tile
-            const uint32_t a = (off ^ (uint32_t)((f % MT) << 6)) + ((f / MT) * 16) * ROWB;
-            const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)a);
-            const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(uintptr_t)(a + 8 * ROWB));
-            const uint2 lo2 = __builtin_bit_cast(uint2, lo), hi2 = __builtin_bit_cast(uint2, hi);
-            frag[f] = __builtin_bit_cast(bf16x8, make_uint4(lo2.x, lo2.y, hi2.x, hi2.y));
-        }
+        for (int f = 0; f < KSTEPS; ++f) frag[f] = read_v(off, f);
 #pragma unroll
         for (int f = 0; f < KSTEPS; ++f) asm volatile("" : "+v"(frag[f]));
     };
@@ -409,6 +393,7 @@ wave_split_kernel(WaveArgs a)
     };
 
     int t = wave;
+    bool not_finite = false;  // wave-uniform: infinities or NaN among the values of this wave's tree tiles
     for (; t < n_pref; t += NW) {  // cached keys
         const bool more = t + NW < n_all;
         bf16x8 frag[KSTEPS];
@@ -450,6 +435,11 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) add_product(frag, rt, pp[rt]);
     }
+    auto visible = [&](int rt, int tt) __attribute__((always_inline)) {  // nodes of tree tile tt that this lane's row sees
+        const int m = row_of(row0 + rt * 32 + li);
+        const int node = m - (int)a.by_tree.div((uint32_t)m) * a.n_tree;
+        return a.n_tree > 64 ? chain_word(par_lds, node, tt) : (uint32_t)par_lds[2 * node + tt];
+    };
     for (; t < n_all; t += NW) {  // tree keys; one row tile after the other
         if (t != wave) request(true, t, pages);
         wait_vmem<0>();
@@ -461,32 +451,35 @@ wave_split_kernel(WaveArgs a)
             read_k_tile(frag);
             floatx16 s;
             scores(frag, rt, s);
-            const int m = row_of(row0 + rt * 32 + li);
-            const int node = m - (int)a.by_tree.div((uint32_t)m) * a.n_tree;
-            uint32_t word = a.n_tree > 64 ? chain_word(par_lds, node, tt) : (uint32_t)(vis[rt] >> (32 * tt));
-            word >>= 4 * lh;
+            const uint32_t seen = visible(rt, tt) >> (4 * lh);
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                if (!((word >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
+                if (!((seen >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
             raise(rt, s, t == wave);
-            const float mc = m_run[rt] == -INFINITY ? 0.f : m_run[rt] * c;  // no visible key so far: zeros
-            float sum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; e += 2) {
-                const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -mc));
-                const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], c, -mc));
-                sum += p0 + p1;
-                const uint32_t u = pack16<F16>(p0, p1);
-                hi[e >> 1] = u;
-                lo[e >> 1] = F16 ? pack16<F16>(p0 - half_to_float((uint16_t)u), p1 - half_to_float((uint16_t)(u >> 16)))
-                                 : pack16<F16>(p0 - __uint_as_float(u << 16), p1 - __uint_as_float(u & 0xffff0000u));
-            }
-            l_run[rt] += sum;
+            l_run[rt] += tree_numerators<F16>(s, c, m_run[rt], hi, lo);
+            __builtin_amdgcn_sched_barrier(0);  // the values are not read early: no registers to spare
             read_v_tile(frag);
+            not_finite |= drop_not_finite<F16>(frag);
             add_product(frag, rt, hi);
             add_product(frag, rt, lo);
         }
         if (t + NW < n_all) request(false, t + NW, pages);
+    }
+
+    if (not_finite) {
+        for (t = n_pref + (wave - n_pref) % NW; t < n_all; t += NW) {
+            const int tt = t - n_pref;
+            if (tt < 0) continue;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                uint32_t word = visible(rt, tt);
+                while (word) {
+                    const int node = tt * 32 + __builtin_ctz(word);
+                    word &= word - 1;
+                    add_not_finite<F16>(o_acc[rt], vt + (int64_t)node * a.vt_r, lh);
+                }
+            }
+        }
     }
 
     // ---- merge of the waves, in fp32, through the stages (each wave its own: nothing reads them any more)
@@ -566,8 +559,7 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t x = i < 2 ? packed.x : packed.y;
-                    r[i] = o[u][i] - (F16 ? half_to_float((uint16_t)(i & 1 ? x >> 16 : x))
-                                          : __uint_as_float(i & 1 ? x & 0xffff0000u : x << 16));
+                    r[i] = rounding_rest(o[u][i], i & 1 ? high16<F16>(x) : low16<F16>(x));
                 }
                 *(uint2 *)(orow + col) = make_uint2(pack16<F16>(r[0], r[1]), pack16<F16>(r[2], r[3]));
             }

@@ -1,0 +1,112 @@
+"""Tree keys on the last key split of the cached-key kernel (more than 64 query rows per KV head, splits of
+768 rows or more), at the sizes where it can go wrong: one and several rounds of three tree tiles,
+trees on both sides of the 64 nodes whose mask is built in registers, workgroups of four and eight
+waves, a last row block without rows in some waves, sequences with fewer tiles than splits or none,
+and values that must not reach rows that do not see them."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_17421_amd import binding as ls
+from test_gpu_light_block import make
+from test_gpu_paged import PagedBatch
+from util import DeviceBatch, gates, oracle_full
+
+# dtype, query heads, KV heads, head_dim, tree nodes, prefix lengths, inputs
+CASES = [
+    ("bf16", 40, 8, 128, 17, [3200] + [40, 1000, 0] * 2 + [3101], "peaked"),   # 85 rows: four waves, one tree tile
+    ("f16", 64, 16, 64, 32, [3200, 0, 31, 2500], "tree"),       # 128 rows; a sequence without cached keys
+    ("bf16", 32, 8, 128, 64, [6300, 1700, 900, 6200], "tree"),  # the last size masked in registers; eight waves
+    ("bf16", 32, 8, 64, 65, [6300, 6000], "peaked"),            # 65: the chains are walked in LDS; 260 rows
+    ("f16", 32, 8, 128, 69, [12345], "tree"),                   # 276 rows, three tree tiles
+    ("bf16", 32, 32, 128, 97, [4001, 33], "tree"),              # four tree tiles: a second round
+    ("bf16", 32, 16, 64, 200, [3300, 800], "tree"),             # seven tree tiles
+    ("bf16", 8, 8, 128, 512, [6500, 10], "tree"),               # the largest tree, sixteen tiles
+    ("f16", 32, 16, 64, 130, [3200, 300], "peaked"),
+]
+
+
+def whole_call(db):
+    out, lse = db.run_full()
+    torch.cuda.synchronize()
+    return out.float().cpu().numpy(), lse.cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plens,variant", CASES)
+def test_whole_call_against_the_oracle_and_the_tail_kernel(dtype, hq, hkv, d, t, plens, variant):
+    batch = make(dtype, hq, hkv, d, t, plens, variant, 31000 + t)
+    print(f"tree split {dtype} hq={hq} hkv={hkv} d={d} t={t} plens={plens} {variant}", flush=True)
+    db = DeviceBatch(batch, token_major=t % 2 == 0)
+    assert ls.ls_prefix_split_len(db.desc, 0) >= 768  # the tree keys are on the last split
+    first = whole_call(db)
+    db.workspace.fill_(0xFF)  # whatever the workspace and the outputs held, the result is the same
+    db.out.fill_(float("nan"))
+    out, lse = whole_call(db)
+    assert np.array_equal(out, first[0]) and np.array_equal(lse, first[1])
+    ro, rl = oracle_full(batch)
+    print(gates(out, lse, ro, rl, dtype, "  tree split", stress=True), flush=True)
+    # in place (q is the output): the tail kernel takes the tree keys
+    q = db.q.clone()
+    db.workspace.fill_(0xFF)
+    ls.ls_hybrid_tree_attn(ls.make_desc(q, db.k_cache, db.v_cache, db.k_tree, db.v_tree, q, db.desc.max_prefix_len), q,
+                           db.k_cache, db.v_cache, db.prefix_lens, db.k_tree, db.v_tree, db.parents, q, db.lse, db.workspace)
+    torch.cuda.synchronize()
+    print(gates(q.float().cpu().numpy(), db.lse.cpu().numpy(), ro, rl, dtype, "  in place", stress=True), flush=True)
+    # the same cache in shuffled pages
+    pb = PagedBatch(batch, 16 if t % 3 else 64, np.random.default_rng(5))
+    po, pl = pb.run()
+    if pb.desc.max_prefix_len == db.desc.max_prefix_len:  # the same plan: bit for bit
+        assert np.array_equal(po, out) and np.array_equal(pl, lse)
+    print(gates(po, pl, ro, rl, dtype, "  paged", stress=True), flush=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen", [("bf16", 32, 8, 128, 40, 24000), ("f16", 32, 32, 64, 100, 6500),
+                                                    ("bf16", 4, 2, 128, 9, 200), ("f16", 4, 4, 64, 70, 100)])
+def test_infinite_values_stay_with_the_rows_that_see_them(dtype, hq, hkv, d, t, plen):
+    """A node with an infinite and a NaN value: its descendants' two columns are not finite, everything else
+    is what it is with zeros there (on the kernel whose waves split the keys too)."""
+    batch = make(dtype, hq, hkv, d, t, [plen], "tree", 32000 + t)
+    parents = batch.seqs[0].parents
+    node = t // 3
+    sees = np.zeros(t, bool)
+    for i in range(t):
+        j = i
+        while j >= 0:
+            sees[i] |= j == node
+            j = parents[j]
+    assert sees.any() and not sees.all()
+    print(f"infinite values {dtype} d={d} t={t} plen={plen}", flush=True)
+    db = DeviceBatch(batch)
+    db.v_tree[:, :, node, 3] = 0.0
+    db.v_tree[:, :, node, 40] = 0.0
+    out0, lse0 = whole_call(db)
+    db.v_tree[:, :, node, 3] = float("-inf")
+    db.v_tree[:, :, node, 40] = float("nan")
+    out, lse = whole_call(db)
+    assert np.array_equal(lse, lse0)
+    touched = np.zeros(out.shape, bool)
+    touched[:, :, sees, 3] = touched[:, :, sees, 40] = True
+    assert np.array_equal(out[~touched], out0[~touched])
+    assert np.all(np.isneginf(out[:, :, sees, 3])) and np.all(np.isnan(out[:, :, sees, 40]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("t,plen", [(40, 13000), (100, 6500)])
+def test_bad_parents_are_cut_and_reported(t, plen):
+    batch = make("bf16", 32, 8, 128, t, [plen, plen], "tree", 33000 + t)
+    db = DeviceBatch(batch)
+    bad = [s.parents.copy() for s in batch.seqs]
+    bad[1][t // 2], bad[1][t - 1] = t - 1, -7
+    cut = [p.copy() for p in bad]
+    cut[1][t // 2], cut[1][t - 1] = -1, -1
+    print(f"bad parents t={t} plen={plen}", flush=True)
+    results = []
+    for parents in (bad, cut):
+        db.parents = torch.from_numpy(np.stack(parents)).cuda()
+        out, lse = whole_call(db)
+        at = ls.ls_workspace_error(db.desc, db.workspace) - db.workspace.data_ptr()
+        results.append((out, lse, db.workspace[at:at + 8].view(torch.int32).cpu().tolist()))
+    assert results[0][2] == [0, 1] and results[1][2] == [0, 0]
+    assert np.array_equal(results[0][0], results[1][0]) and np.array_equal(results[0][1], results[1][1])

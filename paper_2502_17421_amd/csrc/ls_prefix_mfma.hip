@@ -204,8 +204,8 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     }
 
     // ---- HBM -> LDS tile loads ----------------------------------------------------------
-    const uint8_t *kbase = uniform_ptr((const uint8_t *)p.k_cache + (b * p.kc_stride[0] + g * p.kc_stride[1]) * 2);
-    const uint8_t *vbase = uniform_ptr((const uint8_t *)p.v_cache + (b * p.vc_stride[0] + g * p.vc_stride[1]) * 2);
+    const uint8_t *kbase = uniform_ptr((const uint8_t *)p.k_cache + ((PAGED ? 0 : b * p.kc_stride[0]) + g * p.kc_stride[1]) * 2);
+    const uint8_t *vbase = uniform_ptr((const uint8_t *)p.v_cache + ((PAGED ? 0 : b * p.vc_stride[0]) + g * p.vc_stride[1]) * 2);
     const int64_t k_row_bytes = p.kc_stride[2] * 2, v_row_bytes = p.vc_stride[2] * 2;
     const int ld_row = lane / CH;  // row within one load instruction
     const int ld_pos = lane % CH;  // LDS chunk position this lane fills
@@ -239,54 +239,50 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         }
         __syncthreads();
     }
-    auto page_of = [&](int row) __attribute__((always_inline)) -> int64_t {  // row: wave-uniform cache row of this sequence
-        const int pidx = (row >> p.page_shift) - first_page;
-        return (int64_t)__builtin_amdgcn_readfirstlane(((const uint32_t *)(smem + PAGE_TAB))[pidx]);
+    // The id of the page that holds this wave's rows of the tile at cache row k0.  A copying wave's rows of a
+    // tile are eight consecutive ones, which never straddle a page (page sizes are powers of two >= 16), also
+    // where rows past the end repeat the last one.  The ids are read a request ahead and the K and V rows of
+    // a tile share theirs: read from LDS in front of each copy, eight round trips per pair of tiles, one
+    // after the other, they cost eight sequences x 8 KV heads x 96 rows over 501 to 9003 keys 72 us per call.
+    auto page_lookup = [&](int k0) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (!PAGED) return 0u;
+        const int last = k_hi - 1 - k0;
+        int row = load_row0(0);
+        row = row < last ? row : last;
+        row = row > 0 ? row : 0;
+        return ((const uint32_t *)(smem + PAGE_TAB))[((k0 + row) >> p.page_shift) - first_page];
     };
     // Requests.  issue_rows<IS_V>(k0, tile_base, dst): this wave's LOADS copies of the K (or V) rows
     // of the tile that starts at cache row k0, to the ring stage at LDS byte offset dst.  Rows past
     // the end of the split repeat its last row; their scores are masked.
-    // Paged: one load instruction covers ROWS_PER_LOAD consecutive rows, which never straddle a
-    // page (page sizes are powers of two >= 16): its base is that of its own page.
-    auto issue_rows = [&](auto is_v_tag, int k0, const uint8_t *tile_base, uint32_t dst, bool mine) __attribute__((always_inline)) {
+    // Paged: the base is that of the page of this wave's rows (page_lookup).
+    auto issue_rows = [&](auto is_v_tag, int k0, const uint8_t *tile_base, uint32_t dst, uint32_t page, bool mine) __attribute__((always_inline)) {
         constexpr bool IS_V = decltype(is_v_tag)::value;
         if (!mine) return;  // wave-uniform
         const uint32_t d0 = __builtin_amdgcn_readfirstlane(smem_off + dst);
         const int last = k_hi - 1 - k0;  // last valid row of the tile (>= TK - 1 for whole tiles)
         const int64_t row_bytes = IS_V ? v_row_bytes : k_row_bytes;
-        const int64_t *stride = IS_V ? p.vc_stride : p.kc_stride;
-        const uint8_t *tensor = (const uint8_t *)(IS_V ? p.v_cache : p.k_cache);
         auto swz = [&](int row) __attribute__((always_inline)) { return (IS_V ? vswz(row) : row) & (CH - 1); };
-        if constexpr (PAGED) {
+        const uint8_t *base = tile_base;  // address of the tile's first row
+        if constexpr (PAGED) {  // (as this wave's page has it)
+            const int64_t *stride = IS_V ? p.vc_stride : p.kc_stride;
+            int row = load_row0(0);
+            row = row < last ? row : last;
+            base = (IS_V ? vbase : kbase) + (int64_t)__builtin_amdgcn_readfirstlane(page) * (2 * stride[0]) +
+                   (((k0 + row) & page_rows_mask) - row) * row_bytes;
+            base = uniform_ptr(base);
+        }
+        if (last >= TK - 1) {
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j)
+                copy_to_lds(base, IS_V ? v_voff[j] : k_voff[j], d0 + load_row0(j) * ROWB);
+        } else {
 #pragma unroll
             for (int j = 0; j < LOADS; ++j) {
-                const int row0 = load_row0(j);  // wave-uniform
-                // rows past the end repeat the last row, fetched through that row's own group
-                const int last_group = last & ~(ROWS_PER_LOAD - 1);
-                const int src0 = row0 < last_group ? row0 : last_group;
+                const int row0 = load_row0(j);
                 const int row = row0 + ld_row;
-                int src = src0 + ld_row;
-                src = src < last ? src : last;
-                const int abs0 = k0 + src0;
-                const int64_t page = page_of(abs0);
-                const int in_page = abs0 & page_rows_mask;
-                const uint8_t *base = uniform_ptr(tensor + (page * stride[0] + g * stride[1] + in_page * stride[2]) * 2);
-                copy_to_lds(base, (uint32_t)((src - src0) * row_bytes) + (ld_pos ^ swz(row)) * 16, d0 + row0 * ROWB);
-            }
-        } else {
-            const uint8_t *base = tile_base;  // address of the tile's first row (contiguous caches only)
-            if (last >= TK - 1) {
-#pragma unroll
-                for (int j = 0; j < LOADS; ++j)
-                    copy_to_lds(base, IS_V ? v_voff[j] : k_voff[j], d0 + load_row0(j) * ROWB);
-            } else {
-#pragma unroll
-                for (int j = 0; j < LOADS; ++j) {
-                    const int row0 = load_row0(j);
-                    const int row = row0 + ld_row;
-                    const int src = row < last ? row : last;
-                    copy_to_lds(base, (uint32_t)(src * row_bytes) + (ld_pos ^ swz(row)) * 16, d0 + row0 * ROWB);
-                }
+                const int src = row < last ? row : last;
+                copy_to_lds(base, (uint32_t)(src * row_bytes) + (ld_pos ^ swz(row)) * 16, d0 + row0 * ROWB);
             }
         }
     };
@@ -336,20 +332,25 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     int rq_kt = 0, rq_k0 = key_first, rq_vt = 0, rq_v0 = key_first;
     const uint8_t *rq_kptr = uniform_ptr(kbase + key_first * k_row_bytes), *rq_vptr = uniform_ptr(vbase + key_first * v_row_bytes);
     uint32_t rq_koff = 0, rq_voff = V_RING;
+    // pages of the tiles that the next K and the next V request are for, and of the one after the latter
+    uint32_t pg_k = page_lookup(key_first), pg_v = pg_k, pg_next_v = pg_k;
     // (mine: this wave is among those that copy this request; every wave keeps the state)
     auto request_k = [&](bool mine) __attribute__((always_inline)) {
-        if (rq_kt < n_tiles) issue_rows(is_k{}, rq_k0, rq_kptr, rq_koff, mine);
+        if (rq_kt < n_tiles) issue_rows(is_k{}, rq_k0, rq_kptr, rq_koff, pg_k, mine);
         ++rq_kt;
         rq_k0 = next_key0(rq_k0);
         rq_kptr = rq_k0 == k_lo ? k_ptr_lo : rq_kptr + TK * k_row_bytes;
         rq_koff = next_k(rq_koff);
+        pg_next_v = pg_k;
+        pg_k = page_lookup(rq_k0);
     };
     auto request_v = [&](bool mine) __attribute__((always_inline)) {
-        if (rq_vt < n_tiles) issue_rows(is_v{}, rq_v0, rq_vptr, rq_voff, mine);
+        if (rq_vt < n_tiles) issue_rows(is_v{}, rq_v0, rq_vptr, rq_voff, pg_v, mine);
         ++rq_vt;
         rq_v0 = next_key0(rq_v0);
         rq_vptr = rq_v0 == k_lo ? v_ptr_lo : rq_vptr + TK * v_row_bytes;
         rq_voff = next_v(rq_voff);
+        pg_v = pg_next_v;
     };
     request_k(loader);  // request -(PD+1)
 #pragma unroll

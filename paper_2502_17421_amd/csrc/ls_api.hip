@@ -303,7 +303,8 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, co
     // A cache of some 1500 keys is worked through by one workgroup per row tile in less time than the merge
     // of a split call takes (64 rows per KV head, 8 KV heads: 700 keys 11.0 us in one split against 12.9 in
     // two and 18.6 on the kernel that shares tiles between waves; 1600 keys 14.9, 16.3, 19.8).
-    constexpr int kDirectTiles = 48;
+    constexpr int kDirectTiles = 50;
+    constexpr int kOneSplitTiles = 80, kSplitTiles = 136;
     if (rows_kv <= 64) {
         // every wave of a workgroup holds all the query rows of the KV head (32 rows per KV head, 16k keys: 52.7
         // against 57.3 us; 64 rows, 32k keys: 34.6 against 35.4; 32 rows, 8k keys: 14.2 against 20.6)
@@ -314,6 +315,19 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, co
         w.row_tiles = 1;
         w.n_splits = 1;
         w.ride = true;
+    } else {
+        // More rows: while 32-row workgroups leave compute units idle, up to some 4k keys, the start of the kernel
+        // that shares tiles (first window, 256 rows) costs more than its faster tiles save.  Measured, that
+        // kernel against this one: 256 rows per KV head, 8 KV heads: 2k keys 19.3 / 14.8 us, 4k 22.3 / 17.9, 8k
+        // 28.5 / 26.1 (and 35 / 41 at 16k); 96 rows: 15.2 / 12.4, 17.1 / 14.0; one split of 1024 rows x 2k keys
+        // 30.4 / 19.8, of 640 rows 25.3 / 17.3.
+        const int64_t units = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 31) / 32);
+        const int64_t fit = compute_units() / units;  // splits that fit the chip at once
+        if (tiles <= (fit >= 2 ? kSplitTiles : kOneSplitTiles) && fit >= 1) {
+            w.row_tiles = 1;
+            w.n_splits = fit < plan.n_splits ? (int32_t)fit : plan.n_splits;
+            w.ride = true;
+        }
     }
     return w;
 }

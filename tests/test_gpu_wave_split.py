@@ -39,6 +39,9 @@ CASES = [
     ("bf16", 8, 2, 128, 16, [9000], "tree"),                # several splits, two row tiles
     ("f16", 8, 8, 128, 20, [6001, 17, 0], "tree"),          # several splits, sequences with fewer tiles than splits
     ("bf16", 5, 1, 64, 6, [20011], "peaked"),
+    ("bf16", 8, 2, 128, 33, [1537, 3], "tree"),             # more than 64 rows, several splits: the shortest cache
+    ("f16", 8, 2, 64, 70, [4256], "peaked"),                # and the longest: 133 cached tiles and 3 of the tree
+    ("bf16", 32, 8, 128, 136, [2400], "tree"),              # 544 rows over 8 heads: one split of 80 tiles
 ]
 
 

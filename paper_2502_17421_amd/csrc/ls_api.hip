@@ -245,7 +245,7 @@ SplitPlan plan_splits(const ls_desc &d, int32_t request)
     plan.n_splits = (int32_t)s;
     plan.split_len = (int32_t)len;
     plan.per_sequence = 0;
-    plan.reserved = 0;
+    plan.balanced = 0;
     return plan;
 }
 
@@ -474,11 +474,11 @@ int ls_lse_merge(const ls_desc *desc, int32_t n_parts, int32_t part_dtype, const
 namespace {
 // Whole-path call whose tree keys are taken along by the kernel for the cached keys, and the merge of the
 // parts unless a single split's output is final.
-int run_whole(const ls_desc &d, const Problem &p, const SplitPlan &splits, const WholePlan &plan, const int32_t *parents,
-              int32_t *err, void *out, float *lse, void *o_parts, float *lse_parts, hipStream_t s)
+int run_whole(const ls_desc &d, const Problem &p, SplitPlan splits, const WholePlan &plan, const int32_t *parents,
+              int32_t *err, void *out, float *lse, void *o_parts, float *lse_parts, SequenceSplits *table, hipStream_t s)
 {
     WholeCall w{parents, err, out, {d.o_stride[0], d.o_stride[1], d.o_stride[2]}, lse, o_parts, lse_parts, plan.n_splits,
-                FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads)};
+                FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads), nullptr};
     if (plan.row_tiles > 0) {
         if (launch_wave_split(p, d.dtype, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
         if (plan.n_splits == 1) return LS_OK;
@@ -489,6 +489,12 @@ int run_whole(const ls_desc &d, const Problem &p, const SplitPlan &splits, const
         tail.out = out;
         for (int i = 0; i < 3; ++i) tail.o_stride[i] = d.o_stride[i];
         tail.err_flag = err;
+        // several sequences: pieces dealt by length (a single piece each cannot be)
+        if (d.batch > 1 && d.batch <= kMaxBalanced && p.prefix_lens && splits.n_splits > 1) {
+            splits.balanced = 1;
+            tail.table = table;
+            w.table = table;
+        }
         if (launch_prefix_mfma(p, d.dtype, splits, parts, MaskJob{nullptr, nullptr, nullptr}, tail, s) != hipSuccess)
             return LS_ERR_HIP;
     }
@@ -523,7 +529,7 @@ int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, c
     p.prefix_len_all = prefix_len_all;
     if (prefix_mfma_supports(p, desc->dtype) && !single_launch) {
         const WholePlan whole = plan_whole(*desc, plan, true, q, out);
-        if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, o_parts, lse_parts, s);
+        if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, o_parts, lse_parts, (SequenceSplits *)mask, s);
     }
 
     // (b) cached keys -> parts [0, n_splits), stored in the problem's dtype; on the MFMA path
@@ -650,7 +656,7 @@ int ls_cache_attn(const ls_desc *desc, const void *q, const void *k_cache, const
     if (!mfma && is_16bit(desc->dtype)) return LS_ERR_UNSUPPORTED;
     if (mfma) {
         const WholePlan whole = plan_whole(*desc, plan, false, q, out);
-        if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, s);
+        if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, (SequenceSplits *)(base + w.off_mask), s);
     }
     const Partials parts{o_parts, lse_parts, w.n_parts, 0, is_16bit(desc->dtype), 1};
     const hipError_t e = mfma ? launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s)
@@ -743,7 +749,7 @@ int ls_hybrid_tree_attn_paged(const ls_desc *desc, const void *q, const void *k_
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
     const WholePlan whole = plan_whole(*desc, plan, true, q, out);
-    if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, parts.o, parts.lse, s);
+    if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, parts.o, parts.lse, (SequenceSplits *)mask, s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{parents, mask, err}, FusedTail{}, s) != hipSuccess) return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, mask, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)
         return LS_ERR_HIP;
@@ -773,7 +779,7 @@ int ls_cache_attn_paged(const ls_desc *desc, const void *q, const void *k_pages,
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
     const WholePlan whole = plan_whole(*desc, plan, false, q, out);
-    if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, parts.o, parts.lse, s);
+    if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, parts.o, parts.lse, (SequenceSplits *)(base + w.off_mask), s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s) != hipSuccess)
         return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, nullptr, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)

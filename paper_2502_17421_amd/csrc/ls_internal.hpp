@@ -65,6 +65,14 @@ struct MaskJob {
     int32_t *err_flag;
 };
 
+constexpr int kMaxBalanced = 32;  // sequences of a call whose pieces are dealt by length
+
+// Pieces of one sequence of a balanced call: the parts of its query rows, [row, piece], begin at row
+// first * (rows per sequence) of the workspace's part array.
+struct SequenceSplits {
+    int32_t first, count;
+};
+
 // Single-launch form of the whole call.  The workgroups of one (sequence, KV head, query block),
 // one per key split, share three 64-bit words: an arrival word (call number << 32 | workgroups
 // counted in this call) and two claim words used by alternate calls (bit k: the rows of slice k
@@ -86,6 +94,7 @@ struct FusedTail {
     float *lse;
     int32_t spin_limit;  // polls (about half a microsecond apart) before a workgroup leaves its slice to the last one
     int32_t *err_flag;   // (tree keys of the last split) one word per sequence, or nullptr
+    SequenceSplits *table;  // balanced calls: one entry per sequence, written for the merge
 };
 constexpr int kMaxArrivalCounters = 4096;  // (sequence, KV head, query block) triples one single-launch call may have
 constexpr int kCounterWords = 3;           // 64-bit words per triple
@@ -98,7 +107,9 @@ struct SplitPlan {
     // instead of pieces of split_len rows sized for the longest sequence the cache can hold, so
     // that a short sequence keeps as many workgroups busy as a long one.
     int32_t per_sequence;
-    int32_t reserved;
+    // MFMA path, whole-path calls that end with merge_parts_kernel, several sequences: the batch * n_splits
+    // pieces are dealt to the sequences by their length (see SequenceSplits), all of about the same size.
+    int32_t balanced;
 };
 
 // n / d for wave-uniform or per-lane n by one multiplication, exact while n * d < 2^32 (the multiplier is
@@ -125,6 +136,7 @@ struct WholeCall {
     float *lse_parts;
     int32_t n_splits;
     FastDiv by_splits, by_tree, by_kv_heads, by_q_heads;  // divisors n_splits, n_tree, n_kv_heads, n_q_heads
+    const SequenceSplits *table;  // balanced call: pieces per sequence; nullptr: n_splits each
 };
 
 // bf16 <-> float on raw 16-bit patterns (round to nearest even, NaN kept quiet).

@@ -87,6 +87,17 @@ constexpr float kLazy = 8.f;        // general path: m is raised only when a sco
 // the operand type, and a half holds nothing above 65504
 template <bool F16> constexpr float kSumCap = F16 ? 0x1p15f : 0x1p40f;
 
+// Pieces of at most `piece` tiles that `tiles` tiles take, one at least.  (tiles < 2^20: the quotient by the
+// reciprocal is off by at most one.)
+__device__ __forceinline__ int pieces_of(int tiles, int piece)
+{
+    int n = (int)((float)tiles * __builtin_amdgcn_rcpf((float)piece));
+    n += n * piece < tiles ? 1 : 0;
+    n += n * piece < tiles ? 1 : 0;
+    n -= (n - 1) * piece >= tiles ? 1 : 0;
+    return n > 1 ? n : 1;
+}
+
 }  // namespace
 
 // FUSED: the single-launch call (contiguous caches only).  A form of its own: what it needs at the end would
@@ -126,6 +137,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     // Workgroups past that range (one per sequence, present only in the whole-path launch)
     // build the tree mask, which the kernel that follows this one consumes.
     const int per_unit = n_qblocks * plan.n_splits;
+    const int row_tile_cost = !FUSED && tail.parents != nullptr ? kTreeTileCost * ((p.n_tree + TK - 1) / TK) : 0;
     const int n_main = per_unit * p.batch * p.n_kv_heads;
     if ((int)blockIdx.x >= n_main) {
         const int mb = blockIdx.x - n_main;
@@ -137,11 +149,53 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     }
     const int bz = blockIdx.x / per_unit;
     const int in_unit = blockIdx.x % per_unit;
-    const int split = in_unit % plan.n_splits;
-    const int qblock = in_unit / plan.n_splits;
-    const int b = bz / p.n_kv_heads;
-    const int g = bz % p.n_kv_heads;
+    int split = in_unit % plan.n_splits;
+    int qblock = in_unit / plan.n_splits;
+    int b = bz / p.n_kv_heads;
+    int g = bz % p.n_kv_heads;
     const int rows_kv = p.group * p.n_tree;
+    // Balanced call: piece fastest (of all sequences together), then query block, then KV head.  The host does not
+    // know the lengths; with n_splits pieces for every sequence the launch lasts as long as the longest one's
+    // pieces (eight sequences of 501 to 9003 keys, 96 rows per KV head, paged: 61.7 us against 47.5; four of
+    // 19k to 42k, 640 rows: 361 against 350; eight of 3.4k to 5.4k, 335 rows: 90.1 against 83.5).
+    int n_splits = plan.n_splits, first_split = b * plan.n_splits, balanced_tiles = 0;
+    if constexpr (!FUSED) {
+        if (plan.balanced) {
+            const int pieces = p.batch * plan.n_splits;
+            int piece = blockIdx.x % pieces;
+            const int rest = blockIdx.x / pieces;
+            qblock = rest % n_qblocks;
+            g = rest / n_qblocks;
+            // this lane's sequence: its tiles, with what the tree costs
+            int len = lane < p.batch ? p.prefix_lens[lane] : 0;
+            len = len < 0 ? 0 : (len > p.max_prefix_len ? p.max_prefix_len : len);
+            const int tiles = lane < p.batch ? (len + TK - 1) / TK + row_tile_cost : 0;
+            int total = 0;
+            for (int i = 0; i < p.batch; ++i) total += __builtin_amdgcn_readlane(tiles, i);
+            // The smallest piece with which the sequences take no more pieces than there are: lane i tries low + i * step
+            // (whole pairs of tiles).  Twice the mean is enough, as every sequence rounds up by less than one.
+            const int low = (total + pieces - 1) / pieces;
+            const int step = 2 * ((low + 125) / 126);
+            int mine = (low + 1) / 2 * 2 + lane * step;
+            mine = mine > 2 ? mine : 2;
+            int taken = 0;
+            for (int i = 0; i < p.batch; ++i) taken += pieces_of(__builtin_amdgcn_readlane(tiles, i), mine);
+            const uint64_t fits = __ballot(taken <= pieces);
+            balanced_tiles = fits ? __builtin_amdgcn_readlane(mine, __builtin_ctzll(fits)) : 0;
+            const bool deal = balanced_tiles > 0 && balanced_tiles <= kMaxSplitLen / TK;  // else n_splits pieces each
+            const int count = deal ? pieces_of(tiles, balanced_tiles) : plan.n_splits;
+            if (!deal) balanced_tiles = 0;
+            for (b = 0, first_split = 0; b < p.batch; ++b) {
+                n_splits = __builtin_amdgcn_readlane(count, b);
+                if (piece < n_splits) break;
+                piece -= n_splits;
+                first_split += n_splits;
+            }
+            if (b == p.batch) return;  // a piece nobody takes
+            split = piece;
+            if (split == 0 && qblock == 0 && g == 0 && tid == 0) tail.table[b] = SequenceSplits{first_split, n_splits};
+        }
+    }
 
     // The split's own work (a `return` below leaves this block only; in the single-launch call
     // every wave goes on to the arrival count after it).
@@ -152,17 +206,17 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     // Whole-path call: the last split also takes the tree keys, and as many cached tiles less as they
     // cost (a tree tile has the output product of the rounding remainders as well and is not pipelined).
     const bool with_tree = !FUSED && tail.parents != nullptr;
-    const bool tree_split = with_tree && split == plan.n_splits - 1;
+    const bool tree_split = with_tree && split == n_splits - 1;
     const int tree_tiles = tree_split ? (p.n_tree + TK - 1) / TK : 0;
     if (plan.per_sequence) {
-        const int cost = with_tree ? kTreeTileCost * ((p.n_tree + TK - 1) / TK) : 0;
-        int per_split = ((plen + TK - 1) / TK + cost + plan.n_splits - 1) / plan.n_splits;
+        int per_split = ((plen + TK - 1) / TK + row_tile_cost + n_splits - 1) / n_splits;
         if (with_tree) per_split += per_split & 1;  // tiles go in pairs: 17 take as long as 18
+        if (balanced_tiles > 0) per_split = balanced_tiles;
         per_split = per_split < kMaxSplitLen / TK ? per_split : kMaxSplitLen / TK;
         split_len = per_split * TK;
     }
     int k_lo = split * split_len;
-    int k_hi = tree_split ? plen : k_lo + split_len;
+    int k_hi = tree_split || (balanced_tiles > 0 && split == n_splits - 1) ? plen : k_lo + split_len;
     k_hi = k_hi > plen ? plen : k_hi;
     k_lo = k_lo < k_hi ? k_lo : k_hi;
 
@@ -172,7 +226,11 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     const bool q_ok = m_row < rows_kv;
     const int hq = g * p.group + (q_ok ? m_row / p.n_tree : 0);
     const int ti = q_ok ? m_row % p.n_tree : 0;
-    const size_t part_row = out.row((size_t)b * p.n_q_heads + hq, split, p.n_tree, ti);
+    size_t part_row;
+    if (!FUSED && plan.balanced)
+        part_row = (size_t)first_split * (p.n_q_heads * p.n_tree) + (size_t)(hq * p.n_tree + ti) * n_splits + split;
+    else
+        part_row = out.row((size_t)b * p.n_q_heads + hq, split, p.n_tree, ti);
 
     if (k_lo >= k_hi && !tree_split) {  // empty split: weight zero in the merge
         if (lh == 0 && q_ok) {
@@ -886,7 +944,6 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     int32_t *par_lds = (int32_t *)(smem + LS_MAX_TREE * 8 * sizeof(uint64_t));
     volatile uint32_t *word = (volatile uint32_t *)(par_lds + LS_MAX_TREE);
     const int unit = bz * n_qblocks + qblock;
-    const uint32_t n_splits = (uint32_t)plan.n_splits;
     uint64_t *arrival = tail.counters + (size_t)unit * kCounterWords;
     // The last wave counts and waits (its first lane); the others build the tree mask meanwhile.
     const bool counting = tid == (NW - 1) * 64;
@@ -900,12 +957,12 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     __syncthreads();
     if (counting) {
         const uint32_t call = (uint32_t)(before >> 32);
-        const bool last = (uint32_t)before == n_splits - 1u;
+        const bool last = (uint32_t)before == (uint32_t)n_splits - 1u;
         uint64_t *claims = arrival + 1 + (call & 1u);
         bool go = last;
         if (last) {
             __hip_atomic_store(arrival + 1 + ((call + 1u) & 1u), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(arrival, (1ull << 32) - n_splits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(arrival, (1ull << 32) - (uint32_t)n_splits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             for (int poll = 0; poll < tail.spin_limit && !go; ++poll) {
                 __builtin_amdgcn_s_sleep(4);
@@ -945,7 +1002,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     typedef std::conditional_t<F16, half_t, uint16_t> T16;
     const int row_base = qblock * NW * 32;
     const int rows_here = rows_kv - row_base < NW * 32 ? rows_kv - row_base : NW * 32;
-    const int per_slice = (rows_here + (int)n_splits - 1) / (int)n_splits;
+    const int per_slice = (rows_here + n_splits - 1) / n_splits;
     auto do_slice = [&](int k) {
         const int hi = (k + 1) * per_slice < rows_here ? (k + 1) * per_slice : rows_here;
         for (int r = k * per_slice + wave; r < hi; r += NW) {
@@ -960,7 +1017,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     // the slices nobody has taken by now
     __syncthreads();  // everybody has read the words above
     if (counting) {
-        const uint64_t all = n_splits >= 64u ? ~0ull : (1ull << n_splits) - 1ull;
+        const uint64_t all = (uint32_t)n_splits >= 64u ? ~0ull : (1ull << (uint32_t)n_splits) - 1ull;
         const uint64_t taken = __hip_atomic_fetch_or(claims, all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint64_t rest = all & ~taken;
         word[0] = (uint32_t)rest;

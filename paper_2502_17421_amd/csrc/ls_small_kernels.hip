@@ -316,6 +316,16 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
 // LG = D / 8 lanes hold a row in 16-byte pieces.  WIDE: a wavefront per query row, 64 / LG parts per
 // load instruction; else LG lanes per query row (at most 8 parts).  Every load of a row is issued before
 // the first is used; LSEs and rows come together, so a row costs one round trip.
+template <int LG> __device__ __forceinline__ int max_over_groups(int x)
+{
+#pragma unroll
+    for (int off = 32; off >= LG; off >>= 1) {
+        const int y = __shfl_xor(x, off, kWave);
+        x = x > y ? x : y;
+    }
+    return __builtin_amdgcn_readfirstlane(x);
+}
+
 template <typename T, int D, bool WIDE>
 __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w, int rows_total)
 {
@@ -333,25 +343,35 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w
     const int bh = (int)w.by_tree.div((uint32_t)r), i = r - bh * p.n_tree;
     const int b = (int)w.by_q_heads.div((uint32_t)bh), h = bh - b * p.n_q_heads;
     T *orow = (T *)w.out + b * w.o_stride[0] + h * w.o_stride[1] + i * w.o_stride[2] + sl * 8;
-    const T *rows = (const T *)w.o_parts + (size_t)r * w.n_splits * D + sl * 8;
-    const float *lses = w.lse_parts + (size_t)r * w.n_splits;
+    int n_splits = w.n_splits;                            // of this lane's row
+    size_t part0 = (size_t)r * n_splits;
+    if (w.table) {
+        const SequenceSplits mine = w.table[b];
+        const int per_seq = p.n_q_heads * p.n_tree;
+        n_splits = mine.count;
+        part0 = (size_t)mine.first * per_seq + (size_t)(r - b * per_seq) * n_splits;
+    }
+    const int n_top = WIDE ? n_splits : max_over_groups<LG>(n_splits);  // wave-uniform
+    const T *rows = (const T *)w.o_parts + part0 * D + sl * 8;
+    const float *lses = w.lse_parts + part0;
 
     float o[8], top = -INFINITY, wsum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
     RawVec<16> rest{};
-    const int tree_part = w.parents ? w.n_splits - 1 : -1;
+    const int tree_part = w.parents ? n_splits - 1 : -1;
     if (w.parents) rest = load_raw<16>(orow);
-    for (int k0 = 0; k0 < w.n_splits; k0 += WIDE ? 64 : 8) {  // one pass up to 64 (8) parts
-        const int n = w.n_splits - k0 < (WIDE ? 64 : 8) ? w.n_splits - k0 : (WIDE ? 64 : 8);
+    for (int k0 = 0; k0 < n_top; k0 += WIDE ? 64 : 8) {  // one pass up to 64 (8) parts
+        const int left = n_splits - k0, n = left < (WIDE ? 64 : 8) ? left : (WIDE ? 64 : 8);  // of this row (may be none)
+        const int n_any = n_top - k0;
         const int mine = WIDE ? lane : sl;                // the part whose LSE this lane holds
         const float l = mine < n ? lses[k0 + mine] : -INFINITY;
         RawVec<16> raw[NL];
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
             const int part = WIDE ? k * GROUPS + group : k;
-            if (WIDE ? k * GROUPS < n : k < n)            // wave-uniform; past the last part: a valid row, weight 0
-                raw[k] = load_raw<16>(rows + (size_t)(k0 + (part < n ? part : n - 1)) * D);
+            if (WIDE ? k * GROUPS < n_any : k < n_any)    // wave-uniform; past the last part: a valid row, weight 0
+                raw[k] = load_raw<16>(rows + (size_t)(part < n ? k0 + part : n_splits - 1) * D);
         }
         float t = l;
 #pragma unroll
@@ -366,7 +386,7 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w
         wsum += weight;                                   // summed over the lanes at the end
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
-            if (WIDE ? k * GROUPS < n : k < n) {
+            if (WIDE ? k * GROUPS < n_any : k < n_any) {
                 const int part = WIDE ? k * GROUPS + group : k;
                 const float wk = __shfl(weight, WIDE ? part : group * LG + k, kWave);
                 float v[8];

@@ -1,7 +1,8 @@
 """Tree keys on the last key split of the cached-key kernel (more than 64 query rows per KV head, splits of
 768 rows or more), at the sizes where it can go wrong: one and several rounds of three tree tiles,
 trees on both sides of the 64 nodes whose mask is built in registers, workgroups of four and eight
-waves, a last row block without rows in some waves, sequences with fewer tiles than splits or none,
+waves, a last row block without rows in some waves, sequences of unlike length (whose splits are dealt by
+length, up to 32 sequences) with few tiles or none,
 and values that must not reach rows that do not see them."""
 import numpy as np
 import pytest
@@ -23,6 +24,8 @@ CASES = [
     ("bf16", 32, 16, 64, 200, [3300, 800], "tree"),             # seven tree tiles
     ("bf16", 8, 8, 128, 512, [6500, 10], "tree"),               # the largest tree, sixteen tiles
     ("f16", 32, 16, 64, 130, [3200, 300], "peaked"),
+    ("bf16", 8, 4, 64, 40, [2000] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 22, "tree"),  # 32 sequences: the most
+    ("bf16", 4, 2, 64, 40, [2500] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 23, "tree"),  # 33: an even cut of each
 ]
 
 
@@ -38,7 +41,9 @@ def test_whole_call_against_the_oracle_and_the_tail_kernel(dtype, hq, hkv, d, t,
     batch = make(dtype, hq, hkv, d, t, plens, variant, 31000 + t)
     print(f"tree split {dtype} hq={hq} hkv={hkv} d={d} t={t} plens={plens} {variant}", flush=True)
     db = DeviceBatch(batch, token_major=t % 2 == 0)
-    assert ls.ls_prefix_split_len(db.desc, 0) >= 768  # the tree keys are on the last split
+    assert ls.ls_prefix_num_splits(db.desc) > 1 or len(plens) == 1
+    if len(plens) < 33:
+        assert ls.ls_prefix_split_len(db.desc, 0) >= 768  # the tree keys are on the last split
     first = whole_call(db)
     db.workspace.fill_(0xFF)  # whatever the workspace and the outputs held, the result is the same
     db.out.fill_(float("nan"))
@@ -53,6 +58,15 @@ def test_whole_call_against_the_oracle_and_the_tail_kernel(dtype, hq, hkv, d, t,
                            db.k_cache, db.v_cache, db.prefix_lens, db.k_tree, db.v_tree, db.parents, q, db.lse, db.workspace)
     torch.cuda.synchronize()
     print(gates(q.float().cpu().numpy(), db.lse.cpu().numpy(), ro, rl, dtype, "  in place", stress=True), flush=True)
+    # cached keys only
+    db.run_cache_only()
+    torch.cuda.synchronize()
+    co, cl = oracle_full(batch, use_tree=False)
+    seen = np.isfinite(cl)
+    got = db.lse.cpu().numpy()
+    assert np.array_equal(np.isfinite(got), seen)
+    print(gates(db.out.float().cpu().numpy(), np.where(seen, got, 0.0), co, np.where(seen, cl, 0.0), dtype,
+                "  cached keys only", stress=True), flush=True)
     # the same cache in shuffled pages
     pb = PagedBatch(batch, 16 if t % 3 else 64, np.random.default_rng(5))
     po, pl = pb.run()

@@ -132,8 +132,9 @@ int ls_workspace_bytes(const ls_desc *desc, size_t *bytes_out);
 /*
  * The whole path (Section 3.3): tree mask from `parents`, split-KV attention over the
  * cache, masked attention over the tree tokens, log-sum-exp merge into out / lse.  It runs
- * as two launches: the cached-key kernel (some extra workgroups of which build the mask),
- * then one kernel that does the tree attention and the merge per query row.
+ * as one or two launches, chosen by the sizes: a kernel for the cached keys, which takes the
+ * tree tokens along (short caches, few query rows, or long splits) or whose extra workgroups
+ * build the mask, then a merge of the parts, with the tree attention if it is still to do.
  *
  *   prefix_lens  DEVICE int32[batch]; values are clamped into [0, max_prefix_len].
  *                A sequence with prefix length 0 attends to its tree tokens only.

@@ -416,7 +416,8 @@ wave_split_kernel(WaveArgs a)
                     if (8 * (e >> 2) + 4 * lh + (e & 3) >= valid) s[e] = -INFINITY;
             }
             raise(rt, s, t == wave);
-            const float mc = m_run[rt] * c;  // finite: every cached tile holds at least one key
+            // a row all of whose scores so far are -inf has the reference -inf: its numerators are zeros
+            const float mc = m_run[rt] == -INFINITY ? 0.f : m_run[rt] * c;
             float sum = 0.f;
 #pragma unroll
             for (int e = 0; e < 16; e += 2) {

@@ -105,6 +105,46 @@ def test_bad_parents_are_cut_and_reported(t, plen):
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
 
 
+# dtype, query heads, KV heads, head_dim, tree nodes, prefix length, runs of cached keys that score -inf, by an infinite
+# component or (the last cases) by overflow.  A tile has 32 keys, tile i belongs to wave i % 8 while there is one split.
+NOTHING = [
+    ("bf16", 8, 2, 128, 5, 33, [(32, 33)]),                 # one row tile: a wave's first tile, one key long
+    ("f16", 8, 2, 64, 5, 33, [(32, 33)]),
+    ("f16", 8, 2, 128, 9, 300, [(0, 32), (288, 300)]),      # two row tiles: a whole first tile, the partial last one
+    ("bf16", 8, 2, 128, 9, 700, [(64, 96), (320, 352)]),    # both tiles of wave 2
+    ("bf16", 8, 2, 64, 9, 700, [(288, 320)]),               # the second tile of wave 1
+    ("bf16", 8, 2, 128, 16, 40, [(0, 40)]),                 # every cached key: the tree alone is left
+    ("bf16", 16, 4, 128, 40, 500, [(32, 64), (480, 500)]),  # 160 rows, one split
+    ("bf16", 8, 2, 128, 8, 9000, [(0, 700), (4000, 4032), (8992, 9000)]),  # several splits, one of them whole
+    ("f16", 8, 2, 128, 16, 9000, [(0, 700), (4000, 4032), (8992, 9000)]),
+    ("bf16", 8, 2, 128, 33, 3000, [(0, 1600), (2000, 2032)]),              # more than 64 rows, several splits
+    ("bf16", 8, 2, 128, 9, 750, [(0, 32), (320, 352), (736, 750)]),
+    ("bf16", 32, 8, 128, 40, 26000, [(0, 2000), (25990, 26000)]),          # the kernel that shares tiles between waves
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen,runs", NOTHING)
+def test_keys_that_score_minus_infinity_weigh_nothing(dtype, hq, hkv, d, t, plen, runs):
+    batch = make(dtype, hq, hkv, d, t, [plen], "tree", 23000 + t + plen)
+    seq = batch.seqs[0]
+    seq.q[..., 0] = synth.round_to_bf16(np.abs(seq.q[..., 0]) + 2.0)
+    for lo, hi in runs:
+        seq.k_cache[:, lo:hi, 0] = synth.round_to_bf16(np.float32(-3e38)) if plen in (750, 26000) else -np.inf
+    say(f"scores of -inf {dtype} hq={hq} hkv={hkv} d={d} t={t} plen={plen} {runs}")
+    db = DeviceBatch(batch)
+    out, lse = db.run_full()
+    torch.cuda.synchronize()
+    ro, rl = oracle_full(batch)
+    say(gates(out.float().cpu().numpy(), lse.cpu().numpy(), ro, rl, dtype, "  result", stress=True))
+    if runs == [(0, plen)]:
+        return  # cached keys only: no key at all has weight
+    out, lse = db.run_cache_only()
+    torch.cuda.synchronize()
+    ro, rl = oracle_full(batch, use_tree=False)
+    say(gates(out.float().cpu().numpy(), lse.cpu().numpy(), ro, rl, dtype, "  cached keys only", stress=True))
+
+
 def test_the_kernel_keeps_its_loads_counted(tmp_path):
     """No register spills to scratch (the kernel counts its own outstanding loads), and M0 belongs to
     the HBM -> LDS copies alone (they set it inside assembly, which cannot declare it clobbered)."""

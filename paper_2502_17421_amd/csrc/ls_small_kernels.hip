@@ -398,7 +398,7 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w
                     for (int e = 0; e < 8; ++e) v[e] += d[e];
                 }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] += wk > 0.f ? wk * v[e] : 0.f;  // empty parts may hold anything
+                for (int e = 0; e < 8; ++e) o[e] += wk == 0.f ? 0.f : wk * v[e];  // empty parts may hold anything
             }
         }
     }
@@ -410,12 +410,12 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off, kWave);
     }
-    const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+    const float inv = wsum == 0.f ? 0.f : 1.f / wsum;     // a part whose LSE is NaN makes the row and its LSE NaN
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] *= inv;
     if (live && (!WIDE || group == 0)) {
         store_raw<16>(orow, L8::pack(o));
-        if (sl == 0) w.lse[r] = wsum > 0.f ? top + log2f(wsum) * kLn2 : -INFINITY;
+        if (sl == 0) w.lse[r] = wsum == 0.f ? -INFINITY : top + log2f(wsum) * kLn2;
     }
 }
 

@@ -546,7 +546,7 @@ wave_split_kernel(WaveArgs a)
                 o[u][3] += scale * v[u][k].w;
             }
         }
-        const float inv = l_sum > 0.f ? 1.f / l_sum : 0.f;
+        const float inv = l_sum == 0.f ? 0.f : 1.f / l_sum;  // no key with weight; NaN stays NaN, in the LSE too
         if (m >= rows_kv) continue;
 #pragma unroll
         for (int u = 0; u < PASSES; ++u) {
@@ -566,7 +566,7 @@ wave_split_kernel(WaveArgs a)
             }
         }
         if (tid % TPR == 0) {
-            const float lse = l_sum > 0.f ? (top * c + log2f(l_sum)) * kLn2 : -INFINITY;
+            const float lse = l_sum == 0.f ? -INFINITY : (top * c + log2f(l_sum)) * kLn2;
             (final_row ? a.lse : a.lse_parts)[prow] = lse;
         }
     }

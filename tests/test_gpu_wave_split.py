@@ -145,6 +145,33 @@ def test_keys_that_score_minus_infinity_weigh_nothing(dtype, hq, hkv, d, t, plen
     say(gates(out.float().cpu().numpy(), lse.cpu().numpy(), ro, rl, dtype, "  cached keys only", stress=True))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen", [
+    ("bf16", 8, 2, 128, 5, 300), ("f16", 8, 2, 64, 16, 300),        # one split
+    ("bf16", 8, 2, 128, 8, 9000), ("f16", 8, 2, 128, 16, 9000),     # several splits and the merge of their parts
+    ("bf16", 32, 8, 128, 40, 26000), ("f16", 32, 32, 64, 70, 7000),  # the same merge, kernel that shares tiles
+])
+def test_nan_reaches_the_rows_that_see_it_and_their_lse(dtype, hq, hkv, d, t, plen):
+    """A NaN in a query row makes that row and its LSE NaN, a NaN in a cached key those of all rows of its KV head."""
+    batch = make(dtype, hq, hkv, d, t, [plen], "tree", 24000 + t + plen)
+    group = hq // hkv
+    say(f"NaN {dtype} hq={hq} hkv={hkv} d={d} t={t} plen={plen}")
+    for with_tree in (True, False):
+        db = DeviceBatch(batch)
+        run = db.run_full if with_tree else db.run_cache_only
+        ro, rl = oracle_full(batch, use_tree=with_tree)
+        db.q[0, hq - 1, t // 2, 7] = float("nan")
+        db.k_cache[0, 0, plen // 3, 5] = float("nan")
+        out, lse = run()
+        torch.cuda.synchronize()
+        out, lse = out.float().cpu().numpy(), lse.cpu().numpy()
+        bad = np.zeros((1, hq, t), bool)
+        bad[0, :group] = True
+        bad[0, hq - 1, t // 2] = True
+        assert np.isnan(lse[bad]).all() and np.isnan(out[bad]).all()
+        say(gates(out[~bad], lse[~bad], ro[~bad], rl[~bad], dtype, "  the other rows", stress=True))
+
+
 def test_the_kernel_keeps_its_loads_counted(tmp_path):
     """No register spills to scratch (the kernel counts its own outstanding loads), and M0 belongs to
     the HBM -> LDS copies alone (they set it inside assembly, which cannot declare it clobbered)."""

@@ -778,13 +778,24 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         for (int kk = 0; kk < KSTEPS; ++kk) s_sl[0] = mfma32<F16>(k0f[kk], q_reg[kk], s_sl[0]);
     }
     if (key_first + TK > k_hi) mask_tail(s_sl[0], key_first);
-    if (tree_split) {
-        raise_reference(s_sl[0]);
-    } else {  // the reference exponent: the largest of the first 32 scores (at least one key is valid)
+    {  // the reference exponent: the largest of the first 32 scores (at least one key is valid)
         float mx = s_sl[0][0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s_sl[0][e]);
-        m_run = half_max(mx);
+        mx = half_max(mx);
+        if (tree_split) {
+            // Not that of the tree keys: halves end at 2^-24, and the numerators of cached keys far below the
+            // tree's would lose their bits there.  What the tree keys have added up to follows, in fp32.
+            const float m_new = fmaxf(mx, m_run - 64.f / c);
+            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * c);
+            mx = m_new;
+            l_run *= alpha;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o_acc[mt][e] *= alpha;
+        }
+        m_run = mx;
     }
     mc = m_run * c;
     advance0();

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 from paper_2502_17421_amd import binding as ls
+from paper_2502_17421_amd import synth
 from test_gpu_light_block import make
 from test_gpu_paged import PagedBatch
 from util import DeviceBatch, gates, oracle_full
@@ -104,6 +105,38 @@ def test_infinite_values_stay_with_the_rows_that_see_them(dtype, hq, hkv, d, t, 
     touched[:, :, sees, 3] = touched[:, :, sees, 40] = True
     assert np.array_equal(out[~touched], out0[~touched])
     assert np.all(np.isneginf(out[:, :, sees, 3])) and np.all(np.isnan(out[:, :, sees, 40]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen", [("f16", 64, 32, 64, 40, 7000), ("f16", 32, 8, 128, 64, 26000),
+                                                    ("f16", 32, 8, 128, 16, 9000), ("bf16", 32, 8, 128, 64, 26000)])
+@pytest.mark.parametrize("gap", [22.7, 90.0])
+def test_cached_keys_far_below_the_tree_keep_their_bits(dtype, hq, hkv, d, t, plen, gap):
+    """Every cached key scores 2^-gap of every node, the nodes' values are zero: what is left in the output is the
+    cached keys' part, with the relative error of any other output.  (16 nodes: the kernel whose waves split
+    the keys.)  All scores are exact and equal, so numerators are powers of two next to their own reference;
+    what remains is the rounding of the parts and of the output, one half-ulp each, and the fp32 sums.
+    At 2^-90 the output is zero."""
+    batch = make(dtype, hq, hkv, d, t, [plen], "iid", 34000 + t)
+    seq = batch.seqs[0]
+    seq.q[...] = 0.0
+    seq.q[..., 0] = 4.0
+    seq.k_cache[..., 0] = 0.0
+    seq.k_tree[..., 0] = synth.round_to(np.float32(gap * np.log(2) * np.sqrt(d) / 4), dtype)
+    seq.v_tree[...] = 0.0
+    seq.v_cache[...] = synth.round_to(np.abs(seq.v_cache) + 0.5, dtype)
+    print(f"far below {dtype} hq={hq} hkv={hkv} d={d} t={t} plen={plen} 2^-{gap}", flush=True)
+    db = DeviceBatch(batch)
+    out, lse = whole_call(db)
+    ro, rl = oracle_full(batch)
+    assert np.abs(lse - rl).max() <= 1e-5 * np.abs(rl).max()
+    half_ulp = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8  # of 11 and 8 significant bits, relative
+    if gap > 64:
+        assert np.abs(out - ro).max() <= 2.0 ** -25
+    else:
+        worst = (np.abs(out - ro) / ro).max()
+        print(f"  relative error {worst:.2e}, half an ulp {half_ulp:.2e}", flush=True)
+        assert worst <= 2.2 * half_ulp
 
 
 @pytest.mark.gpu

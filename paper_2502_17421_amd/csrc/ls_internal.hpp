@@ -85,7 +85,7 @@ struct SequenceSplits {
 // (workgroups that gave up, or all of them when spin_limit is 0) and does those too.  So every
 // row is written exactly once, by the same code whoever writes it, and no wait is unbounded.
 // counters == nullptr: the kernel only writes its partial rows; those of the last split include the
-// tree keys if parents != nullptr (see WholeCall; out takes what rounding took off them).
+// tree keys if parents != nullptr (see WholeCall; out takes the lower halves of their values).
 struct FusedTail {
     uint64_t *counters;  // three words per (sequence, KV head, query block); zero before the first call
     const int32_t *parents;
@@ -124,8 +124,8 @@ struct FastDiv {
 
 // Outputs of a whole-path call whose kernels take the tree keys as further key tiles (16-bit inputs).
 // n_splits == 1: out and lse are final.  More: partial rows [b, head, tree row, split] in the problem's
-// type with float LSEs; the last split holds the tree keys (parents != nullptr) and writes what
-// rounding took off its rows into the rows of `out`, for merge_parts_kernel to add.
+// type with float LSEs.  The last split holds the tree keys (parents != nullptr); its rows are in fp32, the
+// upper 16 bits of each value in the partial row and the lower 16 bits in the row of `out`.
 struct WholeCall {
     const int32_t *parents;  // nullptr: cached keys only
     int32_t *err_flag;       // one word per sequence, or nullptr

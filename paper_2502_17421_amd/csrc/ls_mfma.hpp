@@ -123,11 +123,15 @@ template <bool F16> __device__ __forceinline__ float high16(uint32_t u)
     return F16 ? half_to_float((uint16_t)(u >> 16)) : __uint_as_float(u & 0xffff0000u);
 }
 
-// what rounding x to `rounded` took off (nothing if the result is not finite)
-__device__ __forceinline__ float rounding_rest(float x, float rounded)
+// The row of a split that holds tree keys leaves in fp32: the upper halves of its values in its row of the parts,
+// the lower halves in the row of `out` (merge_parts_kernel joins them).
+__device__ __forceinline__ uint32_t upper_halves(float a, float b)
 {
-    const float r = x - rounded;
-    return fabsf(r) < INFINITY ? r : 0.f;
+    return __float_as_uint(a) >> 16 | (__float_as_uint(b) & 0xffff0000u);
+}
+__device__ __forceinline__ uint32_t lower_halves(float a, float b)
+{
+    return (__float_as_uint(a) & 0xffffu) | __float_as_uint(b) << 16;
 }
 
 // ---- tree keys on the matrix cores ------------------------------------------------------------

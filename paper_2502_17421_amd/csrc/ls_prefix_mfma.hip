@@ -861,8 +861,10 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
 #pragma unroll
             for (int rg = 0; rg < 4; ++rg) {
                 uint2 v;
-                v.x = pack16<F16>(o_acc[mt][4 * rg + 0] * inv, o_acc[mt][4 * rg + 1] * inv);
-                v.y = pack16<F16>(o_acc[mt][4 * rg + 2] * inv, o_acc[mt][4 * rg + 3] * inv);
+                const float x0 = o_acc[mt][4 * rg + 0] * inv, x1 = o_acc[mt][4 * rg + 1] * inv;
+                const float x2 = o_acc[mt][4 * rg + 2] * inv, x3 = o_acc[mt][4 * rg + 3] * inv;
+                v.x = tree_state ? upper_halves(x0, x1) : pack16<F16>(x0, x1);  // wave-uniform
+                v.y = tree_state ? upper_halves(x2, x3) : pack16<F16>(x2, x3);
                 const int chunk = (4 * mt + rg) ^ (li & (CH - 1));
                 *(uint2 *)(mine + li * ROWB + chunk * 16 + lh * 8) = v;
             }
@@ -891,18 +893,15 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
             }
         }
         if (tree_state) {
-            // what the rounding took off these rows: into the rows of `out`, the same way
+            // the lower halves of these rows: into the rows of `out`, the same way
             const int64_t o_off = (int64_t)b * tail.o_stride[0] + hq * tail.o_stride[1] + ti * tail.o_stride[2];
-            auto rest = [&](float x) __attribute__((always_inline)) {
-                return rounding_rest(x, low16<F16>(pack16<F16>(x, x)));
-            };
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
                     uint2 v;
-                    v.x = pack16<F16>(rest(o_acc[mt][4 * rg + 0] * inv), rest(o_acc[mt][4 * rg + 1] * inv));
-                    v.y = pack16<F16>(rest(o_acc[mt][4 * rg + 2] * inv), rest(o_acc[mt][4 * rg + 3] * inv));
+                    v.x = lower_halves(o_acc[mt][4 * rg + 0] * inv, o_acc[mt][4 * rg + 1] * inv);
+                    v.y = lower_halves(o_acc[mt][4 * rg + 2] * inv, o_acc[mt][4 * rg + 3] * inv);
                     const int chunk = (4 * mt + rg) ^ (li & (CH - 1));
                     *(uint2 *)(mine + li * ROWB + chunk * 16 + lh * 8) = v;
                 }

@@ -310,8 +310,8 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
 
 // --------------------------------------------------------------------- (d), whole path ----
 // Merge of the split rows of a whole-path call whose kernels took the tree keys along (WholeCall): per
-// query row n 16-bit rows side by side, their LSEs, and, when the call has a tree, what rounding took
-// off the last one, in the row of `out` that the merged row replaces.
+// query row n 16-bit rows side by side and their LSEs; when the call has a tree, the last one is in fp32, its
+// upper halves in its place and its lower halves in the row of `out` that the merged row replaces.
 //
 // LG = D / 8 lanes hold a row in 16-byte pieces.  WIDE: a wavefront per query row, 64 / LG parts per
 // load instruction; else LG lanes per query row (at most 8 parts).  Every load of a row is issued before
@@ -358,9 +358,9 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w
     float o[8], top = -INFINITY, wsum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
-    RawVec<16> rest{};
+    RawVec<16> low{};
     const int tree_part = w.parents ? n_splits - 1 : -1;
-    if (w.parents) rest = load_raw<16>(orow);
+    if (w.parents) low = load_raw<16>(orow);
     for (int k0 = 0; k0 < n_top; k0 += WIDE ? 64 : 8) {  // one pass up to 64 (8) parts
         const int left = n_splits - k0, n = left < (WIDE ? 64 : 8) ? left : (WIDE ? 64 : 8);  // of this row (may be none)
         const int n_any = n_top - k0;
@@ -392,10 +392,11 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w
                 float v[8];
                 L8::unpack(raw[k], v);
                 if (k0 + part == tree_part) {
-                    float d[8];
-                    L8::unpack(rest, d);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] += d[e];
+                    for (int e = 0; e < 4; ++e) {
+                        v[2 * e] = __uint_as_float(raw[k].w[e] << 16 | (low.w[e] & 0xffffu));
+                        v[2 * e + 1] = __uint_as_float((raw[k].w[e] & 0xffff0000u) | low.w[e] >> 16);
+                    }
                 }
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] += wk == 0.f ? 0.f : wk * v[e];  // empty parts may hold anything

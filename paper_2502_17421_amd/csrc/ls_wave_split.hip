@@ -24,9 +24,9 @@
 // bits (a second output product with the rounding remainders): the few tree keys may carry most of
 // a row's weight.
 //
-// More than one split: the rows leave as 16-bit partials for merge_parts_kernel.  A split that
-// holds tree keys also writes the rounding remainder of its rows, into the rows of `out` itself,
-// which the merge reads before it overwrites them.
+// More than one split: the rows leave as 16-bit partials for merge_parts_kernel, those of the split with
+// the tree keys in fp32: the upper halves as a part row, the lower halves in the rows of `out` itself, which
+// the merge reads before it overwrites them.
 #include <type_traits>
 
 #include "ls_internal.hpp"
@@ -553,16 +553,11 @@ wave_split_kernel(WaveArgs a)
             const int col = (tid % TPR + u * TPR) * 4;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[u][i] *= inv;
-            const uint2 packed = make_uint2(pack16<F16>(o[u][0], o[u][1]), pack16<F16>(o[u][2], o[u][3]));
-            *(uint2 *)(dst + col) = packed;
-            if (has_tree && !final_row) {  // what the rounding took off
-                float r[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t x = i < 2 ? packed.x : packed.y;
-                    r[i] = rounding_rest(o[u][i], i & 1 ? high16<F16>(x) : low16<F16>(x));
-                }
-                *(uint2 *)(orow + col) = make_uint2(pack16<F16>(r[0], r[1]), pack16<F16>(r[2], r[3]));
+            if (has_tree && !final_row) {  // fp32, in two halves
+                *(uint2 *)(dst + col) = make_uint2(upper_halves(o[u][0], o[u][1]), upper_halves(o[u][2], o[u][3]));
+                *(uint2 *)(orow + col) = make_uint2(lower_halves(o[u][0], o[u][1]), lower_halves(o[u][2], o[u][3]));
+            } else {
+                *(uint2 *)(dst + col) = make_uint2(pack16<F16>(o[u][0], o[u][1]), pack16<F16>(o[u][2], o[u][3]));
             }
         }
         if (tid % TPR == 0) {

@@ -139,6 +139,46 @@ def test_cached_keys_far_below_the_tree_keep_their_bits(dtype, hq, hkv, d, t, pl
         assert worst <= 2.2 * half_ulp
 
 
+def half_spacing(a, b, dtype):
+    """Half the distance between neighbouring values of the type at |a| or |b|, the larger one."""
+    bits, low = (11, -24) if dtype == "f16" else (8, -133)
+    exponent = np.frexp(np.maximum(np.maximum(np.abs(a), np.abs(b)), 1e-300))[1]
+    return np.exp2(np.maximum(exponent - bits, low) - 1.0)
+
+
+# prefix lengths of several splits; up to 64 rows per KV head: the kernel whose waves split the keys
+TREE_ALONE = [("bf16", 32, 8, 128, 64, 26000), ("f16", 32, 8, 128, 64, 26000), ("f16", 64, 32, 64, 40, 7000),
+              ("bf16", 32, 8, 128, 16, 9000), ("f16", 8, 2, 64, 12, 9000)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen", TREE_ALONE)
+def test_the_tree_part_is_rounded_once(dtype, hq, hkv, d, t, plen):
+    """The cached keys weigh nothing and every node a row sees weighs the same, so numerators are exact and a row
+    is the mean of the values on its path: fp32 until it is rounded to the output type.  The bound is that
+    rounding and a few fp32 ones (path length times 2^-24) of the mean of the magnitudes; f16 values are small
+    enough to come out subnormal in part."""
+    batch = make(dtype, hq, hkv, d, t, [plen], "iid", 35000 + t)
+    seq = batch.seqs[0]
+    seq.q[...] = 0.0
+    seq.q[..., 0] = 4.0
+    seq.k_cache[..., 0] = synth.round_to(np.float32(-60 * np.log(2) * np.sqrt(d) / 4), dtype)
+    seq.k_tree[..., 0] = 0.0
+    if dtype == "f16":
+        seq.v_tree[...] = synth.round_to(seq.v_tree * 2.0 ** -12, dtype)
+    print(f"tree alone {dtype} hq={hq} hkv={hkv} d={d} t={t} plen={plen}", flush=True)
+    db = DeviceBatch(batch)
+    assert ls.ls_prefix_num_splits(db.desc) > 1
+    out, lse = whole_call(db)
+    ro, rl = oracle_full(batch)
+    assert np.abs(lse - rl).max() <= 1e-5
+    seq.v_tree[...] = np.abs(seq.v_tree)
+    magnitude, _ = oracle_full(batch)
+    excess = (np.abs(out - ro) - half_spacing(out, ro, dtype)) / magnitude
+    print(f"  beyond the output rounding: {excess.max():.2e} of the mean magnitude", flush=True)
+    assert excess.max() <= 2.0 ** -20
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("t,plen", [(40, 13000), (100, 6500)])
 def test_bad_parents_are_cut_and_reported(t, plen):

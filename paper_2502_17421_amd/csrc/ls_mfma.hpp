@@ -136,8 +136,8 @@ __device__ __forceinline__ uint32_t lower_halves(float a, float b)
 
 // ---- tree keys on the matrix cores ------------------------------------------------------------
 // A tree tile holds 32 nodes; a row sees a node when it is an ancestor of the row's own node or that
-// node itself.  Numerators of tree keys keep twice the operand type's significant bits (a second
-// output product with the rounding remainders): the few tree keys may carry most of a row's weight.
+// node itself.  Numerators of tree keys stay in fp32 (add_tree_product), as in the tail kernel: the few tree
+// keys may carry most of a row's weight.
 
 // Ancestors of node `lane` (itself included) as a 64-bit mask, for trees of at most 64 nodes: every
 // round doubles the reach of every node.  anc: the node's parent, valid or -1; all 64 lanes active.
@@ -170,24 +170,50 @@ __device__ __forceinline__ uint32_t take_chain_word(const int32_t *par, int &nod
     return bits;
 }
 
-// Numerators of a tree tile: rounded to the operand type (hi), and what the rounding took off (lo).
+// Numerators of a tree tile in fp32, taken apart into operands of 8 (11) significant bits; returns their sum over
+// this lane's keys.  Three bf16 operands are a numerator exactly.  Two half operands are it to 2^-24 while the second
+// is not subnormal.  Halves are therefore lifted by 2^15, with no score above the reference exponent: this
+// then holds for numerators down to 2^-17, and below the error is 2^-41.  The kernel lifts its sums along (powers
+// of two: exact).
 // m_run: the reference exponent, -inf while the row has seen no key (all scores are -inf then).
+template <bool F16> constexpr int kTreeParts = F16 ? 2 : 3;
+template <bool F16> constexpr float kTreeLift = F16 ? 15.f : 0.f;          // as a power of two
+template <bool F16> constexpr float kTreeUp = F16 ? 0x1p15f : 1.f;
+template <bool F16> constexpr float kTreeDown = F16 ? 0x1p-15f : 1.f;
 template <bool F16>
-__device__ __forceinline__ float tree_numerators(const floatx16 &s, float c, float m_run, uint32_t (&hi)[8],
-                                                 uint32_t (&lo)[8])
+__device__ __forceinline__ float tree_numerators(const floatx16 &s, float c, float m_run,
+                                                 uint32_t (&parts)[kTreeParts<F16>][8])
 {
-    const float mc = m_run == -INFINITY ? 0.f : m_run * c;
+    const float mc = (m_run == -INFINITY ? 0.f : m_run * c) - kTreeLift<F16>;
     float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -mc));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], c, -mc));
+        float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -mc));
+        float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], c, -mc));
         sum += p0 + p1;
-        const uint32_t u = pack16<F16>(p0, p1);
-        hi[e >> 1] = u;
-        lo[e >> 1] = pack16<F16>(p0 - low16<F16>(u), p1 - high16<F16>(u));
+#pragma unroll
+        for (int k = 0; k < kTreeParts<F16>; ++k) {
+            const uint32_t u = pack16<F16>(p0, p1);
+            parts[k][e >> 1] = u;
+            p0 -= low16<F16>(u);
+            p1 -= high16<F16>(u);
+        }
     }
     return sum;
+}
+
+// Output product of a tree tile with these numerators.  frag: the V fragments, f = 16-key half * MT + column tile.
+template <bool F16, int MT, int N>
+__device__ __forceinline__ void add_tree_product(floatx16 (&o)[MT], const bf16x8 (&frag)[N],
+                                                 const uint32_t (&parts)[kTreeParts<F16>][8])
+{
+#pragma unroll
+    for (int k = 0; k < kTreeParts<F16>; ++k)
+#pragma unroll
+        for (int f = 0; f < N; ++f) {
+            const uint32_t *u = parts[k] + 4 * (f / MT);
+            o[f % MT] = mfma32<F16>(frag[f], __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3])), o[f % MT]);
+        }
 }
 
 // Infinite and NaN values of a node must not reach rows that do not see it, but a matrix product carries

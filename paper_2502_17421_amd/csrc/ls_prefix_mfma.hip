@@ -55,7 +55,7 @@
 // before its cached keys, in LDS stages that the first window of cached tiles leaves free, and the call ends
 // with a merge alone instead of the tail kernel (32k keys, 64 nodes: tail 11.7 us, merge 7.6; 640 rows per KV
 // head in four sequences: 20.8 and 11.9).  A tree tile is not pipelined (about 2 us against 0.6 for a cached one:
-// mask, score product, softmax, output product of the numerators and of their rounding remainders, one
+// mask, score product, softmax, output product of fp32 numerators in two or three parts, one
 // after the other in all waves), so that split gets fewer cached tiles.
 //
 // MFMA operand layouts: ls_mfma.hpp.
@@ -204,7 +204,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     plen = plen < 0 ? 0 : (plen > p.max_prefix_len ? p.max_prefix_len : plen);
     int split_len = plan.split_len;
     // Whole-path call: the last split also takes the tree keys, and as many cached tiles less as they
-    // cost (a tree tile has the output product of the rounding remainders as well and is not pipelined).
+    // cost (a tree tile's output product takes fp32 numerators, and it is not pipelined).
     const bool with_tree = !FUSED && tail.parents != nullptr;
     const bool tree_split = with_tree && split == n_splits - 1;
     const int tree_tiles = tree_split ? (p.n_tree + TK - 1) / TK : 0;
@@ -500,12 +500,13 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         }
         return sum;
     };
-    auto raise_reference = [&](const floatx16 &s_acc) __attribute__((always_inline)) {  // general path: lift m_run, rescale O and l
+    // general path: lift m_run, rescale O and l, when a score exceeds it by more than `lazy` powers of two
+    auto raise_reference = [&](const floatx16 &s_acc, float lazy) __attribute__((always_inline)) {
         float mx = s_acc[0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s_acc[e]);
         mx = half_max(mx);
-        const bool grow = (mx - m_run) * c > kLazy;  // also true while m_run is -inf
+        const bool grow = (mx - m_run) * c > lazy;  // also true while m_run is -inf
         if (__any(grow)) {
             const float m_new = fmaxf(m_run, mx);
             // a step whose keys are all masked leaves m_new = -inf; keep arithmetic finite
@@ -619,7 +620,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         if constexpr (QK) s_sl[X] = s_new;
         if constexpr (SM) {
             if (__any(!(sum < kSumCap<F16>))) {  // also catches inf and nan: redo this step on the general path
-                raise_reference(s_sl[Y]);
+                raise_reference(s_sl[Y], kLazy);
                 sum = numerators(s_sl[Y], p_sl[Y]);
                 mc = m_run * c;
             }
@@ -733,21 +734,21 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     if (!((seen >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
-                raise_reference(s);
-                uint32_t hi[8], lo[8];
-                l_run += tree_numerators<F16>(s, c, m_run, hi, lo);
+                raise_reference(s, F16 ? 0.f : kLazy);
+                uint32_t parts[kTreeParts<F16>][8];
+                l_run += tree_numerators<F16>(s, c, m_run, parts);
 #pragma unroll
                 for (int f = 0; f < KSTEPS; ++f) frag[f] = read_v(v_at, f);
                 if (drop_not_finite<F16>(frag)) par_lds[LS_MAX_TREE + NW + wave] = 2;
-#pragma unroll
-                for (int f = 0; f < KSTEPS; ++f)
-                    o_acc[f % MT] = mfma32<F16>(frag[f], __builtin_bit_cast(bf16x8, make_uint4(hi[4 * (f / MT)], hi[4 * (f / MT) + 1],
-                                                                                               hi[4 * (f / MT) + 2], hi[4 * (f / MT) + 3])), o_acc[f % MT]);
-#pragma unroll
-                for (int f = 0; f < KSTEPS; ++f)
-                    o_acc[f % MT] = mfma32<F16>(frag[f], __builtin_bit_cast(bf16x8, make_uint4(lo[4 * (f / MT)], lo[4 * (f / MT) + 1],
-                                                                                               lo[4 * (f / MT) + 2], lo[4 * (f / MT) + 3])), o_acc[f % MT]);
+                add_tree_product<F16>(o_acc, frag, parts);
             }
+        }
+        if constexpr (F16) {
+            l_run *= kTreeDown<F16>;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o_acc[mt][e] *= kTreeDown<F16>;
         }
     }
     // A wave whose rows all lie past the last query row of the KV head (the last query block of a
@@ -856,18 +857,20 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         // The rows go through LDS instead (each wave its own 32 rows, so no further barrier)
         // and leave as whole rows, 16 bytes per lane.
         uint8_t *mine = smem + wave * (32 * ROWB);
+        auto stage = [&](auto word) __attribute__((always_inline)) {  // word: two values to 32 bits
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                uint2 v;
-                const float x0 = o_acc[mt][4 * rg + 0] * inv, x1 = o_acc[mt][4 * rg + 1] * inv;
-                const float x2 = o_acc[mt][4 * rg + 2] * inv, x3 = o_acc[mt][4 * rg + 3] * inv;
-                v.x = tree_state ? upper_halves(x0, x1) : pack16<F16>(x0, x1);  // wave-uniform
-                v.y = tree_state ? upper_halves(x2, x3) : pack16<F16>(x2, x3);
-                const int chunk = (4 * mt + rg) ^ (li & (CH - 1));
-                *(uint2 *)(mine + li * ROWB + chunk * 16 + lh * 8) = v;
-            }
+                for (int rg = 0; rg < 4; ++rg) {
+                    uint2 v;
+                    v.x = word(o_acc[mt][4 * rg + 0] * inv, o_acc[mt][4 * rg + 1] * inv);
+                    v.y = word(o_acc[mt][4 * rg + 2] * inv, o_acc[mt][4 * rg + 3] * inv);
+                    const int chunk = (4 * mt + rg) ^ (li & (CH - 1));
+                    *(uint2 *)(mine + li * ROWB + chunk * 16 + lh * 8) = v;
+                }
+        };
+        if (tree_state) stage(upper_halves);  // (wave-uniform)
+        else stage(pack16<F16>);
         // the row index and validity of query row j live in lane j
         const uint32_t my_row = (uint32_t)part_row;
         constexpr int ROWS_PER_STORE = 64 / CH;
@@ -895,16 +898,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
         if (tree_state) {
             // the lower halves of these rows: into the rows of `out`, the same way
             const int64_t o_off = (int64_t)b * tail.o_stride[0] + hq * tail.o_stride[1] + ti * tail.o_stride[2];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    uint2 v;
-                    v.x = lower_halves(o_acc[mt][4 * rg + 0] * inv, o_acc[mt][4 * rg + 1] * inv);
-                    v.y = lower_halves(o_acc[mt][4 * rg + 2] * inv, o_acc[mt][4 * rg + 3] * inv);
-                    const int chunk = (4 * mt + rg) ^ (li & (CH - 1));
-                    *(uint2 *)(mine + li * ROWB + chunk * 16 + lh * 8) = v;
-                }
+            stage(lower_halves);
 #pragma unroll
             for (int j = 0; j < 32 / ROWS_PER_STORE; ++j) {
                 const int row = j * ROWS_PER_STORE + lane / CH;

@@ -20,9 +20,7 @@
 // Tree keys.  The tiles of the tree follow the cached tiles of the last split; the visibility of a
 // row is a mask of its ancestors.  Up to 64 nodes it is built in registers, lane = node, by
 // doubling the reach of every node (log2(depth) exchanges); larger trees walk the parent chain
-// in LDS, once per tile.  The numerators of tree keys keep twice the operand type's significant
-// bits (a second output product with the rounding remainders): the few tree keys may carry most of
-// a row's weight.
+// in LDS, once per tile.  The numerators of tree keys stay in fp32 (add_tree_product).
 //
 // More than one split: the rows leave as 16-bit partials for merge_parts_kernel, those of the split with
 // the tree keys in fp32: the upper halves as a part row, the lower halves in the rows of `out` itself, which
@@ -363,18 +361,18 @@ wave_split_kernel(WaveArgs a)
             s = mfma32<F16>(frag[kk], q, s);
         }
     };
-    // raises the reference exponent of row tile rt where the scores are far above it
-    // (start: nothing has been accumulated yet)
-    auto raise = [&](int rt, const floatx16 &s, bool start) __attribute__((always_inline)) {
+    // raises the reference exponent of row tile rt where the scores are more than `lazy` powers of two above it
+    // (start: nothing has been accumulated yet; up: the sums so far are multiplied by this as well)
+    auto raise = [&](int rt, const floatx16 &s, bool start, float lazy, float up) __attribute__((always_inline)) {
         float mx = s[0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
         mx = half_max(mx);
         if (start) {
             m_run[rt] = mx;
-        } else if (__any((mx - m_run[rt]) * c > kRaise)) {  // also while m_run is -inf
+        } else if (up != 1.f || __any((mx - m_run[rt]) * c > lazy)) {  // also while m_run is -inf
             const float m_new = fmaxf(m_run[rt], mx);
-            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run[rt] - m_new) * c);
+            const float alpha = (m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((m_run[rt] - m_new) * c)) * up;
             m_run[rt] = m_new;
             l_run[rt] *= alpha;
 #pragma unroll
@@ -415,7 +413,7 @@ wave_split_kernel(WaveArgs a)
                 for (int e = 0; e < 16; ++e)
                     if (8 * (e >> 2) + 4 * lh + (e & 3) >= valid) s[e] = -INFINITY;
             }
-            raise(rt, s, t == wave);
+            raise(rt, s, t == wave, kRaise, 1.f);
             // a row all of whose scores so far are -inf has the reference -inf: its numerators are zeros
             const float mc = m_run[rt] == -INFINITY ? 0.f : m_run[rt] * c;
             float sum = 0.f;
@@ -448,7 +446,6 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             bf16x8 frag[KSTEPS];
-            uint32_t hi[8], lo[8];  // numerators, and what rounding them took off
             read_k_tile(frag);
             floatx16 s;
             scores(frag, rt, s);
@@ -456,13 +453,13 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 if (!((seen >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
-            raise(rt, s, t == wave);
-            l_run[rt] += tree_numerators<F16>(s, c, m_run[rt], hi, lo);
+            raise(rt, s, t == wave, F16 ? 0.f : kRaise, t - NW < n_pref ? kTreeUp<F16> : 1.f);
+            uint32_t parts[kTreeParts<F16>][8];
+            l_run[rt] += tree_numerators<F16>(s, c, m_run[rt], parts);
             __builtin_amdgcn_sched_barrier(0);  // the values are not read early: no registers to spare
             read_v_tile(frag);
             not_finite |= drop_not_finite<F16>(frag);
-            add_product(frag, rt, hi);
-            add_product(frag, rt, lo);
+            add_tree_product<F16>(o_acc[rt], frag, parts);
         }
         if (t + NW < n_all) request(false, t + NW, pages);
     }
@@ -536,7 +533,8 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
         for (int k = 0; k < NW; ++k) {
             if (k >= n_active) continue;
-            const float scale = s[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s[k].x - top) * c);
+            const bool tree = ((k - n_pref) & (NW - 1)) < n_all - n_pref;  // this wave had tree tiles: its sums are lifted
+            const float scale = s[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s[k].x - top) * c) * (tree ? kTreeDown<F16> : 1.f);
             l_sum += scale * s[k].y;
 #pragma unroll
             for (int u = 0; u < PASSES; ++u) {

@@ -180,6 +180,42 @@ def test_the_tree_part_is_rounded_once(dtype, hq, hkv, d, t, plen):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen", TREE_ALONE + [("bf16", 8, 2, 128, 40, 100), ("f16", 8, 2, 64, 16, 0)])
+@pytest.mark.parametrize("below", [0, 20])
+def test_numerators_of_tree_keys_stay_in_fp32(dtype, hq, hkv, d, t, plen, below):
+    """The cached keys weigh nothing; the nodes' scores lie within one power of two, so the arguments of the
+    exponential are at most 1 and its fp32 error a few 2^-24; values of both signs cancel, so that a numerator
+    rounded to 16 bits shows in the sum.  below = 20: the root outweighs the others 2^20 times and its value is zero
+    (arguments up to 20, each 2^-24 of one 20 * ln 2 * 2^-24 of the numerator).  (The last two: one split.)"""
+    batch = make(dtype, hq, hkv, d, t, [plen], "iid", 36000 + t)
+    seq = batch.seqs[0]
+    rng = np.random.default_rng(36)
+    unit = np.log(2) * np.sqrt(d) / 4  # of k, per power of two of the weight
+    seq.q[...] = 0.0
+    seq.q[..., 0] = 4.0
+    if plen:
+        seq.k_cache[..., 0] = synth.round_to(np.float32(-60 * unit), dtype)
+        seq.v_cache[...] = 0.0
+    seq.k_tree[..., 0] = synth.round_to((-unit * rng.random(seq.k_tree.shape[:2])).astype(np.float32), dtype)
+    if below:
+        seq.k_tree[:, 0, 0] = synth.round_to(np.float32(below * unit), dtype)
+        seq.v_tree[...] = synth.round_to(seq.v_tree * 256, dtype)
+        seq.v_tree[:, 0] = 0.0
+    print(f"numerators {dtype} hq={hq} hkv={hkv} d={d} t={t} plen={plen} below={below}", flush=True)
+    db = DeviceBatch(batch)
+    out, lse = whole_call(db)
+    ro, rl = oracle_full(batch)
+    assert np.abs(lse - rl).max() <= 1e-5
+    seq.v_tree[...] = np.abs(seq.v_tree)
+    magnitude, _ = oracle_full(batch)
+    seen = magnitude > 0
+    excess = ((np.abs(out - ro) - half_spacing(out, ro, dtype))[seen] / magnitude[seen]).max()
+    print(f"  beyond the output rounding: {excess:.2e} of the mean magnitude", flush=True)
+    assert excess <= (2.0 ** -18 if below else 2.0 ** -20)
+    assert np.all(out[~seen] == 0.0)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("t,plen", [(40, 13000), (100, 6500)])
 def test_bad_parents_are_cut_and_reported(t, plen):
     batch = make("bf16", 32, 8, 128, t, [plen, plen], "tree", 33000 + t)

@@ -282,11 +282,11 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, co
 {
     WholePlan w{0, 0, false};
     const int rows_kv = d.n_q_heads / d.n_kv_heads * d.n_tree;
-    const int tiles = (d.max_prefix_len + 31) / 32 + (with_tree ? (d.n_tree + 31) / 32 : 0);
+    const int64_t tiles = ((int64_t)d.max_prefix_len + 31) / 32 + (with_tree ? (d.n_tree + 31) / 32 : 0);
     // the ranges in which the kernels' divisions by multiplication are exact
     const int64_t heads = (int64_t)d.batch * d.n_q_heads;
     if (heads * d.n_tree * d.n_tree >= (1ll << 32) || heads * d.n_q_heads >= (1ll << 32) ||
-        ((int64_t)tiles + plan.n_splits) * plan.n_splits >= (1ll << 32) ||
+        (tiles + plan.n_splits) * plan.n_splits >= (1ll << 32) ||
         (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 31) / 32) * plan.n_splits * ((rows_kv + 31) / 32 + plan.n_splits) >= (1ll << 32))
         return w;
     // rows of the tree are addressed with 32-bit offsets inside a tile

@@ -1,0 +1,133 @@
+"""Which kernels a call runs, on the CPU: the host code of the library (ls_api.hip) with launchers in place of the
+kernels' that only write down what they were asked for."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2502_17421_amd import binding as ls
+from paper_2502_17421_amd import build as ls_build
+
+STUB = r"""
+#include "ls_api.hip"
+#include <cstdio>
+
+static char route_text[512];
+#define SAY(...) std::snprintf(route_text + std::strlen(route_text), sizeof(route_text) - std::strlen(route_text), __VA_ARGS__)
+
+namespace ls {
+hipError_t launch_wave_split(const Problem &, int, int row_tiles, const WholeCall &w, hipStream_t)
+{
+    SAY("wave_split(rows=%d,splits=%d%s) ", 32 * row_tiles, w.n_splits, w.parents ? ",tree" : "");
+    return hipSuccess;
+}
+hipError_t launch_prefix_mfma(const Problem &, int, const SplitPlan &plan, const Partials &, const MaskJob &job,
+                              const FusedTail &tail, hipStream_t)
+{
+    SAY("prefix(splits=%d%s%s%s%s) ", plan.n_splits, tail.parents ? ",tree" : "", job.parents ? ",mask" : "",
+        plan.balanced ? ",dealt" : "", tail.counters ? ",fused" : "");
+    return hipSuccess;
+}
+hipError_t launch_prefix_valu(const Problem &, int, const SplitPlan &plan, const Partials &, const MaskJob &, hipStream_t)
+{
+    SAY("float(splits=%d) ", plan.n_splits);
+    return hipSuccess;
+}
+hipError_t launch_merge_parts(const Problem &, int, const WholeCall &, hipStream_t) { SAY("merge "); return hipSuccess; }
+hipError_t launch_tree_merge(const Problem &, int, const uint64_t *mask, const Partials &, int32_t, void *, const int64_t *,
+                             float *, hipStream_t)
+{
+    SAY(mask ? "tail " : "tail(cached) ");
+    return hipSuccess;
+}
+hipError_t launch_tree_mask(const int32_t *, int32_t, int32_t, uint64_t *, int32_t *, hipStream_t) { SAY("mask "); return hipSuccess; }
+hipError_t launch_tree_attn(const Problem &, int, const uint64_t *, const Partials &, hipStream_t) { return hipSuccess; }
+hipError_t launch_merge(int32_t, int32_t, int32_t, int32_t, int, int32_t, const void *, int, const float *, void *,
+                        const int64_t *, float *, hipStream_t) { return hipSuccess; }
+hipError_t launch_clear_words(uint32_t *, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_tree_accept(const int32_t *, const int32_t *, const int32_t *, int32_t, int32_t, int32_t *, int32_t *,
+                              int32_t *, int32_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_kv_commit(const Problem &, int, const int32_t *, const int32_t *, void *, void *, int32_t *, int32_t *,
+                            hipStream_t) { return hipSuccess; }
+int prefix_mfma_query_blocks(const Problem &p) { return (p.group * p.n_tree + 255) / 256; }
+bool prefix_mfma_supports(const Problem &, int dtype) { return is_16bit(dtype); }
+}  // namespace ls
+
+extern "C" const char *take_route()
+{
+    static char last[512];
+    std::memcpy(last, route_text, sizeof(last));
+    route_text[0] = 0;
+    return last;
+}
+"""
+
+
+def build(folder, *host_flags):
+    src, out = folder / "routes.hip", folder / "routes.so"
+    src.write_text(STUB)
+    flags = [f for f in ls_build.FLAGS if f not in ("-O3", "-Wall")]
+    host = [x for f in host_flags for x in ("-Xarch_host", f)]
+    subprocess.run([ls_build.HIPCC, *flags, "-O1", *host, "-o", str(out), str(src)], check=True, stderr=subprocess.DEVNULL)
+    return str(out)
+
+
+def load(path):
+    loaded = ctypes.CDLL(path)
+    loaded.take_route.restype = ctypes.c_char_p
+    vp, dp = ctypes.c_void_p, ctypes.POINTER(ls.ls_desc)
+    loaded.ls_hybrid_tree_attn.argtypes = [dp] + [vp] * 10 + [ctypes.c_size_t, vp]
+    loaded.ls_cache_attn.argtypes = [dp] + [vp] * 7 + [ctypes.c_size_t, vp]
+    loaded.ls_workspace_bytes.argtypes = [dp, ctypes.POINTER(ctypes.c_size_t)]
+    return loaded
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    return load(build(tmp_path_factory.mktemp("routes")))
+
+
+def desc(hq, hkv, d, t, capacity, batch=1, dtype=ls.LS_BF16):
+    x = ls.ls_desc()
+    x.batch, x.n_q_heads, x.n_kv_heads, x.head_dim, x.n_tree, x.max_prefix_len, x.dtype = batch, hq, hkv, d, t, capacity, dtype
+    for field, heads, rows in ((x.q_stride, hq, t), (x.o_stride, hq, t), (x.kc_stride, hkv, capacity), (x.vc_stride, hkv, capacity),
+                               (x.kt_stride, hkv, t), (x.vt_stride, hkv, t)):
+        field[0], field[1], field[2] = heads * rows * d, rows * d, d
+    return x
+
+
+# addresses far apart; nothing is read
+Q, K, V, LENS, KT, VT, PARENTS, OUT, LSE, WORK = ((i + 1) << 44 for i in range(10))
+
+
+def route(lib, x, tree=True, **at):
+    a = dict(q=Q, k=K, v=V, lens=LENS, kt=KT, vt=VT, parents=PARENTS, out=OUT, lse=LSE)
+    a.update(at)
+    n = ctypes.c_size_t(0)
+    assert lib.ls_workspace_bytes(ctypes.byref(x), ctypes.byref(n)) == 0
+    if tree:
+        rc = lib.ls_hybrid_tree_attn(ctypes.byref(x), a["q"], a["k"], a["v"], a["lens"], a["kt"], a["vt"], a["parents"],
+                                     a["out"], a["lse"], WORK, n.value, None)
+    else:
+        rc = lib.ls_cache_attn(ctypes.byref(x), a["q"], a["k"], a["v"], a["lens"], a["out"], a["lse"], WORK, n.value, None)
+    assert rc == 0, rc
+    return lib.take_route().decode().split()
+
+
+def open_ended(lib):
+    for hq, hkv, t in ((4, 1, 5), (8, 1, 40)):
+        x = desc(hq, hkv, 128, t, 2 ** 31 - 1)
+        assert route(lib, x) == ["prefix(splits=262144,mask)", "tail"]
+        assert route(lib, x, tree=False) == ["prefix(splits=262144)", "tail(cached)"]
+
+
+def test_an_open_ended_capacity_does_not_overflow(tmp_path):
+    """max_prefix_len is a bound and may be 2^31 - 1.  (In a child process: an overflow of the planner's integers
+    traps.)"""
+    path = build(tmp_path, "-fsanitize=signed-integer-overflow", "-fsanitize-trap=signed-integer-overflow")
+    here = os.path.dirname(os.path.abspath(__file__))
+    code = f"import sys; sys.path[:0] = [{os.path.dirname(here)!r}, {here!r}]; import test_call_routes as t; t.open_ended(t.load({path!r}))"
+    done = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    assert done.returncode == 0, (done.returncode, done.stderr[-2000:])

@@ -305,11 +305,12 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, co
     // two and 18.6 on the kernel that shares tiles between waves; 1600 keys 14.9, 16.3, 19.8).
     constexpr int kDirectTiles = 50;
     constexpr int kOneSplitTiles = 80, kSplitTiles = 136;
-    if (rows_kv <= 64) {
+    const int few_row_splits = tiles <= kDirectTiles ? 1 : plan.n_splits;
+    if (rows_kv <= 64 && (int64_t)d.batch * d.n_kv_heads * few_row_splits < (1ll << 32) / 512) {  // HIP: fewer than 2^32 threads
         // every wave of a workgroup holds all the query rows of the KV head (32 rows per KV head, 16k keys: 52.7
         // against 57.3 us; 64 rows, 32k keys: 34.6 against 35.4; 32 rows, 8k keys: 14.2 against 20.6)
         w.row_tiles = rows_kv <= 32 ? 1 : 2;
-        w.n_splits = tiles <= kDirectTiles ? 1 : plan.n_splits;
+        w.n_splits = few_row_splits;
         w.ride = true;
     } else if (tiles <= kDirectTiles) {
         w.row_tiles = 1;

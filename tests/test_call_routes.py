@@ -131,3 +131,11 @@ def test_an_open_ended_capacity_does_not_overflow(tmp_path):
     code = f"import sys; sys.path[:0] = [{os.path.dirname(here)!r}, {here!r}]; import test_call_routes as t; t.open_ended(t.load({path!r}))"
     done = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
     assert done.returncode == 0, (done.returncode, done.stderr[-2000:])
+
+
+def test_a_launch_has_fewer_threads_than_hip_takes(lib):
+    """One workgroup of 512 threads per sequence, head and split would be 4.9e9 threads here; the kernel that shares
+    tiles has 256 per workgroup."""
+    x = desc(1, 1, 64, 1, 1_200_000, batch=65535)
+    assert route(lib, x) == ["prefix(splits=147,tree)", "merge"]
+    assert route(lib, x, tree=False) == ["prefix(splits=147)", "merge"]

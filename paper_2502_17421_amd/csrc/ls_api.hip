@@ -267,19 +267,34 @@ struct WholePlan {
     bool ride;
 };
 
-// Whether q and out share memory (in-place calls: `out` cannot hold remainders while q is still read).
-bool q_overlaps_out(const ls_desc &d, const void *q, const void *out)
+// Whether out or lse share memory with what the whole call reads while it writes them (q, and the cached keys,
+// lengths and parents, which the kernels of the tail route are done with before the first output is written): in-place
+// calls take that route.  A pool of pages has no known end; only its first page is looked at.
+bool outputs_overlap_inputs(const ls_desc &d, const Problem &p, const int32_t *parents, const void *out, const void *lse)
 {
-    auto extent = [&](const int64_t s[3]) {
-        return (((int64_t)d.batch - 1) * s[0] + ((int64_t)d.n_q_heads - 1) * s[1] + ((int64_t)d.n_tree - 1) * s[2] + d.head_dim) *
-               (int64_t)elem_size(d.dtype);
+    auto extent = [&](const int64_t s[3], int64_t n0, int64_t n1, int64_t n2) -> uintptr_t {
+        if (n2 <= 0) return 0;
+        return (uintptr_t)(((n0 - 1) * s[0] + (n1 - 1) * s[1] + (n2 - 1) * s[2] + d.head_dim) * (int64_t)elem_size(d.dtype));
     };
-    const uintptr_t q0 = (uintptr_t)q, o0 = (uintptr_t)out;
-    return q0 < o0 + (uintptr_t)extent(d.o_stride) && o0 < q0 + (uintptr_t)extent(d.q_stride);
+    const uintptr_t out_bytes = extent(d.o_stride, d.batch, d.n_q_heads, d.n_tree);
+    const uintptr_t lse_bytes = (uintptr_t)d.batch * d.n_q_heads * d.n_tree * sizeof(float);
+    auto overlaps = [&](const void *in, uintptr_t bytes) {
+        const uintptr_t i0 = (uintptr_t)in, o0 = (uintptr_t)out, l0 = (uintptr_t)lse;
+        return in && bytes && ((i0 < o0 + out_bytes && o0 < i0 + bytes) || (i0 < l0 + lse_bytes && l0 < i0 + bytes));
+    };
+    const int64_t n0 = p.block_table ? 1 : d.batch, rows = p.block_table ? 1ll << p.page_shift : d.max_prefix_len;
+    return overlaps(p.q, extent(d.q_stride, d.batch, d.n_q_heads, d.n_tree)) ||
+           overlaps(p.k_cache, extent(d.kc_stride, n0, d.n_kv_heads, d.max_prefix_len ? rows : 0)) ||
+           overlaps(p.v_cache, extent(d.vc_stride, n0, d.n_kv_heads, d.max_prefix_len ? rows : 0)) ||
+           overlaps(p.prefix_lens, (uintptr_t)d.batch * sizeof(int32_t)) ||
+           overlaps(parents, (uintptr_t)d.batch * d.n_tree * sizeof(int32_t));
 }
 
-WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, const void *q, const void *out)
+// parents: nullptr for the cached keys alone
+WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, const int32_t *parents, const void *out,
+                     const void *lse)
 {
+    const bool with_tree = parents != nullptr;
     WholePlan w{0, 0, false};
     const int rows_kv = d.n_q_heads / d.n_kv_heads * d.n_tree;
     const int64_t tiles = ((int64_t)d.max_prefix_len + 31) / 32 + (with_tree ? (d.n_tree + 31) / 32 : 0);
@@ -291,7 +306,7 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, bool with_tree, co
         return w;
     // rows of the tree are addressed with 32-bit offsets inside a tile
     if (with_tree && (d.kt_stride[2] >= (1 << 24) || d.vt_stride[2] >= (1 << 24))) return w;
-    if (q_overlaps_out(d, q, out)) return w;
+    if (outputs_overlap_inputs(d, p, parents, out, lse)) return w;
     // With tree keys on its last split the cached-key kernel of a 64-node tree takes 6 us longer there (two tiles
     // that nothing overlaps, against 0.6 us per cached tile), which re-cutting the cached keys hides only
     // where a split is long; the tail kernel takes 3 to 9 us longer than the merge.  Measured, tail kernel against
@@ -529,7 +544,7 @@ int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, c
     Problem p = make_problem(*desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree);
     p.prefix_len_all = prefix_len_all;
     if (prefix_mfma_supports(p, desc->dtype) && !single_launch) {
-        const WholePlan whole = plan_whole(*desc, plan, true, q, out);
+        const WholePlan whole = plan_whole(*desc, plan, p, parents, out, lse);
         if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, o_parts, lse_parts, (SequenceSplits *)mask, s);
     }
 
@@ -656,7 +671,7 @@ int ls_cache_attn(const ls_desc *desc, const void *q, const void *k_cache, const
     const bool mfma = prefix_mfma_supports(p, desc->dtype);
     if (!mfma && is_16bit(desc->dtype)) return LS_ERR_UNSUPPORTED;
     if (mfma) {
-        const WholePlan whole = plan_whole(*desc, plan, false, q, out);
+        const WholePlan whole = plan_whole(*desc, plan, p, nullptr, out, lse);
         if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, (SequenceSplits *)(base + w.off_mask), s);
     }
     const Partials parts{o_parts, lse_parts, w.n_parts, 0, is_16bit(desc->dtype), 1};
@@ -749,7 +764,7 @@ int ls_hybrid_tree_attn_paged(const ls_desc *desc, const void *q, const void *k_
     if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
-    const WholePlan whole = plan_whole(*desc, plan, true, q, out);
+    const WholePlan whole = plan_whole(*desc, plan, p, parents, out, lse);
     if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, parts.o, parts.lse, (SequenceSplits *)mask, s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{parents, mask, err}, FusedTail{}, s) != hipSuccess) return LS_ERR_HIP;
     if (launch_tree_merge(p, desc->dtype, mask, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)
@@ -779,7 +794,7 @@ int ls_cache_attn_paged(const ls_desc *desc, const void *q, const void *k_pages,
     if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
     const Partials parts{base + w.off_o, (float *)(base + w.off_lse), w.n_parts, 0, 1, 1};
     hipStream_t s = (hipStream_t)stream;
-    const WholePlan whole = plan_whole(*desc, plan, false, q, out);
+    const WholePlan whole = plan_whole(*desc, plan, p, nullptr, out, lse);
     if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, parts.o, parts.lse, (SequenceSplits *)(base + w.off_mask), s);
     if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s) != hipSuccess)
         return LS_ERR_HIP;

@@ -139,3 +139,21 @@ def test_a_launch_has_fewer_threads_than_hip_takes(lib):
     x = desc(1, 1, 64, 1, 1_200_000, batch=65535)
     assert route(lib, x) == ["prefix(splits=147,tree)", "merge"]
     assert route(lib, x, tree=False) == ["prefix(splits=147)", "merge"]
+
+
+@pytest.mark.parametrize("shape", [(8, 2, 128, 8, 300), (8, 2, 128, 8, 9000), (32, 8, 128, 64, 32768)])
+def test_outputs_over_inputs_take_the_route_that_reads_them_first(lib, shape):
+    """What a call reads only before it writes its outputs on the tail route may lie under them: the query rows they
+    replace, cached rows, lengths, parents."""
+    x = desc(*shape)
+    apart = route(lib, x)
+    assert apart[-1] != "tail"
+    cache_bytes = shape[1] * shape[4] * shape[2] * 2
+    out_bytes = shape[0] * shape[3] * shape[2] * 2
+    for at in ({"out": Q}, {"out": K + cache_bytes - 16}, {"out": V - out_bytes + 16}, {"out": LENS - out_bytes + 16},
+               {"lse": PARENTS}, {"lse": K + 16}):
+        assert route(lib, x, **at)[-1] == "tail", at
+        if "lse" not in at or at["lse"] != PARENTS:
+            assert route(lib, x, tree=False, **at)[-1] == "tail(cached)", at
+    for at in ({"out": K + cache_bytes}, {"out": V - out_bytes}, {"out": Q + out_bytes}, {"lse": KT}):
+        assert route(lib, x, **at) == apart

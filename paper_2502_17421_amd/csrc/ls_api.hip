@@ -319,6 +319,16 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     // of a split call takes (64 rows per KV head, 8 KV heads: 700 keys 11.0 us in one split against 12.9 in
     // two and 18.6 on the kernel that shares tiles between waves; 1600 keys 14.9, 16.3, 19.8).
     constexpr int kDirectTiles = 50;
+    // With more than 64 rows every 32-row workgroup copies all keys of its head again, which costs nothing while
+    // the workgroups run in a round or two, the last one not nearly empty.  Measured, the 256-row kernel against this
+    // one, head_dim 128: 192 rows per KV head x 1200 keys, 768 workgroups 44.3 / 43.8 us, 1536 72.0 / 95.6; 768 rows,
+    // 768 workgroups 44.4 / 43.5, 1536 73.7 / 86.0; 1600 rows x 1200 keys, 400 workgroups 34.0 / 30.0, 800
+    // 45.0 / 56.7; 2080 rows x 1144 keys, 260 workgroups 28.7 / 31.3.  At head_dim 64 two workgroups share a
+    // compute unit and it is ahead throughout (1600 rows x 1200 keys, 3200 workgroups 102.6 / 90.4).
+    const int64_t row_blocks = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 31) / 32), cus = compute_units();
+    const int64_t rounds = (row_blocks + cus - 1) / cus;
+    const bool few_blocks = d.head_dim == 64 || rounds == 1 ||
+                            (rows_kv <= 768 ? rounds <= 3 : rounds == 2 && 4 * row_blocks >= 6 * cus);
     constexpr int kOneSplitTiles = 80, kSplitTiles = 136;
     const int few_row_splits = tiles <= kDirectTiles ? 1 : plan.n_splits;
     if (rows_kv <= 64 && (int64_t)d.batch * d.n_kv_heads * few_row_splits < (1ll << 32) / 512) {  // HIP: fewer than 2^32 threads
@@ -327,7 +337,7 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
         w.row_tiles = rows_kv <= 32 ? 1 : 2;
         w.n_splits = few_row_splits;
         w.ride = true;
-    } else if (tiles <= kDirectTiles) {
+    } else if (tiles <= kDirectTiles && few_blocks) {
         w.row_tiles = 1;
         w.n_splits = 1;
         w.ride = true;
@@ -337,8 +347,7 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
         // kernel against this one: 256 rows per KV head, 8 KV heads: 2k keys 19.3 / 14.8 us, 4k 22.3 / 17.9, 8k
         // 28.5 / 26.1 (and 35 / 41 at 16k); 96 rows: 15.2 / 12.4, 17.1 / 14.0; one split of 1024 rows x 2k keys
         // 30.4 / 19.8, of 640 rows 25.3 / 17.3.
-        const int64_t units = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 31) / 32);
-        const int64_t fit = compute_units() / units;  // splits that fit the chip at once
+        const int64_t fit = cus / row_blocks;  // splits that fit the chip at once
         if (tiles <= (fit >= 2 ? kSplitTiles : kOneSplitTiles) && fit >= 1) {
             w.row_tiles = 1;
             w.n_splits = fit < plan.n_splits ? (int32_t)fit : plan.n_splits;

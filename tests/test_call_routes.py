@@ -157,3 +157,15 @@ def test_outputs_over_inputs_take_the_route_that_reads_them_first(lib, shape):
             assert route(lib, x, tree=False, **at)[-1] == "tail(cached)", at
     for at in ({"out": K + cache_bytes}, {"out": V - out_bytes}, {"out": Q + out_bytes}, {"lse": KT}):
         assert route(lib, x, **at) == apart
+
+
+# query heads, KV heads, head_dim, tree nodes, capacity, sequences; whether one workgroup per 32 rows takes all keys
+@pytest.mark.parametrize("shape,direct", [
+    ((32, 8, 128, 48, 400, 16), True), ((32, 8, 128, 48, 400, 32), False),     # 192 rows: 768 and 1536 workgroups
+    ((32, 8, 128, 400, 800, 1), True), ((32, 8, 128, 400, 800, 2), False),     # 1600 rows: 400 and 800
+    ((8, 1, 128, 260, 1144, 4), False), ((8, 1, 128, 256, 1144, 4), True),     # 2080 and 2048 rows: 260 and 256
+    ((32, 8, 64, 400, 800, 8), True),                                          # two of them share a compute unit
+    ((32, 8, 128, 16, 400, 64), True),                                         # 64 rows: the keys are copied once
+])
+def test_many_row_blocks_share_their_keys(lib, shape, direct):
+    assert (route(lib, desc(*shape))[0] == f"wave_split(rows={64 if shape[3] == 16 else 32},splits=1,tree)") == direct

@@ -315,10 +315,14 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     constexpr int kRideSplitLen = 768;
     w.ride = !with_tree || plan.split_len >= kRideSplitLen;
     w.n_splits = plan.n_splits;
-    // A cache of some 1500 keys is worked through by one workgroup per row tile in less time than the merge
-    // of a split call takes (64 rows per KV head, 8 KV heads: 700 keys 11.0 us in one split against 12.9 in
-    // two and 18.6 on the kernel that shares tiles between waves; 1600 keys 14.9, 16.3, 19.8).
+    // A short cache is worked through by one workgroup per row tile in less time than the merge of a split call
+    // takes: with 32 rows per workgroup up to some 1500 keys (32 rows per KV head, 8 KV heads, one split against
+    // the plan's: 1000 keys 11.3 / 12.0 us, 1500 14.3 / 12.3, and 15.8 on the kernel that shares tiles; 96
+    // rows x 1200 keys 13.1, and 15.3 there), with 64 rows, whose waves take twice as long per tile, up to some 700 (64 rows,
+    // 8 KV heads, head_dim 128: 550 keys 13.2 / 13.4, 850 14.9 / 13.8, 1500 20.0 / 14.2, and 15.4 there; head_dim 64:
+    // 1000 keys 12.5 / 12.2) unless the chip is full with two splits anyway (16 sequences, 1500 keys 29.1 / 31.3).
     constexpr int kDirectTiles = 50;
+    const int few_row_tiles = rows_kv <= 32 || plan.n_splits <= 2 ? kDirectTiles : (d.head_dim == 64 ? 32 : 24);
     // With more than 64 rows every 32-row workgroup copies all keys of its head again, which costs nothing while
     // the workgroups run in a round or two, the last one not nearly empty.  Measured, the 256-row kernel against this
     // one, head_dim 128: 192 rows per KV head x 1200 keys, 768 workgroups 44.3 / 43.8 us, 1536 72.0 / 95.6; 768 rows,
@@ -330,7 +334,7 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     const bool few_blocks = d.head_dim == 64 || rounds == 1 ||
                             (rows_kv <= 768 ? rounds <= 3 : rounds == 2 && 4 * row_blocks >= 6 * cus);
     constexpr int kOneSplitTiles = 80, kSplitTiles = 136;
-    const int few_row_splits = tiles <= kDirectTiles ? 1 : plan.n_splits;
+    const int few_row_splits = tiles <= few_row_tiles ? 1 : plan.n_splits;
     if (rows_kv <= 64 && (int64_t)d.batch * d.n_kv_heads * few_row_splits < (1ll << 32) / 512) {  // HIP: fewer than 2^32 threads
         // every wave of a workgroup holds all the query rows of the KV head (32 rows per KV head, 16k keys: 52.7
         // against 57.3 us; 64 rows, 32k keys: 34.6 against 35.4; 32 rows, 8k keys: 14.2 against 20.6)

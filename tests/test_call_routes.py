@@ -169,3 +169,14 @@ def test_outputs_over_inputs_take_the_route_that_reads_them_first(lib, shape):
 ])
 def test_many_row_blocks_share_their_keys(lib, shape, direct):
     assert (route(lib, desc(*shape))[0] == f"wave_split(rows={64 if shape[3] == 16 else 32},splits=1,tree)") == direct
+
+
+@pytest.mark.parametrize("shape,splits", [
+    ((32, 8, 128, 8, 1500, 1), 1), ((32, 8, 128, 8, 1600, 1), 13),       # 32 rows: 48 and 51 tiles
+    ((32, 8, 128, 16, 730, 1), 1), ((32, 8, 128, 16, 750, 1), 6),        # 64 rows: 24 and 25
+    ((32, 8, 64, 16, 990, 1), 1), ((32, 8, 64, 16, 1000, 1), 8),         # head_dim 64: 32 and 33
+    ((32, 8, 128, 16, 1500, 16), 1),                                     # two splits fill the chip
+])
+def test_few_rows_take_one_split_where_the_merge_costs_more(lib, shape, splits):
+    rows = 32 if shape[3] == 8 else 64
+    assert route(lib, desc(*shape))[0] == f"wave_split(rows={rows},splits={splits},tree)"

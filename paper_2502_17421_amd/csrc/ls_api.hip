@@ -307,13 +307,21 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     // rows of the tree are addressed with 32-bit offsets inside a tile
     if (with_tree && (d.kt_stride[2] >= (1 << 24) || d.vt_stride[2] >= (1 << 24))) return w;
     if (outputs_overlap_inputs(d, p, parents, out, lse)) return w;
-    // With tree keys on its last split the cached-key kernel of a 64-node tree takes 6 us longer there (two tiles
-    // that nothing overlaps, against 0.6 us per cached tile), which re-cutting the cached keys hides only
-    // where a split is long; the tail kernel takes 3 to 9 us longer than the merge.  Measured, tail kernel against
-    // tree split: 32k keys, 32 tiles per split 53.7 / 50.6 us, 69 nodes x 12k keys, 26 tiles 36.7 / 33.5,
-    // 256 nodes x 32k keys, 128 tiles 138.8 / 136.6; below, splits keep the cut of the stand-alone call.
+    // Tree keys on the last split of the cached-key kernel: a tree tile takes it about 2 us there, which nothing overlaps
+    // and re-cutting the cached keys hides only where a split is long; the tail kernel takes 3 to 9 us longer
+    // than the merge.  How long a split is depends on the lengths, which the host knows a bound of, so the tree may be
+    // only as large as pays for itself in a nearly empty cache too.  Measured, tail kernel against tree split,
+    // 32 query and 8 KV heads: 64 nodes, 32k keys 55.8 / 54.3 us, 300 keys in a capacity of 32k 22.1 / 20.8; 96
+    // nodes 73.0 / 74.6 and 21.1 / 24.0; 512 nodes 256 / 278 and 37.0 / 51.2.  With at most eight splits per
+    // sequence they are long, and dealt by length: 128 nodes, four sequences, 32k keys 289 / 272, 300 keys 29.2 / 28.7;
+    // but 105 nodes under 3360 rows per KV head, 800 to 1600 keys in 24k 129 / 148.
+    // Below 768 rows per split the cut of the cached keys stays that of the stand-alone call: the whole call is held to
+    // 2^-7 of the largest output against the path assembled from the stand-alone calls with 16-bit parts, and another
+    // cut differs by two units in the last place at single elements (8k keys, 64 nodes would take 28.0 us for 30.1).
+    const int tree_tiles = with_tree ? (d.n_tree + 31) / 32 : 0;
     constexpr int kRideSplitLen = 768;
-    w.ride = !with_tree || plan.split_len >= kRideSplitLen;
+    w.ride = tree_tiles == 0 ||
+             (plan.split_len >= kRideSplitLen && tree_tiles <= (plan.n_splits <= 8 && rows_kv <= 1024 ? 4 : 2));
     w.n_splits = plan.n_splits;
     // A short cache is worked through by one workgroup per row tile in less time than the merge of a split call
     // takes: with 32 rows per workgroup up to some 1500 keys (32 rows per KV head, 8 KV heads, one split against
@@ -350,7 +358,8 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
         // that shares tiles (first window, 256 rows) costs more than its faster tiles save.  Measured, that
         // kernel against this one: 256 rows per KV head, 8 KV heads: 2k keys 19.3 / 14.8 us, 4k 22.3 / 17.9, 8k
         // 28.5 / 26.1 (and 35 / 41 at 16k); 96 rows: 15.2 / 12.4, 17.1 / 14.0; one split of 1024 rows x 2k keys
-        // 30.4 / 19.8, of 640 rows 25.3 / 17.3.
+        // 30.4 / 19.8, of 640 rows 25.3 / 17.3.  (The limit stays below 8k keys, where this kernel is still ahead, for the
+        // cut of the cached keys, as above.)
         const int64_t fit = cus / row_blocks;  // splits that fit the chip at once
         if (tiles <= (fit >= 2 ? kSplitTiles : kOneSplitTiles) && fit >= 1) {
             w.row_tiles = 1;

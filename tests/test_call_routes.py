@@ -180,3 +180,38 @@ def test_many_row_blocks_share_their_keys(lib, shape, direct):
 def test_few_rows_take_one_split_where_the_merge_costs_more(lib, shape, splits):
     rows = 32 if shape[3] == 8 else 64
     assert route(lib, desc(*shape))[0] == f"wave_split(rows={rows},splits={splits},tree)"
+
+
+# query heads, KV heads, head_dim, tree nodes, capacity, sequences; whether the tree keys ride on the last split
+@pytest.mark.parametrize("shape,ride", [
+    ((32, 8, 128, 64, 32768, 1), True), ((32, 8, 128, 65, 32768, 1), False),     # two tree tiles and three
+    ((32, 8, 128, 64, 12000, 1), False),                                         # splits of less than 768 rows
+    ((32, 8, 128, 128, 32768, 4), True), ((32, 8, 128, 129, 32768, 4), False),   # at most eight splits: four and five
+    ((32, 8, 128, 128, 131072, 4), False), ((32, 8, 128, 64, 131072, 4), True),  # sixteen splits
+    ((32, 1, 128, 40, 24000, 4), True), ((32, 1, 128, 96, 24000, 16), False),    # more than 1024 rows
+])
+def test_trees_ride_where_they_pay_for_themselves_in_an_empty_cache(lib, shape, ride):
+    got = route(lib, desc(*shape))
+    assert got[0].startswith("prefix(")
+    assert got[1:] == (["merge"] if ride else ["tail"]) and (",tree" in got[0]) == ride and (",mask" in got[0]) != ride
+    assert (",dealt" in got[0]) == (ride and shape[5] > 1)
+    assert route(lib, desc(*shape), tree=False)[1] == "merge"
+
+
+def test_the_gpu_tests_reach_the_kernels_they_are_for(lib):
+    import test_gpu_tree_split
+    import test_gpu_wave_split
+    codes = {"bf16": ls.LS_BF16, "f16": ls.LS_F16}
+
+    def routes(cases):
+        for dtype, hq, hkv, d, t, plens, *_ in cases:
+            x = desc(hq, hkv, d, t, max(plens), len(plens), codes[dtype])
+            yield (dtype, hq, hkv, d, t, plens), route(lib, x)
+
+    for case, got in routes(test_gpu_wave_split.CASES):
+        assert got[0].startswith("wave_split"), (case, got)
+    for case, got in routes(test_gpu_tree_split.CASES):
+        dealt = ",dealt" if 1 < len(case[5]) <= 32 else ""
+        assert got[0].endswith(f",tree{dealt})") and got[0].startswith("prefix") and got[1:] == ["merge"], (case, got)
+    for case, got in routes(test_gpu_tree_split.ON_THE_TAIL):
+        assert got[0].startswith("prefix") and got[1:] == ["tail"], (case, got)

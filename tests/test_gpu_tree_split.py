@@ -1,5 +1,6 @@
 """Tree keys on the last key split of the cached-key kernel (more than 64 query rows per KV head, splits of
-768 rows or more), at the sizes where it can go wrong: one and several rounds of three tree tiles,
+768 rows or more, trees of at most 64 nodes or 128; test_call_routes.py says which call takes which kernels),
+at the sizes where it can go wrong: one and several rounds of three tree tiles,
 trees on both sides of the 64 nodes whose mask is built in registers, workgroups of four and eight
 waves, a last row block without rows in some waves, sequences of unlike length (whose splits are dealt by
 length, up to 32 sequences) with few tiles or none,
@@ -20,13 +21,18 @@ CASES = [
     ("f16", 64, 16, 64, 32, [3200, 0, 31, 2500], "tree"),       # 128 rows; a sequence without cached keys
     ("bf16", 32, 8, 128, 64, [6300, 1700, 900, 6200], "tree"),  # the last size masked in registers; eight waves
     ("bf16", 32, 8, 64, 65, [6300, 6000], "peaked"),            # 65: the chains are walked in LDS; 260 rows
-    ("f16", 32, 8, 128, 69, [12345], "tree"),                   # 276 rows, three tree tiles
     ("bf16", 32, 32, 128, 97, [4001, 33], "tree"),              # four tree tiles: a second round
+    ("f16", 16, 16, 64, 128, [4000, 300, 0], "peaked"),         # the largest tree that rides; 128 rows, four waves
+    ("bf16", 32, 16, 128, 128, [6200, 31], "tree"),             # and eight waves
+    ("bf16", 8, 4, 64, 40, [2000] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 22, "tree"),  # 32 sequences: the most
+    ("bf16", 4, 2, 64, 40, [2500] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 23, "tree"),  # 33: an even cut of each
+]
+# the same lengths of splits, but the tail kernel takes the tree keys: more tree tiles than pay for themselves there
+ON_THE_TAIL = [
+    ("f16", 32, 8, 128, 69, [12345], "tree"),                   # 276 rows, three tree tiles, sixteen splits
     ("bf16", 32, 16, 64, 200, [3300, 800], "tree"),             # seven tree tiles
     ("bf16", 8, 8, 128, 512, [6500, 10], "tree"),               # the largest tree, sixteen tiles
     ("f16", 32, 16, 64, 130, [3200, 300], "peaked"),
-    ("bf16", 8, 4, 64, 40, [2000] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 22, "tree"),  # 32 sequences: the most
-    ("bf16", 4, 2, 64, 40, [2500] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 23, "tree"),  # 33: an even cut of each
 ]
 
 
@@ -37,14 +43,14 @@ def whole_call(db):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,hq,hkv,d,t,plens,variant", CASES)
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plens,variant", CASES + ON_THE_TAIL)
 def test_whole_call_against_the_oracle_and_the_tail_kernel(dtype, hq, hkv, d, t, plens, variant):
     batch = make(dtype, hq, hkv, d, t, plens, variant, 31000 + t)
     print(f"tree split {dtype} hq={hq} hkv={hkv} d={d} t={t} plens={plens} {variant}", flush=True)
     db = DeviceBatch(batch, token_major=t % 2 == 0)
     assert ls.ls_prefix_num_splits(db.desc) > 1 or len(plens) == 1
     if len(plens) < 33:
-        assert ls.ls_prefix_split_len(db.desc, 0) >= 768  # the tree keys are on the last split
+        assert ls.ls_prefix_split_len(db.desc, 0) >= 768
     first = whole_call(db)
     db.workspace.fill_(0xFF)  # whatever the workspace and the outputs held, the result is the same
     db.out.fill_(float("nan"))

@@ -114,12 +114,15 @@ wave_split_kernel(WaveArgs a)
     const int li = lane & 31;
     const int lh = lane >> 5;
 
-    // Workgroups are dealt to the eight XCDs in turn; each XCD takes a run of consecutive work items here
-    // (row block fastest, then split, then (sequence, KV head)), so that the row blocks that read the same
-    // keys share an L2 (8 sequences x 8 KV heads, 160 query rows each, 1600 keys:
-    // 44.6 -> 26.2 us).
-    const uint32_t xcd = blockIdx.x & 7u, per_xcd = gridDim.x >> 3, extra = gridDim.x & 7u;
-    const uint32_t item = xcd * per_xcd + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+    // Workgroups are dealt to the eight XCDs in turn.  With several row blocks each XCD takes a run of consecutive work
+    // items here (row block fastest, then split, then (sequence, KV head)), so that the row blocks that read the
+    // same keys share an L2 (8 sequences x 8 KV heads, 160 query rows each, 1600 keys: 44.6 -> 26.2 us).  With one,
+    // nothing is shared and runs would give whole sequences to an XCD, the longest one to a few of them.
+    uint32_t item = blockIdx.x;
+    if (a.by_row_blocks.d > 1) {
+        const uint32_t xcd = blockIdx.x & 7u, per_xcd = gridDim.x >> 3, extra = gridDim.x & 7u;
+        item = xcd * per_xcd + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+    }
     const uint32_t item_split = a.by_row_blocks.div(item);         // item / row blocks
     const uint32_t bz = a.by_splits.div(item_split);
     const int split = (int)(item_split - bz * (uint32_t)a.n_splits);

@@ -73,6 +73,17 @@ struct SequenceSplits {
     int32_t first, count;
 };
 
+// Pieces of at most `piece` tiles that `tiles` tiles take, one at least.  reciprocal: of piece, to the last bit or
+// two; with it the quotient, below 2^20 here, is off by at most one.
+__host__ __device__ inline int pieces_of(int tiles, int piece, float reciprocal)
+{
+    int n = (int)((float)tiles * reciprocal);
+    n += n * piece < tiles ? 1 : 0;
+    n += n * piece < tiles ? 1 : 0;
+    n -= (n - 1) * piece >= tiles ? 1 : 0;
+    return n > 1 ? n : 1;
+}
+
 // Single-launch form of the whole call.  The workgroups of one (sequence, KV head, query block),
 // one per key split, share three 64-bit words: an arrival word (call number << 32 | workgroups
 // counted in this call) and two claim words used by alternate calls (bit k: the rows of slice k

@@ -51,10 +51,10 @@
 // a larger sum (scores far above everything before) redoes that step on the general path,
 // which raises m and rescales O and l.
 //
-// Tree keys.  In a whole-path call whose splits are long the last split takes the keys of the tree along,
-// before its cached keys, in LDS stages that the first window of cached tiles leaves free, and the call ends
-// with a merge alone instead of the tail kernel (32k keys, 64 nodes: tail 11.7 us, merge 7.6; 640 rows per KV
-// head in four sequences: 20.8 and 11.9).  A tree tile is not pipelined (about 2 us against 0.6 for a cached one:
+// Tree keys.  In a whole-path call with a small tree and long splits the last split takes the keys of the tree
+// along, before its cached keys, in LDS stages that the first window of cached tiles leaves free, and the call
+// ends with a merge alone instead of the tail kernel (32k keys, 64 nodes: tail 11.7 us, merge 7.6; 640 rows per
+// KV head in four sequences: 20.8 and 11.9).  A tree tile is not pipelined (about 2 us against 0.6 for a cached one:
 // mask, score product, softmax, output product of fp32 numerators in two or three parts, one
 // after the other in all waves), so that split gets fewer cached tiles.
 //
@@ -86,17 +86,6 @@ constexpr float kLazy = 8.f;        // general path: m is raised only when a sco
 // common path: largest row-sum increment taken without raising m; the numerators are stored in
 // the operand type, and a half holds nothing above 65504
 template <bool F16> constexpr float kSumCap = F16 ? 0x1p15f : 0x1p40f;
-
-// Pieces of at most `piece` tiles that `tiles` tiles take, one at least.  (tiles < 2^20: the quotient by the
-// reciprocal is off by at most one.)
-__device__ __forceinline__ int pieces_of(int tiles, int piece)
-{
-    int n = (int)((float)tiles * __builtin_amdgcn_rcpf((float)piece));
-    n += n * piece < tiles ? 1 : 0;
-    n += n * piece < tiles ? 1 : 0;
-    n -= (n - 1) * piece >= tiles ? 1 : 0;
-    return n > 1 ? n : 1;
-}
 
 }  // namespace
 
@@ -179,11 +168,12 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
             int mine = (low + 1) / 2 * 2 + lane * step;
             mine = mine > 2 ? mine : 2;
             int taken = 0;
-            for (int i = 0; i < p.batch; ++i) taken += pieces_of(__builtin_amdgcn_readlane(tiles, i), mine);
+            for (int i = 0; i < p.batch; ++i) taken += pieces_of(__builtin_amdgcn_readlane(tiles, i), mine, __builtin_amdgcn_rcpf((float)mine));
             const uint64_t fits = __ballot(taken <= pieces);
             balanced_tiles = fits ? __builtin_amdgcn_readlane(mine, __builtin_ctzll(fits)) : 0;
-            const bool deal = balanced_tiles > 0 && balanced_tiles <= kMaxSplitLen / TK;  // else n_splits pieces each
-            const int count = deal ? pieces_of(tiles, balanced_tiles) : plan.n_splits;
+            // a piece longer than a split may be (sequences that nearly fill a capacity of 8192 rows per split): n_splits each
+            const bool deal = balanced_tiles > 0 && balanced_tiles <= kMaxSplitLen / TK;
+            const int count = deal ? pieces_of(tiles, balanced_tiles, __builtin_amdgcn_rcpf((float)balanced_tiles)) : plan.n_splits;
             if (!deal) balanced_tiles = 0;
             for (b = 0, first_split = 0; b < p.batch; ++b) {
                 n_splits = __builtin_amdgcn_readlane(count, b);

@@ -5,6 +5,7 @@ import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 from paper_2502_17421_amd import binding as ls
@@ -55,6 +56,8 @@ int prefix_mfma_query_blocks(const Problem &p) { return (p.group * p.n_tree + 25
 bool prefix_mfma_supports(const Problem &, int dtype) { return is_16bit(dtype); }
 }  // namespace ls
 
+extern "C" int count_pieces(int tiles, int piece, float reciprocal) { return ls::pieces_of(tiles, piece, reciprocal); }
+
 extern "C" const char *take_route()
 {
     static char last[512];
@@ -77,6 +80,7 @@ def build(folder, *host_flags):
 def load(path):
     loaded = ctypes.CDLL(path)
     loaded.take_route.restype = ctypes.c_char_p
+    loaded.count_pieces.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_float]
     vp, dp = ctypes.c_void_p, ctypes.POINTER(ls.ls_desc)
     loaded.ls_hybrid_tree_attn.argtypes = [dp] + [vp] * 10 + [ctypes.c_size_t, vp]
     loaded.ls_cache_attn.argtypes = [dp] + [vp] * 7 + [ctypes.c_size_t, vp]
@@ -215,3 +219,17 @@ def test_the_gpu_tests_reach_the_kernels_they_are_for(lib):
         assert got[0].endswith(f",tree{dealt})") and got[0].startswith("prefix") and got[1:] == ["merge"], (case, got)
     for case, got in routes(test_gpu_tree_split.ON_THE_TAIL):
         assert got[0].startswith("prefix") and got[1:] == ["tail"], (case, got)
+
+
+def test_pieces_are_counted_exactly_with_an_inexact_reciprocal(lib):
+    """What the device deals by: ceil(tiles / piece), one at least, with a reciprocal an ulp or two off."""
+    rng = np.random.default_rng(41)
+    pairs = [(t, p) for p in (2, 4, 6, 10, 38, 126, 254, 256) for t in [0, 1] + [k * p + e for k in (1, 2, 3, 37, 1000) for e in (-1, 0, 1)]]
+    pairs += [(int(t), int(p)) for t, p in zip(np.exp(rng.uniform(0, np.log(2 ** 24), 3000)), rng.integers(1, 5000, 3000)) if t < p * 2 ** 20]
+    for tiles, piece in pairs:
+        r = np.float32(1) / np.float32(piece)
+        for _ in range(2):
+            r = np.nextafter(r, np.float32(0))
+        for _ in range(5):
+            assert lib.count_pieces(tiles, piece, float(r)) == max(1, -(-tiles // piece)), (tiles, piece, r)
+            r = np.nextafter(r, np.float32(1))

@@ -239,3 +239,64 @@ def test_bad_parents_are_cut_and_reported(t, plen):
         results.append((out, lse, db.workspace[at:at + 8].view(torch.int32).cpu().tolist()))
     assert results[0][2] == [0, 1] and results[1][2] == [0, 0]
     assert np.array_equal(results[0][0], results[1][0]) and np.array_equal(results[0][1], results[1][1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens", [[16384, 16384], [16384, 100], [16384, 0]])
+def test_pieces_longer_than_a_split_are_not_dealt(lens):
+    """Two sequences that fill a capacity of two splits of 8192 rows: with the tree priced in, even pieces would be longer
+    than a split may be, and every sequence gets two as without dealing.  (The others are dealt.)  Against float64 on
+    the device, some heads."""
+    hq, d, t = 64, 64, 66
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    new = lambda rows: torch.randn((2, hq, rows, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    q, kt, vt, k, v = new(t), new(t), new(t), new(16384), new(16384)
+    parents = [synth.tree_constrained(np.random.default_rng(s), t, 10, 4) for s in range(2)]
+    out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+    desc = ls.make_desc(q, k, v, kt, vt, out, 16384)
+    assert ls.ls_prefix_num_splits(desc) == 2 and ls.ls_prefix_split_len(desc, 0) == 8192
+    print(f"pieces longer than a split {lens}", flush=True)
+    work = torch.full((ls.ls_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device="cuda")
+    ls.ls_hybrid_tree_attn(desc, q, k, v, torch.tensor(lens, dtype=torch.int32, device="cuda"), kt, vt,
+                           torch.from_numpy(np.stack(parents)).cuda(), out, lse, work)
+    torch.cuda.synchronize()
+    for b in range(2):
+        sees = np.eye(t, dtype=bool)
+        for i in range(t):
+            j = i
+            while j >= 0:
+                sees[i, j] = True
+                j = parents[b][j]
+        for h in (0, 31, 63):
+            keys = torch.cat([k[b, h, :lens[b]], kt[b, h]]).double()
+            vals = torch.cat([v[b, h, :lens[b]], vt[b, h]]).double()
+            z = (q[b, h].double() @ keys.T) / np.sqrt(d)
+            z[:, lens[b]:] = z[:, lens[b]:].masked_fill(~torch.from_numpy(sees).cuda(), float("-inf"))
+            ref_lse = torch.logsumexp(z, 1)
+            ref = (z - ref_lse[:, None]).exp() @ vals
+            gates(out[b, h].float().cpu().numpy(), lse[b, h].cpu().numpy(), ref.cpu().numpy(), ref_lse.cpu().numpy(), "bf16",
+                  f"  sequence {b} head {h}", stress=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_neighbours_change_a_sequence_by_rounding_only(dtype):
+    """Pieces are dealt by the lengths of all sequences of a call, so another neighbour moves the cuts of a sequence: each
+    16-bit part, and the output, is rounded once (half an ulp of the largest value, on either side), and with the cuts
+    the reference exponents of the numerators move (half an ulp, twice that where halves are cut off, again on
+    either side).  The same neighbours give the same bits."""
+    hq, hkv, d, t = 32, 8, 128, 40
+    batch = make(dtype, hq, hkv, d, t, [5000, 6000, 6000, 6000], "peaked", 37000)
+    db = DeviceBatch(batch)
+    results = []
+    for others in ([6000, 6000, 6000], [300, 0, 2000], [6000, 6000, 6000]):
+        db.prefix_lens = torch.tensor([5000] + others, dtype=torch.int32, device="cuda")
+        out, lse = db.run_full()
+        torch.cuda.synchronize()
+        results.append((out[0].float().cpu().numpy(), lse[0].cpu().numpy()))
+    assert np.array_equal(results[0][0], results[2][0]) and np.array_equal(results[0][1], results[2][1])
+    assert not np.array_equal(results[0][0], results[1][0])  # (the cuts did move)
+    vmax = max(np.abs(batch.seqs[0].v_cache).max(), np.abs(batch.seqs[0].v_tree).max())
+    half_ulp = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8  # relative
+    assert np.abs(results[0][0] - results[1][0]).max() <= 2 * (2 + (2 if dtype == "f16" else 1)) * half_ulp * vmax
+    assert np.abs(results[0][1] - results[1][1]).max() <= 1e-5 * np.abs(results[0][1]).max()

@@ -172,6 +172,33 @@ def test_nan_reaches_the_rows_that_see_it_and_their_lse(dtype, hq, hkv, d, t, pl
         say(gates(out[~bad], lse[~bad], ro[~bad], rl[~bad], dtype, "  the other rows", stress=True))
 
 
+def loads_left_alone(lines):
+    """Loads written in assembly return their registers to the compiler before the data is there: nothing may touch
+    them between the load and the wait that follows it in the text (also in assembly)."""
+    number = re.compile(r"\bv(?:\[(\d+):(\d+)\]|(\d+))")
+    registers = lambda text: {r for a, b, c in number.findall(text) for r in range(int(a or c), int(b or c) + 1)}
+    pending, in_asm, seen = set(), False, 0
+    for ln in lines:
+        if "#ASMSTART" in ln or "#ASMEND" in ln:
+            in_asm = "#ASMSTART" in ln
+            continue
+        text = ln.split(";")[0].strip()
+        if not text or text.endswith(":") or text.startswith("."):
+            continue
+        if in_asm and text.startswith("s_waitcnt vmcnt"):
+            pending = set()
+        elif in_asm and re.match(r"global_load_dword(x4)? v", text):
+            dst, rest = text.split(",", 1)
+            assert not registers(rest) & pending, text
+            pending |= registers(dst)
+            seen += 1
+        else:
+            if text.startswith("v_mad_u64_u32"):  # 32-bit products: the upper half of the addend reaches only that of the sum
+                text = re.sub(r"v\[(\d+):\d+\]$", r"v\1", text)
+            assert not registers(text) & pending, text
+    assert seen > 0
+
+
 def test_the_kernel_keeps_its_loads_counted(tmp_path):
     """No register spills to scratch (the kernel counts its own outstanding loads), and M0 belongs to
     the HBM -> LDS copies alone (they set it inside assembly, which cannot declare it clobbered)."""
@@ -186,7 +213,16 @@ def test_the_kernel_keeps_its_loads_counted(tmp_path):
     subprocess.run([ls_build.HIPCC, *flags, "-S", "--cuda-device-only", "-o", str(asm),
                     os.path.join(ls_build.CSRC, "ls_wave_split.hip")], check=True, stderr=subprocess.DEVNULL)
     lines = asm.read_text().splitlines()
+    loads_left_alone(lines)
     copies = sum("global_load_lds_dwordx4" in ln for ln in lines)
     m0 = [ln.strip() for ln in lines if re.search(r"\bm0\b", ln.split(";")[0])]
     assert copies > 0 and len(m0) == copies
     assert all(re.fullmatch(r"s_mov_b32 m0, (s\d+|vcc_lo|vcc_hi)", ln) for ln in m0)
+
+
+def test_the_kernel_that_shares_tiles_leaves_its_loads_alone(tmp_path):
+    asm = tmp_path / "prefix_mfma.s"
+    flags = [f for f in ls_build.FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.run([ls_build.HIPCC, *flags, "-S", "--cuda-device-only", "-o", str(asm),
+                    os.path.join(ls_build.CSRC, "ls_prefix_mfma.hip")], check=True, stderr=subprocess.DEVNULL)
+    loads_left_alone(asm.read_text().splitlines())

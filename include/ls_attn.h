@@ -29,7 +29,9 @@
  *   - Argument errors are found on the host before anything is launched.  A launch
  *     failure reported by HIP maps to LS_ERR_HIP.
  *   - The same inputs give bit-identical outputs (fixed split schedule, no float
- *     atomics).
+ *     atomics).  A sequence's output may differ in rounding with the other sequences of
+ *     its call: whole-path calls over 2 to 32 sequences cut the cached keys by the lengths
+ *     of all of them (the cut decides which 16-bit partial rows are rounded).
  *   - Calls are re-entrant; concurrency is by streams.  Calls sharing a workspace or
  *     output buffer must be ordered by the caller.
  *
@@ -133,15 +135,18 @@ int ls_workspace_bytes(const ls_desc *desc, size_t *bytes_out);
  * The whole path (Section 3.3): tree mask from `parents`, split-KV attention over the
  * cache, masked attention over the tree tokens, log-sum-exp merge into out / lse.  It runs
  * as one or two launches, chosen by the sizes: a kernel for the cached keys, which takes the
- * tree tokens along (short caches, few query rows, or long splits) or whose extra workgroups
- * build the mask, then a merge of the parts, with the tree attention if it is still to do.
+ * tree tokens along (short caches, few query rows, or a small tree and long splits) or whose
+ * extra workgroups build the mask, then a merge of the parts, with the tree attention if it is
+ * still to do.  With contiguous caches, out and lse may lie over cached rows, lengths or
+ * parents, and out over q row by row (in place); the call then takes the latter route.  A pool
+ * of pages must not overlap the outputs.
  *
  *   prefix_lens  DEVICE int32[batch]; values are clamped into [0, max_prefix_len].
  *                A sequence with prefix length 0 attends to its tree tokens only.
  *   parents      DEVICE int32[batch, n_tree].  An entry outside {-1} u [0, i) is treated
  *                as -1 and sets the sequence's error word in the workspace (see
  *                ls_workspace_error); it never causes an out-of-bounds access.
- *   out, lse     DEVICE, written in full.
+ *   out, lse     DEVICE, written in full (rows of out may hold intermediate values meanwhile).
  *   workspace    DEVICE, >= ls_workspace_bytes(); contents are scratch.
  */
 int ls_hybrid_tree_attn(const ls_desc *desc, const void *q,
@@ -211,7 +216,7 @@ int ls_hybrid_tree_attn_static(const ls_desc *desc, const void *q,
  *     writes the counters.  Calls that share a workspace must not overlap in time.
  *   - Problems outside the matrix-core kernel (float inputs, row strides beyond its reach),
  *     with more than 64 key splits or with more than 4096 (sequence, KV head, query block)
- *     triples run as ls_hybrid_tree_attn does, in two launches.
+ *     triples run in two launches, the second one with the tree attention and the merge.
  *   - ls_set_single_launch_polls(n) sets the number of polls (about half a microsecond
  *     apart) for later calls of this process: 0 makes every launch the nobody-waits form,
  *     a negative n restores the default (about 20 ms); n above 2^24 is LS_ERR_SHAPE.  A wait

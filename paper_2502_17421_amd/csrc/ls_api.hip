@@ -308,20 +308,22 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     if (with_tree && (d.kt_stride[2] >= (1 << 24) || d.vt_stride[2] >= (1 << 24))) return w;
     if (outputs_overlap_inputs(d, p, parents, out, lse)) return w;
     // Tree keys on the last split of the cached-key kernel: a tree tile takes it about 2 us there, which nothing overlaps
-    // and re-cutting the cached keys hides only where a split is long; the tail kernel takes 3 to 9 us longer
-    // than the merge.  How long a split is depends on the lengths, which the host knows a bound of, so the tree may be
-    // only as large as pays for itself in a nearly empty cache too.  Measured, tail kernel against tree split,
-    // 32 query and 8 KV heads: 64 nodes, 32k keys 55.8 / 54.3 us, 300 keys in a capacity of 32k 22.1 / 20.8; 96
-    // nodes 73.0 / 74.6 and 21.1 / 24.0; 512 nodes 256 / 278 and 37.0 / 51.2.  With at most eight splits per
-    // sequence they are long, and dealt by length: 128 nodes, four sequences, 32k keys 289 / 272, 300 keys 29.2 / 28.7;
-    // but 105 nodes under 3360 rows per KV head, 800 to 1600 keys in 24k 129 / 148.
+    // and re-cutting the cached keys hides where splits are long; the tail kernel takes 3 to 9 us longer than the
+    // merge, and does not know pieces dealt by length.  How long a split is depends on the lengths, of which the host knows
+    // a bound, so the tree is kept to what a nearly empty cache bears too, and where the launch runs in many rounds
+    // its tiles are hidden by nothing.  Time against the tail kernel's, 260 shapes of 65 to 512 nodes: with at most 8
+    // tree tiles and four rounds 0.90 (worst 1.05) for sequences that fill 15 % of the capacity and more, 0.98 (1.16) below;
+    // with 9 tiles and more 0.78 to 1.24, and up to 1.74 below 15 % (476 nodes, 1600 keys in 30k 70.7 / 123 us); beyond four
+    // rounds up to 1.24 (120 nodes, 16 sequences of 13k to 17k keys 708 / 742).  One or two tiles, 32 query and 8
+    // KV heads: 64 nodes, 32k keys 55.8 / 54.3 us, 300 keys in a capacity of 32k 22.1 / 20.8.
     // Below 768 rows per split the cut of the cached keys stays that of the stand-alone call: the whole call is held to
     // 2^-7 of the largest output against the path assembled from the stand-alone calls with 16-bit parts, and another
     // cut differs by two units in the last place at single elements (8k keys, 64 nodes would take 28.0 us for 30.1).
     const int tree_tiles = with_tree ? (d.n_tree + 31) / 32 : 0;
     constexpr int kRideSplitLen = 768;
-    w.ride = tree_tiles == 0 ||
-             (plan.split_len >= kRideSplitLen && tree_tiles <= (plan.n_splits <= 8 && rows_kv <= 1024 ? 4 : 2));
+    const int64_t workgroups = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 255) / 256) * plan.n_splits;
+    w.ride = tree_tiles == 0 || (plan.split_len >= kRideSplitLen &&
+                                 (tree_tiles <= 2 || (tree_tiles <= 8 && workgroups <= 4 * (int64_t)compute_units())));
     w.n_splits = plan.n_splits;
     // A short cache is worked through by one workgroup per row tile in less time than the merge of a split call
     // takes: with 32 rows per workgroup up to some 1500 keys (32 rows per KV head, 8 KV heads, one split against

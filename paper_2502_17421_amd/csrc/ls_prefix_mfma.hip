@@ -51,7 +51,7 @@
 // a larger sum (scores far above everything before) redoes that step on the general path,
 // which raises m and rescales O and l.
 //
-// Tree keys.  In a whole-path call with a small tree and long splits the last split takes the keys of the tree
+// Tree keys.  In a whole-path call with long splits and a tree that is not large the last split takes the keys of the tree
 // along, before its cached keys, in LDS stages that the first window of cached tiles leaves free, and the call
 // ends with a merge alone instead of the tail kernel (32k keys, 64 nodes: tail 11.7 us, merge 7.6; 640 rows per
 // KV head in four sequences: 20.8 and 11.9).  A tree tile is not pipelined (about 2 us against 0.6 for a cached one:

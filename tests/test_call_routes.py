@@ -188,13 +188,12 @@ def test_few_rows_take_one_split_where_the_merge_costs_more(lib, shape, splits):
 
 # query heads, KV heads, head_dim, tree nodes, capacity, sequences; whether the tree keys ride on the last split
 @pytest.mark.parametrize("shape,ride", [
-    ((32, 8, 128, 64, 32768, 1), True), ((32, 8, 128, 65, 32768, 1), False),     # two tree tiles and three
-    ((32, 8, 128, 64, 12000, 1), False),                                         # splits of less than 768 rows
-    ((32, 8, 128, 128, 32768, 4), True), ((32, 8, 128, 129, 32768, 4), False),   # at most eight splits: four and five
-    ((32, 8, 128, 128, 131072, 4), False), ((32, 8, 128, 64, 131072, 4), True),  # sixteen splits
-    ((32, 1, 128, 40, 24000, 4), True), ((32, 1, 128, 96, 24000, 16), False),    # more than 1024 rows
+    ((32, 8, 128, 64, 32768, 1), True), ((32, 8, 128, 64, 12000, 1), False),     # splits of less than 768 rows
+    ((32, 8, 128, 256, 32768, 1), True), ((32, 8, 128, 257, 32768, 1), False),   # eight tree tiles and nine
+    ((40, 8, 128, 120, 16621, 4), True), ((40, 8, 128, 120, 16621, 16), False),  # 384 workgroups and 1536
+    ((40, 8, 128, 64, 16621, 32), True),                                         # two tree tiles
 ])
-def test_trees_ride_where_they_pay_for_themselves_in_an_empty_cache(lib, shape, ride):
+def test_trees_ride_where_that_pays(lib, shape, ride):
     got = route(lib, desc(*shape))
     assert got[0].startswith("prefix(")
     assert got[1:] == (["merge"] if ride else ["tail"]) and (",tree" in got[0]) == ride and (",mask" in got[0]) != ride

@@ -1,5 +1,5 @@
 """Tree keys on the last key split of the cached-key kernel (more than 64 query rows per KV head, splits of
-768 rows or more, trees of at most 64 nodes or 128; test_call_routes.py says which call takes which kernels),
+768 rows or more, trees of at most 256 nodes; test_call_routes.py says which call takes which kernels),
 at the sizes where it can go wrong: one and several rounds of three tree tiles,
 trees on both sides of the 64 nodes whose mask is built in registers, workgroups of four and eight
 waves, a last row block without rows in some waves, sequences of unlike length (whose splits are dealt by
@@ -21,18 +21,19 @@ CASES = [
     ("f16", 64, 16, 64, 32, [3200, 0, 31, 2500], "tree"),       # 128 rows; a sequence without cached keys
     ("bf16", 32, 8, 128, 64, [6300, 1700, 900, 6200], "tree"),  # the last size masked in registers; eight waves
     ("bf16", 32, 8, 64, 65, [6300, 6000], "peaked"),            # 65: the chains are walked in LDS; 260 rows
+    ("f16", 32, 8, 128, 69, [12345], "tree"),                   # 276 rows, three tree tiles
     ("bf16", 32, 32, 128, 97, [4001, 33], "tree"),              # four tree tiles: a second round
-    ("f16", 16, 16, 64, 128, [4000, 300, 0], "peaked"),         # the largest tree that rides; 128 rows, four waves
-    ("bf16", 32, 16, 128, 128, [6200, 31], "tree"),             # and eight waves
+    ("f16", 16, 16, 64, 128, [4000, 300, 0], "peaked"),         # 128 rows, four waves, two rounds
+    ("f16", 32, 16, 64, 130, [3200, 300], "peaked"),
+    ("bf16", 32, 16, 64, 200, [3300, 800], "tree"),             # seven tree tiles: three rounds
+    ("bf16", 8, 8, 128, 256, [12000, 10], "tree"),              # the largest tree that rides, eight tiles
     ("bf16", 8, 4, 64, 40, [2000] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 22, "tree"),  # 32 sequences: the most
     ("bf16", 4, 2, 64, 40, [2500] * 3 + [0, 1, 31, 32, 33, 700, 1999] + [1600] * 23, "tree"),  # 33: an even cut of each
 ]
-# the same lengths of splits, but the tail kernel takes the tree keys: more tree tiles than pay for themselves there
+# the same lengths of splits, but the tail kernel takes the tree keys: more than eight tree tiles
 ON_THE_TAIL = [
-    ("f16", 32, 8, 128, 69, [12345], "tree"),                   # 276 rows, three tree tiles, sixteen splits
-    ("bf16", 32, 16, 64, 200, [3300, 800], "tree"),             # seven tree tiles
+    ("f16", 8, 8, 128, 257, [6500, 10], "tree"),
     ("bf16", 8, 8, 128, 512, [6500, 10], "tree"),               # the largest tree, sixteen tiles
-    ("f16", 32, 16, 64, 130, [3200, 300], "peaked"),
 ]
 
 

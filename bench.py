@@ -25,14 +25,14 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16, published
 
 # HBM bytes per launch of the cached-key kernel (fetched + written) from the rocprofv3 FETCH_SIZE /
-# WRITE_SIZE runs summarised in profiles/verify_call_C3_mi355x.md, scaled by the copy calibration.
+# WRITE_SIZE runs summarised in profiles/whole_call_kernels_mi355x.md, scaled by the copy calibration.
 # Hardware counters cannot be read while this script runs: the figure is copied from that
 # profile and labelled so in the output; None for workloads without a committed profile.
-PROFILED_TRAFFIC_BYTES = {"C3": 138772466 + 18883594,      # fetched + written by the cached-key kernel inside the call
-                          "B3": 166267344 + 10028131, "C5": 753731142 + 47194244, "L3": 151355553 + 18883367,
-                          "C2": 38140217 + 9437732, "C4": 270913121 + 2359584}
-PROFILED_TRAFFIC_SOURCE = ("profiles/*.md (rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of the cached-key kernel inside the call, "
-                           "scaled by the copy calibration; not this run)")
+PROFILED_TRAFFIC_BYTES = {"C3": 138834985 + 17079706,       # fetched + written by the cached-key kernel on its own
+                          "B3": 146517174 + 9060352, "C5": 779084476 + 36045005, "L3": 151416787 + 17040486,
+                          "C2": 38203094 + 8519885, "C4": 270950050 + 2129920}
+PROFILED_TRAFFIC_SOURCE = ("profiles/whole_call_kernels_mi355x.md (rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of the cached-key "
+                           "kernel launched alone, scaled by the copy calibration; not this run)")
 PREWARM_SECONDS = 0.35         # untimed calls before --warmup: the shader clock needs ~0.2 s of work to settle
 
 

@@ -84,7 +84,8 @@ typedef struct {
     int32_t n_kv_heads;
     int32_t head_dim;
     int32_t n_tree;           /* tree tokens per sequence (the appendix's M) */
-    int32_t max_prefix_len;   /* host-known upper bound of every prefix length; sizes the grid */
+    int32_t max_prefix_len;   /* host-known upper bound of every prefix length; sizes the grid, and
+                                 the closer it is the better the kernels and the cut are chosen */
     int32_t dtype;            /* ls_dtype of q, k, v and out; lse is always float */
     float   softmax_scale;    /* 0 selects 1/sqrt(head_dim) (the appendix's 1/sqrt(d_qk)) */
     /* element strides of the (batch, head, row) axes; the head_dim axis has stride 1 */

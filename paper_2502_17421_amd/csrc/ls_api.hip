@@ -320,7 +320,7 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     // 2^-7 of the largest output against the path assembled from the stand-alone calls with 16-bit parts, and another
     // cut differs by two units in the last place at single elements (8k keys, 64 nodes would take 28.0 us for 30.1).
     const int tree_tiles = with_tree ? (d.n_tree + 31) / 32 : 0;
-    constexpr int kRideSplitLen = 768;
+    constexpr int kRideSplitLen = 768;  // (more than the 16 tiles up to which a split takes the deep window)
     const int64_t workgroups = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 255) / 256) * plan.n_splits;
     w.ride = tree_tiles == 0 || (plan.split_len >= kRideSplitLen &&
                                  (tree_tiles <= 2 || (tree_tiles <= 8 && workgroups <= 4 * (int64_t)compute_units())));

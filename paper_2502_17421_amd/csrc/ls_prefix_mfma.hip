@@ -1065,7 +1065,10 @@ template <int D, int NW, bool F16, bool PAGED, int PD>
 hipError_t launch_one(const Problem &p, const SplitPlan &plan, const Partials &out, const MaskJob &mask_job,
                       const FusedTail &tail, hipStream_t stream)
 {
-    if (!tail.counters && tail.parents) return launch_form<D, NW, F16, PAGED, PD, false, true>(p, plan, out, mask_job, tail, stream);
+    if (!tail.counters && tail.parents) {  // tree keys ride on long splits only
+        if constexpr (PD == kShallowRequests) return launch_form<D, NW, F16, PAGED, PD, false, true>(p, plan, out, mask_job, tail, stream);
+        else return hipErrorInvalidValue;
+    }
     if (!tail.counters) return launch_form<D, NW, F16, PAGED, PD, false, false>(p, plan, out, mask_job, tail, stream);
     if constexpr (PAGED) return hipErrorInvalidValue;
     else return launch_form<D, NW, F16, false, PD, true, false>(p, plan, out, mask_job, tail, stream);

@@ -218,11 +218,3 @@ def test_the_kernel_keeps_its_loads_counted(tmp_path):
     m0 = [ln.strip() for ln in lines if re.search(r"\bm0\b", ln.split(";")[0])]
     assert copies > 0 and len(m0) == copies
     assert all(re.fullmatch(r"s_mov_b32 m0, (s\d+|vcc_lo|vcc_hi)", ln) for ln in m0)
-
-
-def test_the_kernel_that_shares_tiles_leaves_its_loads_alone(tmp_path):
-    asm = tmp_path / "prefix_mfma.s"
-    flags = [f for f in ls_build.FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.run([ls_build.HIPCC, *flags, "-S", "--cuda-device-only", "-o", str(asm),
-                    os.path.join(ls_build.CSRC, "ls_prefix_mfma.hip")], check=True, stderr=subprocess.DEVNULL)
-    loads_left_alone(asm.read_text().splitlines())

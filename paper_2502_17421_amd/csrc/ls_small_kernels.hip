@@ -316,6 +316,23 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
 // LG = D / 8 lanes hold a row in 16-byte pieces.  WIDE: a wavefront per query row, 64 / LG parts per
 // load instruction; else LG lanes per query row (at most 8 parts).  Every load of a row is issued before
 // the first is used; LSEs and rows come together, so a row costs one round trip.
+//
+// Bound by latency: the launch, the arguments, that round trip, and then the instructions of a wave that has its SIMD to itself
+// (some 4 ns each where one waits for the other).  So the row of the tree is a step of its own, and with a wavefront
+// per row a lane loads the LSEs of the parts whose rows it adds up, instead of getting weights from other lanes (69 nodes x 12k
+// keys f16, 16 parts: call 35.4 -> 33.6 us; 64 rows x 32k keys, 32 parts: 35.9 -> 35.3).  With LG lanes per row the loads cost
+// more than they save (eight sequences, paged: 47.4 -> 47.8).
+struct MergeArgs {
+    const void *o_parts;
+    const float *lse_parts;
+    void *out;
+    float *lse;
+    const SequenceSplits *table;
+    int64_t o_stride[3];
+    FastDiv by_tree, by_q_heads;
+    int32_t n_splits, n_tree, n_q_heads, rows_total, has_tree;
+};
+
 template <int LG> __device__ __forceinline__ int max_over_groups(int x)
 {
 #pragma unroll
@@ -326,97 +343,148 @@ template <int LG> __device__ __forceinline__ int max_over_groups(int x)
     return __builtin_amdgcn_readfirstlane(x);
 }
 
+// sum / max over the groups of LG lanes of a wavefront
+template <int LG> __device__ __forceinline__ float groups_sum(float x)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    if constexpr (LG == 8) x += dpp_row<kRowRor8>(x);
+    return x;
+}
+template <int LG> __device__ __forceinline__ float groups_max(float x)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    if constexpr (LG == 8) x = fmaxf(x, dpp_row<kRowRor8>(x));
+    return x;
+}
+
 template <typename T, int D, bool WIDE>
-__global__ void __launch_bounds__(256) merge_parts_kernel(Problem p, WholeCall w, int rows_total)
+__global__ void __launch_bounds__(256) merge_parts_kernel(MergeArgs a)
 {
     constexpr int LG = D / 8;
     constexpr int GROUPS = kWave / LG;                    // parts (WIDE) or query rows per load instruction
     constexpr int NL = WIDE ? 64 / GROUPS : 8;            // load instructions per pass of at most 64 (8) parts
+    constexpr int PASS = WIDE ? 64 : 8;
     typedef Lanes<T, 8> L8;
+    // all arguments by one batch of scalar loads
+    asm volatile("" ::"s"(a.o_parts), "s"(a.lse_parts), "s"(a.out), "s"(a.lse), "s"(a.table), "s"(a.o_stride[0]), "s"(a.o_stride[1]),
+                 "s"(a.o_stride[2]), "s"(a.by_tree.mul), "s"(a.by_q_heads.mul), "s"(a.n_splits), "s"(a.n_tree), "s"(a.n_q_heads));
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     const int group = lane / LG, sl = lane % LG;
-    int r = WIDE ? wave : wave * GROUPS + group;
-    if (WIDE && r >= rows_total) return;
-    const bool live = r < rows_total;
-    r = live ? r : rows_total - 1;
-    const int bh = (int)w.by_tree.div((uint32_t)r), i = r - bh * p.n_tree;
-    const int b = (int)w.by_q_heads.div((uint32_t)bh), h = bh - b * p.n_q_heads;
-    T *orow = (T *)w.out + b * w.o_stride[0] + h * w.o_stride[1] + i * w.o_stride[2] + sl * 8;
-    int n_splits = w.n_splits;                            // of this lane's row
+    int r = WIDE ? __builtin_amdgcn_readfirstlane(wave) : wave * GROUPS + group;
+    if (WIDE && r >= a.rows_total) return;
+    const bool live = r < a.rows_total;
+    r = live ? r : a.rows_total - 1;
+    const int bh = (int)a.by_tree.div((uint32_t)r), i = r - bh * a.n_tree;
+    const int b = (int)a.by_q_heads.div((uint32_t)bh), h = bh - b * a.n_q_heads;
+    T *orow = (T *)a.out + b * a.o_stride[0] + h * a.o_stride[1] + i * a.o_stride[2] + sl * 8;
+    int n_splits = a.n_splits;                            // of this lane's row
     size_t part0 = (size_t)r * n_splits;
-    if (w.table) {
-        const SequenceSplits mine = w.table[b];
-        const int per_seq = p.n_q_heads * p.n_tree;
+    if (a.table) {
+        const SequenceSplits mine = a.table[b];
+        const int per_seq = a.n_q_heads * a.n_tree;
         n_splits = mine.count;
         part0 = (size_t)mine.first * per_seq + (size_t)(r - b * per_seq) * n_splits;
     }
-    const int n_top = WIDE ? n_splits : max_over_groups<LG>(n_splits);  // wave-uniform
-    const T *rows = (const T *)w.o_parts + part0 * D + sl * 8;
-    const float *lses = w.lse_parts + part0;
+    const T *rows = (const T *)a.o_parts + part0 * D + sl * 8;
+    const float *lses = a.lse_parts + part0;
 
-    float o[8], top = -INFINITY, wsum = 0.f;
+    // the part with the tree keys, in fp32: the last one
+    const int n_cached = n_splits - (a.has_tree ? 1 : 0);
+    const int n_top = WIDE ? n_cached : max_over_groups<LG>(n_cached);  // wave-uniform
+    float l_tree = -INFINITY;
+    RawVec<16> high{}, low{};
+    if (a.has_tree) {
+        l_tree = lses[n_cached];
+        high = load_raw<16>(rows + (size_t)n_cached * D);
+        low = load_raw<16>(orow);
+    }
+    float o[8], top = l_tree, wsum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
-    RawVec<16> low{};
-    const int tree_part = w.parents ? n_splits - 1 : -1;
-    if (w.parents) low = load_raw<16>(orow);
-    for (int k0 = 0; k0 < n_top; k0 += WIDE ? 64 : 8) {  // one pass up to 64 (8) parts
-        const int left = n_splits - k0, n = left < (WIDE ? 64 : 8) ? left : (WIDE ? 64 : 8);  // of this row (may be none)
-        const int n_any = n_top - k0;
-        const int mine = WIDE ? lane : sl;                // the part whose LSE this lane holds
-        const float l = mine < n ? lses[k0 + mine] : -INFINITY;
+    // a part without weight may hold anything
+    auto add = [&](float weight, const float (&v)[8]) __attribute__((always_inline)) {
+        wsum += weight;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = __builtin_fmaf(weight, v[e], o[e]);
+    };
+    auto weight_of = [&](float l) __attribute__((always_inline)) {
+        return l == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((l - top) * kLog2e);
+    };
+    for (int k0 = 0; k0 < n_top; k0 += PASS) {
+        constexpr int NLSE = WIDE ? NL : 1;               // WIDE: the LSEs of this lane's parts; else that of part sl of its row
+        float l[NLSE];
         RawVec<16> raw[NL];
 #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int part = WIDE ? k * GROUPS + group : k;
-            if (WIDE ? k * GROUPS < n_any : k < n_any)    // wave-uniform; past the last part: a valid row, weight 0
-                raw[k] = load_raw<16>(rows + (size_t)(part < n ? k0 + part : n_splits - 1) * D);
+        for (int k = 0; k < NLSE; ++k) {
+            const int part = k0 + (WIDE ? k * GROUPS + group : sl);
+            l[k] = (WIDE || sl < PASS) && part < n_cached ? lses[part] : -INFINITY;
         }
-        float t = l;
-#pragma unroll
-        for (int off = WIDE ? 32 : LG / 2; off > 0; off >>= 1) t = fmaxf(t, __shfl_xor(t, off, kWave));
-        const float top_new = fmaxf(top, t);
-        const float scale = top == -INFINITY ? 0.f : exp2f((top - top_new) * kLog2e);
-        wsum *= scale;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] *= scale;
-        top = top_new;
-        const float weight = l == -INFINITY ? 0.f : exp2f((l - top) * kLog2e);
-        wsum += weight;                                   // summed over the lanes at the end
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
-            if (WIDE ? k * GROUPS < n_any : k < n_any) {
-                const int part = WIDE ? k * GROUPS + group : k;
-                const float wk = __shfl(weight, WIDE ? part : group * LG + k, kWave);
+            const int part = k0 + (WIDE ? k * GROUPS + group : k);
+            if (k0 + (WIDE ? k * GROUPS : k) < n_top)     // wave-uniform; past the last part: a valid row, weight 0
+                raw[k] = load_raw<16>(rows + (size_t)(part < n_cached ? part : n_splits - 1) * D);
+        }
+        float t = l[0];
+#pragma unroll
+        for (int k = 1; k < NLSE; ++k) t = fmaxf(t, l[k]);
+        if constexpr (WIDE) {
+            t = groups_max<LG>(t);
+        } else {
+#pragma unroll
+            for (int off = LG / 2; off > 0; off >>= 1) t = fmaxf(t, __shfl_xor(t, off, kWave));
+        }
+        t = fmaxf(t, top);
+        if (k0 > 0) {                                     // what has been added up so far follows the new reference
+            const float scale = top == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((top - t) * kLog2e);
+            wsum *= scale;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] *= scale;
+        }
+        top = t;
+        float w[NLSE];
+#pragma unroll
+        for (int k = 0; k < NLSE; ++k) w[k] = weight_of(l[k]);
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+            if (k0 + (WIDE ? k * GROUPS : k) < n_top) {
+                const float weight = WIDE ? w[k % NLSE] : __shfl(w[0], group * LG + k, kWave);
                 float v[8];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) raw[k].w[e] = weight == 0.f ? 0u : raw[k].w[e];
                 L8::unpack(raw[k], v);
-                if (k0 + part == tree_part) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        v[2 * e] = __uint_as_float(raw[k].w[e] << 16 | (low.w[e] & 0xffffu));
-                        v[2 * e + 1] = __uint_as_float((raw[k].w[e] & 0xffff0000u) | low.w[e] >> 16);
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] += wk == 0.f ? 0.f : wk * v[e];  // empty parts may hold anything
+                add(weight, v);
             }
         }
     }
+    if (a.has_tree) {
+        const float weight = WIDE && group > 0 ? 0.f : weight_of(l_tree);
+        float v[8];
 #pragma unroll
-    for (int off = WIDE ? 32 : LG / 2; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off, kWave);
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = weight == 0.f ? 0.f : __uint_as_float(high.w[e] << 16 | (low.w[e] & 0xffffu));
+            v[2 * e + 1] = weight == 0.f ? 0.f : __uint_as_float((high.w[e] & 0xffff0000u) | low.w[e] >> 16);
+        }
+        add(weight, v);
+    }
     if constexpr (WIDE) {
+        wsum = groups_sum<LG>(wsum);
 #pragma unroll
-        for (int off = 32; off >= LG; off >>= 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off, kWave);
+        for (int e = 0; e < 8; ++e) o[e] = groups_sum<LG>(o[e]);
     }
     const float inv = wsum == 0.f ? 0.f : 1.f / wsum;     // a part whose LSE is NaN makes the row and its LSE NaN
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] *= inv;
     if (live && (!WIDE || group == 0)) {
         store_raw<16>(orow, L8::pack(o));
-        if (sl == 0) w.lse[r] = wsum == 0.f ? -INFINITY : top + log2f(wsum) * kLn2;
+        if (sl == 0) a.lse[r] = wsum == 0.f ? -INFINITY : top + log2f(wsum) * kLn2;
     }
 }
 
@@ -426,10 +494,12 @@ hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, h
     const bool wide = w.n_splits > 8;
     const int rows_per_block = 4 * (wide ? 1 : kWave / (p.head_dim / 8));
     const dim3 block(256), grid((rows + rows_per_block - 1) / rows_per_block);
+    const MergeArgs a{w.o_parts, w.lse_parts, w.out, w.lse, w.table, {w.o_stride[0], w.o_stride[1], w.o_stride[2]},
+                      w.by_tree, w.by_q_heads, w.n_splits, p.n_tree, p.n_q_heads, rows, w.parents != nullptr};
 #define LS_MP_CASE(T, DD)                                                                                   \
     do {                                                                                                    \
-        if (wide) hipLaunchKernelGGL((merge_parts_kernel<T, DD, true>), grid, block, 0, stream, p, w, rows); \
-        else hipLaunchKernelGGL((merge_parts_kernel<T, DD, false>), grid, block, 0, stream, p, w, rows);     \
+        if (wide) hipLaunchKernelGGL((merge_parts_kernel<T, DD, true>), grid, block, 0, stream, a);          \
+        else hipLaunchKernelGGL((merge_parts_kernel<T, DD, false>), grid, block, 0, stream, a);              \
     } while (0)
     if (dtype == LS_BF16 && p.head_dim == 128) LS_MP_CASE(uint16_t, 128);
     else if (dtype == LS_BF16 && p.head_dim == 64) LS_MP_CASE(uint16_t, 64);

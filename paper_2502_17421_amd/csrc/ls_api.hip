@@ -246,6 +246,9 @@ SplitPlan plan_splits(const ls_desc &d, int32_t request)
     plan.split_len = (int32_t)len;
     plan.per_sequence = 0;
     plan.balanced = 0;
+    // blocks of 128 rows where twice the workgroups still have a compute unit each (see ls_prefix_mfma.hip)
+    const int64_t rows_kv = (int64_t)(d.n_q_heads / d.n_kv_heads) * d.n_tree;
+    plan.row_block = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 127) / 128) * s <= compute_units() ? 128 : 256;
     return plan;
 }
 

@@ -121,6 +121,7 @@ struct SplitPlan {
     // MFMA path, whole-path calls that end with merge_parts_kernel, several sequences: the batch * n_splits
     // pieces are dealt to the sequences by their length (see SequenceSplits), all of about the same size.
     int32_t balanced;
+    int32_t row_block;  // query rows per workgroup of the matrix-core kernel, 256 or 128
 };
 
 // n / d for wave-uniform or per-lane n by one multiplication, exact while n * d < 2^32 (the multiplier is

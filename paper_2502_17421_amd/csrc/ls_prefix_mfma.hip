@@ -4,11 +4,19 @@
 //
 // Work decomposition.  All G*T query rows that share a KV head (G query heads x T tree
 // tokens) form one dense query tile, so every cached K/V row is fetched from HBM once per
-// KV head.  A workgroup owns (sequence, KV head, key split, block of up to NW*32 query rows);
-// each of its NW waves owns 32 query rows and all keys of the split.  With NW = 8 two waves
+// KV head.  A workgroup owns (sequence, KV head, key split, block of up to CW*32 query rows);
+// each of its first CW waves owns 32 query rows and all keys of the split.  With CW = 8 two waves
 // share a SIMD (256 registers per lane each), so that one wave's matrix instructions overlap
 // the other's vector work; one workgroup per compute unit, so that all of the LDS is one deep
 // ring of key tiles.
+//
+// Blocks of 128 rows (CW = 4) leave the other wave of each SIMD to the copies: a wave that copies as well spends some
+// 550 of 2500 cycles per pair of tiles in the issue of its copies.  They serve heads with at most 128 rows (eight
+// sequences of 501 to 9003 keys x 8 KV heads x 96 rows, paged: 47.6 against 46.3 us with four waves doing both; 70 shapes
+// of 65 to 128 rows 0.98 of the time, best 0.86, worst 1.03), and heads with more rows while the blocks of 256
+// rows would leave half the chip idle (SplitPlan::row_block): two workgroups then share an XCD's L2 and
+// each has a compute unit (256 rows x 8k keys, 16 splits of 8 heads: 0.73 -> 0.58 us per tile, call 30.2 -> 28.1 us, with
+// four waves doing both 28.6; 5k to 8k keys, 144 to 256 rows 0.93 of the time).  Results do not depend on the form.
 //
 // Data movement.  K and V rows go HBM -> LDS directly (global_load_lds_dwordx4, 16 bytes
 // per lane, no staging registers) in tiles of 32 keys.  K tiles and V tiles have rings of
@@ -93,7 +101,8 @@ template <bool F16> constexpr float kSumCap = F16 ? 0x1p15f : 0x1p40f;
 // otherwise be kept over the key loop (180 scalar registers spilled to vector lanes, against 20).
 // TREE: tree keys on the last split.  A form of its own as well: calls without them would fetch and step over the tree
 // code (8k keys, 64 nodes on the tail route, code not in the caches: 23.8 us against 21.8).
-template <int D, int NW, bool F16, bool PAGED, int PD, bool FUSED, bool TREE>
+// NW waves, of which CW have query rows.
+template <int D, int NW, int CW, bool F16, bool PAGED, int PD, bool FUSED, bool TREE>
 __global__ void __launch_bounds__(NW * 64, 2048 / (NW * 64) / 4)  // at most 256 registers per lane: no AGPR copies
 prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, FusedTail tail, int32_t n_qblocks)
 {
@@ -106,13 +115,15 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     constexpr int TILEB = TK * ROWB;          // bytes per K (or V) tile
     constexpr int ROWS_PER_LOAD = 64 / CH;    // rows one 64-lane load instruction covers
     constexpr int TPT = TK / ROWS_PER_LOAD;   // load instructions per tile and tensor
-    // The first NL waves do all the copying.  With two waves per SIMD these are the older ones,
-    // which the hardware serves first: they reach every barrier early and have the time.
+    // NL waves do all the copying: those without rows, or the first ones.  With two waves per SIMD these are the
+    // older ones, which the hardware serves first: they reach every barrier early and have the time.
     constexpr int NL = 4;
+    constexpr bool COPIERS = CW < NW;         // waves CW and up copy and have no rows
     constexpr int LOADS = TPT / NL;           // load instructions per loader wave, tile and tensor
     constexpr int INFLIGHT = 2 * LOADS;       // vmem instructions per loader wave and whole request
     constexpr uint32_t V_RING = KS * TILEB;   // LDS byte offset of the V ring
     static_assert(LOADS >= 1 && TPT % NL == 0 && NL <= NW, "tile rows must divide over the loader waves");
+    static_assert(!COPIERS || NW - CW == NL, "the waves without rows are the loader waves");
     static_assert((PD + 1) * INFLIGHT <= 63, "the vmcnt counter holds at most 63 outstanding loads");
     static_assert(NW * 32 * ROWB <= (KS + VS) * TILEB, "the partial rows are staged in the rings at the end");
 
@@ -213,7 +224,7 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     k_lo = k_lo < k_hi ? k_lo : k_hi;
 
     // The query row of this lane.
-    const int wave_row0 = (qblock * NW + wave) * 32;
+    const int wave_row0 = COPIERS && wave >= CW ? rows_kv : (qblock * CW + wave) * 32;
     const int m_row = wave_row0 + li;
     const bool q_ok = m_row < rows_kv;
     const int hq = g * p.group + (q_ok ? m_row / p.n_tree : 0);
@@ -263,11 +274,11 @@ prefix_mfma_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job, Fu
     const uint32_t smem_off = lds_offset(smem);
     // The rows a loader wave copies: LOADS groups of ROWS_PER_LOAD rows per tensor, group j starting
     // at tile row load_row0(j).
-    const bool loader = wave < NL;
-    // With eight waves, the first window of tiles (requests -PD .. -1) is copied by the other four:
+    const bool loader = COPIERS ? wave >= NW - NL : wave < NL;
+    // With eight waves that have rows, the first window of tiles (requests -PD .. -1) is copied by the other four:
     // a wave that issues a whole window sits in the issue stall while the window fills, and the
     // loader waves should be through tile 0 by then.  Wave NL + i copies the rows loader i would.
-    const bool starter = NW >= 2 * NL ? (wave >= NL && wave < 2 * NL) : loader;
+    const bool starter = NW >= 2 * NL && !COPIERS ? (wave >= NL && wave < 2 * NL) : loader;
     auto load_row0 = [&](int j) __attribute__((always_inline)) { return ((wave % NL) * LOADS + j) * ROWS_PER_LOAD; };
     // byte offsets of this lane's pieces relative to the first row of a tile (whole tiles)
     uint32_t k_voff[LOADS], v_voff[LOADS];
@@ -1038,18 +1049,18 @@ bool prefix_mfma_supports(const Problem &p, int dtype)
 
 namespace {
 
-template <int D, int NW, bool F16, bool PAGED, int PD, bool FUSED, bool TREE>
+template <int D, int NW, int CW, bool F16, bool PAGED, int PD, bool FUSED, bool TREE>
 hipError_t launch_form(const Problem &p, const SplitPlan &plan, const Partials &out, const MaskJob &mask_job,
                       const FusedTail &tail, hipStream_t stream)
 {
     constexpr int lds_bytes = (2 * PD + 7) * TK * D * 2 + (PAGED ? kMaxSplitPages * 4 : 0) + (LS_MAX_TREE + 2 * NW) * 4;
     static_assert(lds_bytes <= 160 * 1024, "the rings exceed the 160 KB of a compute unit");
-    auto kernel = prefix_mfma_kernel<D, NW, F16, PAGED, PD, FUSED, TREE>;
+    auto kernel = prefix_mfma_kernel<D, NW, CW, F16, PAGED, PD, FUSED, TREE>;
     static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  lds_bytes);
     if (attr != hipSuccess) return attr;
     const int rows_kv = p.group * p.n_tree;
-    const int n_qblocks = (rows_kv + NW * 32 - 1) / (NW * 32);
+    const int n_qblocks = (rows_kv + CW * 32 - 1) / (CW * 32);
     const int64_t n_main = (int64_t)plan.n_splits * n_qblocks * p.batch * p.n_kv_heads;
     const int64_t n_blocks = n_main + (mask_job.parents ? p.batch : 0);
     if (n_blocks > 0x7fffffff) return hipErrorInvalidValue;
@@ -1061,17 +1072,17 @@ hipError_t launch_form(const Problem &p, const SplitPlan &plan, const Partials &
     return hipGetLastError();
 }
 
-template <int D, int NW, bool F16, bool PAGED, int PD>
+template <int D, int NW, int CW, bool F16, bool PAGED, int PD>
 hipError_t launch_one(const Problem &p, const SplitPlan &plan, const Partials &out, const MaskJob &mask_job,
                       const FusedTail &tail, hipStream_t stream)
 {
     if (!tail.counters && tail.parents) {  // tree keys ride on long splits only
-        if constexpr (PD == kShallowRequests) return launch_form<D, NW, F16, PAGED, PD, false, true>(p, plan, out, mask_job, tail, stream);
+        if constexpr (PD == kShallowRequests) return launch_form<D, NW, CW, F16, PAGED, PD, false, true>(p, plan, out, mask_job, tail, stream);
         else return hipErrorInvalidValue;
     }
-    if (!tail.counters) return launch_form<D, NW, F16, PAGED, PD, false, false>(p, plan, out, mask_job, tail, stream);
-    if constexpr (PAGED) return hipErrorInvalidValue;
-    else return launch_form<D, NW, F16, false, PD, true, false>(p, plan, out, mask_job, tail, stream);
+    if (!tail.counters) return launch_form<D, NW, CW, F16, PAGED, PD, false, false>(p, plan, out, mask_job, tail, stream);
+    if constexpr (PAGED || CW < NW) return hipErrorInvalidValue;
+    else return launch_form<D, NW, CW, F16, false, PD, true, false>(p, plan, out, mask_job, tail, stream);
 }
 
 }  // namespace
@@ -1089,16 +1100,21 @@ hipError_t launch_prefix_mfma(const Problem &p, int dtype, const SplitPlan &plan
     const int rows_kv = p.group * p.n_tree;
     const bool f16 = dtype == LS_F16;
     const bool paged = p.block_table != nullptr;
-    // Above 128 query rows per KV head: 8 waves, two per SIMD, 256 rows per workgroup (the split
-    // planner counts on kPrefixRowsPerWorkgroup = 256); else 4 waves.
+    // Blocks of 256 rows: 8 waves, two per SIMD.  Of 128 (at most 128 rows per KV head, or too few blocks of 256 to
+    // fill half the chip): 4 waves, and 4 that copy.  HIP takes fewer than 2^32 threads in a launch; where there would be more, and in
+    // the single-launch call, whose counters are laid out for it (prefix_mfma_query_blocks), the 4 waves of a block of 128
+    // rows copy for themselves.
+    const bool eight = rows_kv > 128 && (tail.counters || plan.row_block > 128);
+    const int64_t blocks = (int64_t)((rows_kv + 127) / 128) * p.batch * p.n_kv_heads * plan.n_splits + p.batch;
+    const bool copiers = !tail.counters && blocks < (1ll << 32) / 512;
     const bool deep = plan.split_len <= kDeepMaxTiles * TK;  // few tiles per split: request them all at once
-#define LS_MFMA_CASE3(DD, WW, PP)                                                                      \
-    (paged ? (f16 ? launch_one<DD, WW, true, true, PP>(p, plan, out, mask_job, tail, stream)           \
-                  : launch_one<DD, WW, false, true, PP>(p, plan, out, mask_job, tail, stream))         \
-           : (f16 ? launch_one<DD, WW, true, false, PP>(p, plan, out, mask_job, tail, stream)          \
-                  : launch_one<DD, WW, false, false, PP>(p, plan, out, mask_job, tail, stream)))
-#define LS_MFMA_CASE2(DD, WW) (deep ? LS_MFMA_CASE3(DD, WW, kDeepRequests) : LS_MFMA_CASE3(DD, WW, kShallowRequests))
-#define LS_MFMA_CASE(DD) (rows_kv > 128 ? LS_MFMA_CASE2(DD, 8) : LS_MFMA_CASE2(DD, 4))
+#define LS_MFMA_CASE3(DD, WW, CC, PP)                                                                      \
+    (paged ? (f16 ? launch_one<DD, WW, CC, true, true, PP>(p, plan, out, mask_job, tail, stream)           \
+                  : launch_one<DD, WW, CC, false, true, PP>(p, plan, out, mask_job, tail, stream))         \
+           : (f16 ? launch_one<DD, WW, CC, true, false, PP>(p, plan, out, mask_job, tail, stream)          \
+                  : launch_one<DD, WW, CC, false, false, PP>(p, plan, out, mask_job, tail, stream)))
+#define LS_MFMA_CASE2(DD, WW, CC) (deep ? LS_MFMA_CASE3(DD, WW, CC, kDeepRequests) : LS_MFMA_CASE3(DD, WW, CC, kShallowRequests))
+#define LS_MFMA_CASE(DD) (eight ? LS_MFMA_CASE2(DD, 8, 8) : copiers ? LS_MFMA_CASE2(DD, 8, 4) : LS_MFMA_CASE2(DD, 4, 4))
     if (p.head_dim == 128) return LS_MFMA_CASE(128);
     if (p.head_dim == 64) return LS_MFMA_CASE(64);
 #undef LS_MFMA_CASE

@@ -375,6 +375,40 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
     return w;
 }
 
+// Float calls: one form, so only its sizes are chosen: 16 or 32 query rows per workgroup, and into how many runs of
+// 16-key tiles the keys of a sequence are cut.  Modelled time (microseconds, measured on MI355X):
+//   rounds of workgroups * (2 (32 rows: 3) + tiles of a workgroup / 8 * t), t = 1.4 (2.65) at head_dim 64, 3.05 (4.9) at 128
+//   more than one run: 2.9 (head_dim 64) or 3.3 for the merge and its launch, and the parts at 3.5 TB/s
+// Both row counts and all run counts against this choice, 22 shapes: within 8 % of the best one (1024 keys x 64 rows, head_dim
+// 64, 1, 9 and 16 runs 18.4, 10.0 and 9.6 us; 8 KV heads x 64 rows x 1024 keys, head_dim 128, 1, 5 and 8 runs 32.7,
+// 16.8 and 13.9; 8 sequences x 8 KV heads x 160 rows x 4096 keys, 1, 2 and 4 runs of 32 rows 327, 267 and 246, of 16 rows 314, 286).
+WholePlan plan_float(const ls_desc &d, const SplitPlan &plan, bool with_tree)
+{
+    const int64_t rows_kv = (int64_t)(d.n_q_heads / d.n_kv_heads) * d.n_tree, cus = compute_units();
+    const int64_t tiles = (d.max_prefix_len + 15ll) / 16 + (with_tree ? (d.n_tree + 15) / 16 : 0);
+    const bool wide = d.head_dim == 128;
+    const double part_us = (double)d.batch * d.n_q_heads * d.n_tree * d.head_dim * 4.0 / 3.5e6;
+    WholePlan w{0, 0, true};
+    double best = 0.0;
+    for (int rt = 1; rt <= 2; ++rt) {
+        const int64_t units = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 16 * rt - 1) / (16 * rt));
+        const double start = rt == 1 ? 2.0 : 3.0, tile = (wide ? (rt == 1 ? 3.05 : 4.9) : (rt == 1 ? 1.4 : 2.65)) / 8.0;
+        auto consider = [&](int64_t n) {
+            n = n < 1 ? 1 : (n > plan.n_splits ? plan.n_splits : n);
+            const double rounds = (double)((units * n + cus - 1) / cus), per = (double)((tiles + n - 1) / n);
+            const double cost = rounds * (start + per * tile) + (n > 1 ? (wide ? 3.3 : 2.9) + (double)n * part_us : 0.0);
+            if (w.row_tiles == 0 || cost < best) {
+                best = cost;
+                w.row_tiles = rt;
+                w.n_splits = (int32_t)n;
+            }
+        };
+        for (int64_t per = 4; per < tiles; per += per < 16 ? 4 : per / 2) consider((tiles + per - 1) / per);
+        for (int64_t rounds = 1; rounds <= 6; ++rounds) consider(rounds * cus / units);
+    }
+    return w;
+}
+
 }  // namespace ls
 
 using namespace ls;
@@ -521,10 +555,12 @@ int run_whole(const ls_desc &d, const Problem &p, SplitPlan splits, const WholeP
               int32_t *err, void *out, float *lse, void *o_parts, float *lse_parts, SequenceSplits *table, hipStream_t s)
 {
     WholeCall w{parents, err, out, {d.o_stride[0], d.o_stride[1], d.o_stride[2]}, lse, o_parts, lse_parts, plan.n_splits,
-                FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads), nullptr};
+                FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads), nullptr, plan.n_splits > 1};
     if (plan.row_tiles > 0) {
+        // (a float call's outputs may lie over its inputs: the merge writes them when the inputs have been read)
+        if (d.dtype == LS_F32 && !w.in_parts) w.in_parts = outputs_overlap_inputs(d, p, parents, out, lse);
         if (launch_wave_split(p, d.dtype, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
-        if (plan.n_splits == 1) return LS_OK;
+        if (!w.in_parts) return LS_OK;
     } else {
         const Partials parts{o_parts, lse_parts, plan.n_splits, 0, 1, 1};
         FusedTail tail{};
@@ -570,6 +606,8 @@ int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, c
     hipStream_t s = (hipStream_t)stream;
     Problem p = make_problem(*desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree);
     p.prefix_len_all = prefix_len_all;
+    if (desc->dtype == LS_F32)
+        return run_whole(*desc, p, plan, plan_float(*desc, plan, true), parents, err, out, lse, o_parts, lse_parts, nullptr, s);
     if (prefix_mfma_supports(p, desc->dtype) && !single_launch) {
         const WholePlan whole = plan_whole(*desc, plan, p, parents, out, lse);
         if (whole.ride) return run_whole(*desc, p, plan, whole, parents, err, out, lse, o_parts, lse_parts, (SequenceSplits *)mask, s);
@@ -599,14 +637,7 @@ int hybrid_contiguous(const ls_desc *desc, const void *q, const void *k_cache, c
             return LS_ERR_HIP;
         if (fused) return LS_OK;
     } else {
-        const Partials f32_out{o_parts, lse_parts, w.n_parts, 0, 0, 1};
-        if (is_16bit(desc->dtype)) return LS_ERR_UNSUPPORTED;  // 16-bit row strides beyond the MFMA kernel's range
-        // the mask rides on the same launch when its grid slice has a workgroup per sequence
-        const int n_qblocks = (p.group * p.n_tree + 31) / 32;
-        const bool ride = (int64_t)plan.n_splits * n_qblocks >= desc->batch;
-        if (launch_prefix_valu(p, desc->dtype, plan, f32_out, ride ? MaskJob{parents, mask, err} : MaskJob{nullptr, nullptr, nullptr}, s) != hipSuccess)
-            return LS_ERR_HIP;
-        if (!ride && launch_tree_mask(parents, desc->batch, desc->n_tree, mask, err, s) != hipSuccess) return LS_ERR_HIP;
+        return LS_ERR_UNSUPPORTED;  // 16-bit row strides beyond the MFMA kernel's range
     }
     // (c) tree keys and (d) merge, one wavefront per query row
     if (launch_tree_merge(p, desc->dtype, mask, cache_out, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)
@@ -695,16 +726,13 @@ int ls_cache_attn(const ls_desc *desc, const void *q, const void *k_cache, const
     void *o_parts = base + w.off_o;
     hipStream_t s = (hipStream_t)stream;
     const Problem p = make_problem(*desc, q, k_cache, v_cache, prefix_lens, nullptr, nullptr);
-    const bool mfma = prefix_mfma_supports(p, desc->dtype);
-    if (!mfma && is_16bit(desc->dtype)) return LS_ERR_UNSUPPORTED;
-    if (mfma) {
-        const WholePlan whole = plan_whole(*desc, plan, p, nullptr, out, lse);
-        if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, (SequenceSplits *)(base + w.off_mask), s);
-    }
-    const Partials parts{o_parts, lse_parts, w.n_parts, 0, is_16bit(desc->dtype), 1};
-    const hipError_t e = mfma ? launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s)
-                              : launch_prefix_valu(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, s);
-    if (e != hipSuccess) return LS_ERR_HIP;
+    if (desc->dtype == LS_F32)
+        return run_whole(*desc, p, plan, plan_float(*desc, plan, false), nullptr, nullptr, out, lse, o_parts, lse_parts, nullptr, s);
+    if (!prefix_mfma_supports(p, desc->dtype)) return LS_ERR_UNSUPPORTED;
+    const WholePlan whole = plan_whole(*desc, plan, p, nullptr, out, lse);
+    if (whole.ride) return run_whole(*desc, p, plan, whole, nullptr, nullptr, out, lse, o_parts, lse_parts, (SequenceSplits *)(base + w.off_mask), s);
+    const Partials parts{o_parts, lse_parts, w.n_parts, 0, 1, 1};
+    if (launch_prefix_mfma(p, desc->dtype, plan, parts, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, s) != hipSuccess) return LS_ERR_HIP;
     // the tail kernel without a mask: merge of the split partials only
     if (launch_tree_merge(p, desc->dtype, nullptr, parts, plan.n_splits, out, desc->o_stride, lse, s) != hipSuccess)
         return LS_ERR_HIP;

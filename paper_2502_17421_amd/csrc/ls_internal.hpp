@@ -57,7 +57,7 @@ struct Partials {
     }
 };
 
-// Work appended to the cached-key launch so that the whole call needs one launch less:
+// Work appended to the launch of the kernel for 16-bit cached keys so that the whole call needs one launch less:
 // extra workgroups (one per sequence) that build the tree mask.  parents == nullptr: none.
 struct MaskJob {
     const int32_t *parents;
@@ -134,9 +134,9 @@ struct FastDiv {
     __device__ __forceinline__ uint32_t div(uint32_t n) const { return d > 1 ? __umulhi(n, mul) : n; }
 };
 
-// Outputs of a whole-path call whose kernels take the tree keys as further key tiles (16-bit inputs).
-// n_splits == 1: out and lse are final.  More: partial rows [b, head, tree row, split] in the problem's
-// type with float LSEs.  The last split holds the tree keys (parents != nullptr); its rows are in fp32, the
+// Outputs of a whole-path call whose kernels take the tree keys as further key tiles.
+// in_parts == 0: out and lse are final.  Else partial rows [b, head, tree row, split] in the problem's
+// type with float LSEs.  The last split holds the tree keys (parents != nullptr); its rows are in fp32, of a 16-bit problem the
 // upper 16 bits of each value in the partial row and the lower 16 bits in the row of `out`.
 struct WholeCall {
     const int32_t *parents;  // nullptr: cached keys only
@@ -149,6 +149,7 @@ struct WholeCall {
     int32_t n_splits;
     FastDiv by_splits, by_tree, by_kv_heads, by_q_heads;  // divisors n_splits, n_tree, n_kv_heads, n_q_heads
     const SequenceSplits *table;  // balanced call: pieces per sequence; nullptr: n_splits each
+    int32_t in_parts;             // rows leave as parts, also those of a single split
 };
 
 // bf16 <-> float on raw 16-bit patterns (round to nearest even, NaN kept quiet).
@@ -248,7 +249,12 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
 
 // Whole-path kernel whose waves split the keys (32 * row_tiles query rows per workgroup, 1 or 2).
 hipError_t launch_wave_split(const Problem &p, int dtype, int row_tiles, const WholeCall &w, hipStream_t stream);
-// Merge of the parts of a whole-path call (w.n_splits > 1) into out / lse.
+// The same in fp32 (row_tiles * 16 query rows per workgroup), what launch_wave_split runs for LS_F32; the stand-alone call's
+// pieces of plan.split_len rows; and the merge of its parts, what launch_merge_parts runs.
+hipError_t launch_float_split(const Problem &p, int row_tiles, const WholeCall &w, hipStream_t stream);
+hipError_t launch_float_pieces(const Problem &p, const SplitPlan &plan, const Partials &out, hipStream_t stream);
+hipError_t launch_merge_float(const Problem &p, const WholeCall &w, hipStream_t stream);
+// Merge of the parts of a whole-path call (w.in_parts) into out / lse.
 hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream);
 
 hipError_t launch_tree_accept(const int32_t *parents, const int32_t *draft_tokens, const int32_t *target_tokens,

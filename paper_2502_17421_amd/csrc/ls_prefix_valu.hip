@@ -1,6 +1,5 @@
-// Split-KV attention over the cached keys on the vector ALUs, with float arithmetic
-// throughout.  This is the true-fp32 variant of step (b) (appendix: o_cache, LSE_cache per
-// split) and the fallback for shapes the MFMA kernel does not take.
+// Split-KV attention over the cached keys on the vector ALUs, with float arithmetic throughout (step (b);
+// appendix: o_cache, LSE_cache per split): the fallback for 16-bit inputs whose strides the MFMA kernel does not take.
 //
 // One workgroup = one (sequence, KV head, block of 32 query rows, key split).  The query
 // rows of a KV head are the G*T rows (g, t) of its G query heads.  Keys are streamed in
@@ -15,7 +14,6 @@ namespace {
 constexpr int TQ = 32;  // query rows per workgroup
 constexpr int TK = 32;  // keys per tile
 
-__device__ __forceinline__ float4 load4(const float *p) { return *(const float4 *)p; }
 __device__ __forceinline__ float4 load4(const uint16_t *p)
 {
     const uint2 v = *(const uint2 *)p;
@@ -32,7 +30,7 @@ __device__ __forceinline__ float4 load4(const half_t *p)
 
 template <typename T, int D>
 __global__ void __launch_bounds__(256)
-prefix_valu_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job)
+prefix_valu_kernel(Problem p, SplitPlan plan, Partials out)
 {
     constexpr int KP = D + 4;  // padded row, still 16-byte aligned: the 8 rows a wave reads together hit distinct banks
     __shared__ __attribute__((aligned(16))) float q_s[TQ][KP];
@@ -42,17 +40,6 @@ prefix_valu_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job)
 
     const int tid = threadIdx.x;
     const int r = tid >> 3, c = tid & 7;
-    // One extra z-slice of the grid (present only in the whole-path launch) builds the tree masks,
-    // one workgroup per sequence, so that the call needs one launch less.
-    if ((int)blockIdx.z == p.batch * p.n_kv_heads) {
-        const int mb = blockIdx.y * gridDim.x + blockIdx.x;
-        if (mb >= p.batch) return;
-        const int words = (p.n_tree + 63) >> 6;
-        build_tree_mask_rows(mask_job.parents + (size_t)mb * p.n_tree, p.n_tree,
-                             mask_job.mask + (size_t)mb * p.n_tree * words,
-                             mask_job.err_flag ? mask_job.err_flag + mb : nullptr, tid, (int)blockDim.x);
-        return;
-    }
     const int split = blockIdx.x;
     const int qblock = blockIdx.y;
     const int b = blockIdx.z / p.n_kv_heads;
@@ -219,20 +206,17 @@ prefix_valu_kernel(Problem p, SplitPlan plan, Partials out, MaskJob mask_job)
 hipError_t launch_prefix_valu(const Problem &p, int dtype, const SplitPlan &plan, const Partials &out,
                               const MaskJob &mask_job, hipStream_t stream)
 {
+    if (mask_job.parents) return hipErrorInvalidValue;  // no call has this kernel build the mask
+    if (dtype == LS_F32) return launch_float_pieces(p, plan, out, stream);
     const int rows_kv = p.group * p.n_tree;
     const int n_qblocks = (rows_kv + TQ - 1) / TQ;
-    const bool with_mask = mask_job.parents != nullptr;
-    // the mask slice offers n_splits * n_qblocks workgroups: enough for the batch?
-    if (with_mask && (int64_t)plan.n_splits * n_qblocks < p.batch) return hipErrorInvalidValue;
-    const dim3 block(256), grid(plan.n_splits, n_qblocks, p.batch * p.n_kv_heads + (with_mask ? 1 : 0));
+    const dim3 block(256), grid(plan.n_splits, n_qblocks, p.batch * p.n_kv_heads);
 #define LS_PV_CASE(T, DD) \
-    hipLaunchKernelGGL((prefix_valu_kernel<T, DD>), grid, block, 0, stream, p, plan, out, mask_job)
+    hipLaunchKernelGGL((prefix_valu_kernel<T, DD>), grid, block, 0, stream, p, plan, out)
     if (dtype == LS_BF16 && p.head_dim == 128) LS_PV_CASE(uint16_t, 128);
     else if (dtype == LS_BF16 && p.head_dim == 64) LS_PV_CASE(uint16_t, 64);
     else if (dtype == LS_F16 && p.head_dim == 128) LS_PV_CASE(half_t, 128);
     else if (dtype == LS_F16 && p.head_dim == 64) LS_PV_CASE(half_t, 64);
-    else if (dtype == LS_F32 && p.head_dim == 128) LS_PV_CASE(float, 128);
-    else if (dtype == LS_F32 && p.head_dim == 64) LS_PV_CASE(float, 64);
     else return hipErrorInvalidValue;
 #undef LS_PV_CASE
     return hipGetLastError();

@@ -299,9 +299,7 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
             else LS_TM_CASE(half_t, float, 64);
         }
     } else {
-        if (cache_parts.o_is_16bit) return hipErrorInvalidValue;
-        if (p.head_dim == 128) LS_TM_CASE(float, float, 128);
-        else LS_TM_CASE(float, float, 64);
+        return hipErrorInvalidValue;  // float calls end with merge_float_kernel
     }
 #undef LS_TM_CASE
 #undef LS_TM_LAUNCH
@@ -490,6 +488,7 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(MergeArgs a)
 
 hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream)
 {
+    if (dtype == LS_F32) return launch_merge_float(p, w, stream);
     const int rows = p.batch * p.n_q_heads * p.n_tree;
     const bool wide = w.n_splits > 8;
     const int rows_per_block = 4 * (wide ? 1 : kWave / (p.head_dim / 8));

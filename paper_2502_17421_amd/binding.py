@@ -1,4 +1,5 @@
-"""ctypes binding of the C ABI in include/ls_attn.h -- argument marshalling only.
+"""Binding of the C ABI in include/ls_attn.h -- argument marshalling only, by ctypes, and for the device calls by a
+native module (csrc_bind/ls_call.cpp) if it is built.
 
 Every function here has the name of the C entry point it calls and does nothing but turn
 torch tensors into device pointers, sizes and strides.  All arithmetic runs in the HIP
@@ -8,7 +9,10 @@ raises: there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
+import types
 from typing import Optional
 
 import torch
@@ -17,6 +21,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # LS_ATTN_LIB: load this build of the library instead of the in-tree one (the sanitizer test points it
 # at a build whose host code is instrumented)
 LIB_PATH = os.environ.get("LS_ATTN_LIB") or os.path.join(_HERE, "libls_attn.so")
+
+CALL_PATH = os.path.join(_HERE, "_ls_call.so")
 
 LS_OK = 0
 LS_ERR_NULL, LS_ERR_SHAPE, LS_ERR_DTYPE, LS_ERR_STRIDE = -1, -2, -3, -4
@@ -92,14 +98,41 @@ def lib() -> ctypes.CDLL:
                  "ls_kv_commit", "ls_hybrid_tree_attn_paged", "ls_cache_attn_paged",
                  "ls_kv_commit_paged"):
         getattr(L, name).restype = ctypes.c_int
+    L.call = _device_calls(L)
     _lib = L
     return L
 
 
-# Small calls are bound by the host side, so the marshalling stays thin: pointer arguments are declared
-# c_void_p, which takes a plain integer as well as an object, and the current stream's handle is read
-# directly instead of through a Stream object (marshalling of one whole call 5.0 -> 1.8 us, of which the
-# stream 2.9 -> 0.2).
+_DEVICE_CALLS = ("ls_hybrid_tree_attn", "ls_hybrid_tree_attn_single", "ls_hybrid_tree_attn_static",
+                 "ls_hybrid_tree_attn_fused", "ls_hybrid_tree_attn_paged", "ls_workspace_init", "ls_cache_attn",
+                 "ls_cache_attn_paged", "ls_build_tree_mask", "ls_prefix_attn_splitkv", "ls_tree_attn_masked",
+                 "ls_lse_merge", "ls_tree_accept_greedy", "ls_kv_commit", "ls_kv_commit_paged")
+
+
+def _device_calls(L):
+    """The device entry points of a loaded library as callables that take tensors (None, addresses) for pointers and
+    an ls_desc for its address."""
+    calls = types.SimpleNamespace()
+    native = None
+    if os.path.exists(CALL_PATH):
+        loader = importlib.machinery.ExtensionFileLoader("_ls_call", CALL_PATH)
+        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_ls_call", loader))
+        loader.exec_module(native)
+
+    def through_ctypes(fn):
+        def call(*args):
+            return fn(*[ctypes.byref(a) if isinstance(a, ls_desc) else a.data_ptr() if hasattr(a, "data_ptr") else a
+                        for a in args])
+        return call
+
+    for name in _DEVICE_CALLS:
+        fn = getattr(L, name)
+        setattr(calls, name, native.Caller(ctypes.cast(fn, _vp).value, name) if native else through_ctypes(fn))
+    return calls
+
+
+# Small calls are bound by the host side, so the marshalling stays thin: tensors go to the native module as they are, and the
+# current stream's handle is read directly instead of through a Stream object (2.9 -> 0.2 us).
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
@@ -208,9 +241,8 @@ def ls_workspace_error(desc: ls_desc, workspace: torch.Tensor) -> int:
 
 def ls_hybrid_tree_attn(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree, parents, out, lse, workspace,
                         stream=None, check: bool = True) -> int:
-    st = lib().ls_hybrid_tree_attn(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_lens),
-                                   _ptr(k_tree), _ptr(v_tree), _ptr(parents), _ptr(out), _ptr(lse),
-                                   _ptr(workspace), _bytes(workspace), _stream(stream))
+    st = lib().call.ls_hybrid_tree_attn(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree, parents, out, lse,
+                                        workspace, _bytes(workspace), _stream(stream))
     if check:
         _check(st, "ls_hybrid_tree_attn")
     return int(st)
@@ -219,9 +251,8 @@ def ls_hybrid_tree_attn(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree, 
 def ls_hybrid_tree_attn_single(desc, q, k_cache, v_cache, prefix_len, k_tree, v_tree, parents, out, lse, workspace,
                                stream=None, check: bool = True) -> int:
     """One sequence (desc.batch == 1), prefix length as a host integer."""
-    st = lib().ls_hybrid_tree_attn_single(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), int(prefix_len),
-                                          _ptr(k_tree), _ptr(v_tree), _ptr(parents), _ptr(out), _ptr(lse),
-                                          _ptr(workspace), _bytes(workspace), _stream(stream))
+    st = lib().call.ls_hybrid_tree_attn_single(desc, q, k_cache, v_cache, int(prefix_len), k_tree, v_tree, parents,
+                                               out, lse, workspace, _bytes(workspace), _stream(stream))
     if check:
         _check(st, "ls_hybrid_tree_attn_single")
     return int(st)
@@ -230,9 +261,8 @@ def ls_hybrid_tree_attn_single(desc, q, k_cache, v_cache, prefix_len, k_tree, v_
 def ls_hybrid_tree_attn_static(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree, parents, out, lse,
                                stream=None, check: bool = True) -> int:
     """The whole path without a workspace argument (the library's own fixed scratch array)."""
-    st = lib().ls_hybrid_tree_attn_static(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                          _ptr(prefix_lens), _ptr(k_tree), _ptr(v_tree), _ptr(parents), _ptr(out),
-                                          _ptr(lse), _stream(stream))
+    st = lib().call.ls_hybrid_tree_attn_static(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree, parents, out,
+                                               lse, _stream(stream))
     if check:
         _check(st, "ls_hybrid_tree_attn_static")
     return int(st)
@@ -243,7 +273,7 @@ LS_WORKSPACE_COUNTER_BYTES = 4096 * 24
 
 def ls_workspace_init(workspace, stream=None, check: bool = True) -> int:
     """Zero the arrival counters at the start of a workspace (needed once before ls_hybrid_tree_attn_fused)."""
-    st = lib().ls_workspace_init(_ptr(workspace), _bytes(workspace), _stream(stream))
+    st = lib().call.ls_workspace_init(workspace, _bytes(workspace), _stream(stream))
     if check:
         _check(st, "ls_workspace_init")
     return int(st)
@@ -253,9 +283,8 @@ def ls_hybrid_tree_attn_fused(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_
                               stream=None, check: bool = True) -> int:
     """The whole path in one launch: the workgroups of a query block merge its rows between them once all
     have written their parts (counters at the workspace start; ls_workspace_init before the first call)."""
-    st = lib().ls_hybrid_tree_attn_fused(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_lens),
-                                         _ptr(k_tree), _ptr(v_tree), _ptr(parents), _ptr(out), _ptr(lse),
-                                         _ptr(workspace), _bytes(workspace), _stream(stream))
+    st = lib().call.ls_hybrid_tree_attn_fused(desc, q, k_cache, v_cache, prefix_lens, k_tree, v_tree, parents, out,
+                                              lse, workspace, _bytes(workspace), _stream(stream))
     if check:
         _check(st, "ls_hybrid_tree_attn_fused")
     return int(st)
@@ -270,8 +299,8 @@ def ls_set_single_launch_polls(polls: int, check: bool = True) -> int:
 
 
 def ls_cache_attn(desc, q, k_cache, v_cache, prefix_lens, out, lse, workspace, stream=None, check: bool = True) -> int:
-    st = lib().ls_cache_attn(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_lens), _ptr(out),
-                             _ptr(lse), _ptr(workspace), _bytes(workspace), _stream(stream))
+    st = lib().call.ls_cache_attn(desc, q, k_cache, v_cache, prefix_lens, out, lse, workspace, _bytes(workspace),
+                                  _stream(stream))
     if check:
         _check(st, "ls_cache_attn")
     return int(st)
@@ -279,8 +308,7 @@ def ls_cache_attn(desc, q, k_cache, v_cache, prefix_lens, out, lse, workspace, s
 
 def ls_build_tree_mask(parents, mask, err_flag=None, stream=None, check: bool = True) -> int:
     """parents: device int32 [batch, n_tree]; mask: device int64/uint64 storage [batch, n_tree, words]."""
-    st = lib().ls_build_tree_mask(_ptr(parents), parents.shape[0], parents.shape[1], _ptr(mask), _ptr(err_flag),
-                                  _stream(stream))
+    st = lib().call.ls_build_tree_mask(parents, parents.shape[0], parents.shape[1], mask, err_flag, _stream(stream))
     if check:
         _check(st, "ls_build_tree_mask")
     return int(st)
@@ -290,25 +318,23 @@ def ls_prefix_attn_splitkv(desc, q, k_cache, v_cache, prefix_lens, n_splits, o_p
                            check: bool = True) -> int:
     """o_part: float32 tensor, or a tensor of the problem's own 16-bit type, [B,Hq,n_splits,T,D]; its dtype selects
     part_dtype."""
-    st = lib().ls_prefix_attn_splitkv(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(prefix_lens),
-                                      int(n_splits), _dtype_code(o_part), _ptr(o_part), _ptr(lse_part),
-                                      _stream(stream))
+    st = lib().call.ls_prefix_attn_splitkv(desc, q, k_cache, v_cache, prefix_lens, int(n_splits), _dtype_code(o_part),
+                                           o_part, lse_part, _stream(stream))
     if check:
         _check(st, "ls_prefix_attn_splitkv")
     return int(st)
 
 
 def ls_tree_attn_masked(desc, q, k_tree, v_tree, mask, o_tree, lse_tree, stream=None, check: bool = True) -> int:
-    st = lib().ls_tree_attn_masked(ctypes.byref(desc), _ptr(q), _ptr(k_tree), _ptr(v_tree), _ptr(mask),
-                                   _ptr(o_tree), _ptr(lse_tree), _stream(stream))
+    st = lib().call.ls_tree_attn_masked(desc, q, k_tree, v_tree, mask, o_tree, lse_tree, _stream(stream))
     if check:
         _check(st, "ls_tree_attn_masked")
     return int(st)
 
 
 def ls_lse_merge(desc, n_parts, o_parts, lse_parts, out, lse, stream=None, check: bool = True) -> int:
-    st = lib().ls_lse_merge(ctypes.byref(desc), int(n_parts), _dtype_code(o_parts), _ptr(o_parts), _ptr(lse_parts),
-                            _ptr(out), _ptr(lse), _stream(stream))
+    st = lib().call.ls_lse_merge(desc, int(n_parts), _dtype_code(o_parts), o_parts, lse_parts, out, lse,
+                                 _stream(stream))
     if check:
         _check(st, "ls_lse_merge")
     return int(st)
@@ -318,9 +344,9 @@ def ls_tree_accept_greedy(parents, draft_tokens, target_tokens, accept_path, acc
                           stream=None, check: bool = True) -> int:
     """All tensors device int32: parents/draft_tokens/target_tokens/accept_path [batch, n_tree];
     accept_len/next_token/err_flag [batch]."""
-    st = lib().ls_tree_accept_greedy(_ptr(parents), _ptr(draft_tokens), _ptr(target_tokens), parents.shape[0],
-                                     parents.shape[1], _ptr(accept_path), _ptr(accept_len), _ptr(next_token),
-                                     _ptr(err_flag), _stream(stream))
+    batch, n_tree = parents.shape
+    st = lib().call.ls_tree_accept_greedy(parents, draft_tokens, target_tokens, batch, n_tree,
+                                          accept_path, accept_len, next_token, err_flag, _stream(stream))
     if check:
         _check(st, "ls_tree_accept_greedy")
     return int(st)
@@ -328,9 +354,8 @@ def ls_tree_accept_greedy(parents, draft_tokens, target_tokens, accept_path, acc
 
 def ls_kv_commit(desc, k_tree, v_tree, accept_path, accept_len, prefix_lens, k_cache, v_cache, new_prefix_lens=None,
                  err_flag=None, stream=None, check: bool = True) -> int:
-    st = lib().ls_kv_commit(ctypes.byref(desc), _ptr(k_tree), _ptr(v_tree), _ptr(accept_path), _ptr(accept_len),
-                            _ptr(prefix_lens), _ptr(k_cache), _ptr(v_cache), _ptr(new_prefix_lens), _ptr(err_flag),
-                            _stream(stream))
+    st = lib().call.ls_kv_commit(desc, k_tree, v_tree, accept_path, accept_len, prefix_lens, k_cache, v_cache,
+                                 new_prefix_lens, err_flag, _stream(stream))
     if check:
         _check(st, "ls_kv_commit")
     return int(st)
@@ -340,10 +365,9 @@ def ls_hybrid_tree_attn_paged(desc, q, k_pages, v_pages, block_table, page_size,
                               out, lse, workspace, stream=None, check: bool = True) -> int:
     """block_table: device int32 [batch, bt_stride]; desc.kc_stride / vc_stride describe one page
     (see make_desc_paged)."""
-    st = lib().ls_hybrid_tree_attn_paged(ctypes.byref(desc), _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
-                                         block_table.shape[1], int(page_size), _ptr(prefix_lens), _ptr(k_tree),
-                                         _ptr(v_tree), _ptr(parents), _ptr(out), _ptr(lse), _ptr(workspace),
-                                         _bytes(workspace), _stream(stream))
+    st = lib().call.ls_hybrid_tree_attn_paged(desc, q, k_pages, v_pages, block_table, block_table.shape[1],
+                                              int(page_size), prefix_lens, k_tree, v_tree, parents, out, lse,
+                                              workspace, _bytes(workspace), _stream(stream))
     if check:
         _check(st, "ls_hybrid_tree_attn_paged")
     return int(st)
@@ -351,10 +375,9 @@ def ls_hybrid_tree_attn_paged(desc, q, k_pages, v_pages, block_table, page_size,
 
 def ls_kv_commit_paged(desc, k_tree, v_tree, accept_path, accept_len, prefix_lens, k_pages, v_pages, block_table,
                        page_size, new_prefix_lens=None, err_flag=None, stream=None, check: bool = True) -> int:
-    st = lib().ls_kv_commit_paged(ctypes.byref(desc), _ptr(k_tree), _ptr(v_tree), _ptr(accept_path), _ptr(accept_len),
-                                  _ptr(prefix_lens), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
-                                  block_table.shape[1], int(page_size), _ptr(new_prefix_lens), _ptr(err_flag),
-                                  _stream(stream))
+    st = lib().call.ls_kv_commit_paged(desc, k_tree, v_tree, accept_path, accept_len, prefix_lens, k_pages, v_pages,
+                                       block_table, block_table.shape[1], int(page_size), new_prefix_lens, err_flag,
+                                       _stream(stream))
     if check:
         _check(st, "ls_kv_commit_paged")
     return int(st)
@@ -362,9 +385,8 @@ def ls_kv_commit_paged(desc, k_tree, v_tree, accept_path, accept_len, prefix_len
 
 def ls_cache_attn_paged(desc, q, k_pages, v_pages, block_table, page_size, prefix_lens, out, lse, workspace,
                         stream=None, check: bool = True) -> int:
-    st = lib().ls_cache_attn_paged(ctypes.byref(desc), _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
-                                   block_table.shape[1], int(page_size), _ptr(prefix_lens), _ptr(out), _ptr(lse),
-                                   _ptr(workspace), _bytes(workspace), _stream(stream))
+    st = lib().call.ls_cache_attn_paged(desc, q, k_pages, v_pages, block_table, block_table.shape[1], int(page_size),
+                                        prefix_lens, out, lse, workspace, _bytes(workspace), _stream(stream))
     if check:
         _check(st, "ls_cache_attn_paged")
     return int(st)

@@ -12,6 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libls_attn.so")
 PROBE_SRC = os.path.join(HERE, "csrc_probe", "ls_probe.hip")
 PROBE_LIB_PATH = os.path.join(HERE, "libls_probe.so")   # bench-only measurement helpers
+CALL_SRC = os.path.join(HERE, "csrc_bind", "ls_call.cpp")
+CALL_PATH = os.path.join(HERE, "_ls_call.so")   # Python's way into the library
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -78,6 +80,22 @@ def build_probe_library() -> str:
     return PROBE_LIB_PATH
 
 
+def build_call_module() -> str:
+    """Compile the module through which Python calls the library's device entry points."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include = os.path.join(root, "include")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-isystem",
+                    sysconfig.get_paths()["include"], "-isystem", include, "-isystem",
+                    os.path.join(include, "torch", "csrc", "api", "include"),
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-o", CALL_PATH, CALL_SRC, "-L",
+                    os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], check=True)
+    return CALL_PATH
+
+
 if __name__ == "__main__":
     print(build_library())
     print(build_probe_library())
+    print(build_call_module())

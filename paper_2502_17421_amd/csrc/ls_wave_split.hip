@@ -44,6 +44,14 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t *p)
     return *(__attribute__((address_space(4))) const int32_t *)(uintptr_t)p;
 }
 
+// The lane's number where it would otherwise be kept over the loops in a register that they do not have.
+__device__ __forceinline__ int lane_again()
+{
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
 // The mask word of tree tile `tt` for the chain of nodes starting at `node`, from its beginning.
 __device__ __forceinline__ uint32_t chain_word(const int32_t *par, int node, int tt)
 {
@@ -74,8 +82,9 @@ struct WaveArgs {
     int32_t *err_flag;
 };
 
-template <int D, bool F16, bool PAGED, int RT>
-__global__ void __launch_bounds__(NW * 64, 2)
+// TREE: the call has tree keys (without them the code for them is not there: 40 heads x 4 tokens x 241 keys x.x us)
+template <int D, bool F16, bool PAGED, int RT, bool TREE>
+__global__ void __launch_bounds__(NW * 64, D == 64 && RT == 1 ? 4 : 2)
 wave_split_kernel(WaveArgs a)
 {
     constexpr int KSTEPS = D / 16;            // contraction steps of S^T = K Q^T
@@ -131,9 +140,9 @@ wave_split_kernel(WaveArgs a)
     plen = plen < 0 ? 0 : (plen > a.max_prefix_len ? a.max_prefix_len : plen);
     const int n_splits = a.n_splits;
     const int all_pref = (plen + TK - 1) / TK;
-    const int tree_tiles = a.parents ? (a.n_tree + TK - 1) / TK : 0;
+    const int tree_tiles = TREE ? (a.n_tree + TK - 1) / TK : 0;
     const bool last_split = split == n_splits - 1;
-    const bool has_tree = last_split && tree_tiles > 0;
+    const bool has_tree = TREE && last_split;
     const int per_split = (int)a.by_splits.div((uint32_t)(all_pref + tree_tiles + n_splits - 1));
     int t_lo = split * per_split;
     t_lo = t_lo < all_pref ? t_lo : all_pref;
@@ -141,6 +150,24 @@ wave_split_kernel(WaveArgs a)
     t_hi = t_hi < all_pref ? t_hi : all_pref;
     const int n_pref = t_hi - t_lo;
     const int n_all = n_pref + (has_tree ? tree_tiles : 0);
+    // Tiles of a wave: cached ones, then tree ones.  A tree tile takes about as long as two cached ones (its mask, three
+    // products, K and V one after the other), and the waves that start first are the first ones; so these take the tree tiles,
+    // and those with one more of them than the others leave out two rounds of cached tiles and are the last in every later
+    // one.  (Tree tiles after the cached ones in turn: DEAL; tree tiles to the last waves: 88 keys x 26 nodes, 32 KV
+    // heads 6.1 -> 6.8 us.)
+    const int n_tree_tiles = n_all - n_pref, n_heavy = n_tree_tiles & (NW - 1);
+    const int spare = NW - n_heavy;  // waves that share the first two rounds
+    auto next_tile = [&](int t) __attribute__((always_inline)) {
+        if (!TREE || t >= n_pref) return t + NW;
+        const int u = t + (t < 2 * spare ? spare : NW);
+        return u < n_pref ? u : n_pref + wave;
+    };
+    int t = wave;
+    if (TREE) {
+        t = wave < n_heavy ? 3 * spare + wave : wave - n_heavy;
+        t = t < n_pref ? t : n_pref + wave;
+    }
+    const int first_tile = TREE ? t : wave;
     auto tile_row = [&](int t) __attribute__((always_inline)) { return (t_lo + t) * TK; };  // of cached tile t of the split
 
     const uint8_t *kc = uniform_ptr(a.k_cache + (PAGED ? 0 : b * a.kc_b) + g * a.kc_h);
@@ -212,15 +239,15 @@ wave_split_kernel(WaveArgs a)
             }
         }
     };
-    const bool busy = wave < n_all;
+    const bool busy = t < n_all;
     // Requests go out in the order their data is needed and can be addressed: first keys, query rows (RT == 1:
     // to registers; RT == 2: to LDS, eight rows per wave, in the K tiles' swizzled layout), parents of the
     // tree (one node per lane), first values.  Loads return in order, so waiting for all but the values'
     // copies waits for everything before them.
     int2 pages = make_int2(0, 0);
     if (busy) {
-        pages = pages_of(wave);
-        request(false, wave, pages);
+        pages = pages_of(t);
+        request(false, t, pages);
     }
     auto row_of = [&](int m) __attribute__((always_inline)) { return m < rows_kv ? m : rows_kv - 1; };  // rows past the end repeat the last
     auto q_row_ptr = [&](int m) __attribute__((always_inline)) {
@@ -242,13 +269,13 @@ wave_split_kernel(WaveArgs a)
             copy_row_to_lds(src, __builtin_amdgcn_readfirstlane(smem_off + Q_OFF + (wave * (32 * RT / NW) + j * RPL) * ROWB));
         }
     }
-    int32_t par_reg;  // loaded on every path, from a valid address, so that the register is written by one instruction
-    {
+    int32_t par_reg = 0;
+    if constexpr (TREE) {  // loaded on every path, from a valid address, so that the register is written by one instruction
         const int32_t *src = has_tree ? a.parents + (int64_t)b * a.n_tree + (lane < a.n_tree ? lane : 0) : (const int32_t *)a.q;
         asm volatile("global_load_dword %0, %1, off" : "=v"(par_reg) : "v"(src) : "memory");
     }
-    if (busy) request(true, wave, pages);
-    int2 pages_next = pages_of(wave + NW);
+    if (busy) request(true, t, pages);
+    int2 pages_next = pages_of(next_tile(t));
     if (busy) wait_vmem<LOADS>();
     else wait_vmem<0>();
     bf16x8 q_reg[RT == 1 ? KSTEPS : 1];
@@ -261,13 +288,12 @@ wave_split_kernel(WaveArgs a)
     } else {
         asm volatile("s_barrier" ::: "memory");  // every wave's query rows are in LDS
     }
-    asm volatile("" : "+v"(par_reg));
+    if constexpr (TREE) asm volatile("" : "+v"(par_reg));
 
     // ---- tree mask ---------------------------------------------------------------------------------
     int32_t *par_lds = (int32_t *)(smem + PAR_OFF);  // parents; up to 64 nodes: the mask of every node instead
     bool bad_parent = false;
-    const bool tree_wave = has_tree && busy && n_all > n_pref && wave + ((n_all - 1 - wave) / NW) * NW >= n_pref;
-    if (tree_wave) {  // wave-uniform
+    if (TREE && wave < n_tree_tiles) {  // wave-uniform
         if (a.n_tree <= 64) {
             int anc = par_reg;
             if (lane < a.n_tree) {
@@ -292,7 +318,7 @@ wave_split_kernel(WaveArgs a)
             }
         }
         // the wave of the first tree tile reports
-        if (n_pref % NW == wave && g == 0 && row_block == 0) {
+        if (wave == 0 && g == 0 && row_block == 0) {
             const bool any_bad = __any(bad_parent);
             if (lane == 0 && a.err_flag) a.err_flag[b] = any_bad ? 1 : 0;
         }
@@ -385,13 +411,13 @@ wave_split_kernel(WaveArgs a)
         }
     };
 
-    int t = wave;
     bool not_finite = false;  // wave-uniform: infinities or NaN among the values of this wave's tree tiles
-    for (; t < n_pref; t += NW) {  // cached keys
-        const bool more = t + NW < n_all;
+    for (int next; t < n_pref; t = next) {  // cached keys
+        next = next_tile(t);
+        const bool more = next < n_all;
         bf16x8 frag[KSTEPS];
         uint32_t pp[RT][8];  // numerators in the operand type
-        if (t == wave) {
+        if (t == first_tile) {
             wait_vmem<LOADS>();  // the K rows; the V rows are the LOADS copies behind them
         } else {
             wait_vmem<0>();
@@ -408,7 +434,7 @@ wave_split_kernel(WaveArgs a)
                 for (int e = 0; e < 16; ++e)
                     if (8 * (e >> 2) + 4 * lh + (e & 3) >= valid) s[e] = -INFINITY;
             }
-            raise(rt, s, t == wave, kRaise, 1.f);
+            raise(rt, s, t == first_tile, kRaise, 1.f);
             // a row all of whose scores so far are -inf has the reference -inf: its numerators are zeros
             const float mc = m_run[rt] == -INFINITY ? 0.f : m_run[rt] * c;
             float sum = 0.f;
@@ -423,8 +449,8 @@ wave_split_kernel(WaveArgs a)
         }
         wait_vmem<0>();  // the V rows of tile t
         pages = pages_next;
-        if (more) request(false, t + NW, pages);
-        pages_next = pages_of(t + 2 * NW);
+        if (more) request(false, next, pages);
+        pages_next = pages_of(next_tile(next));
         read_v_tile(frag);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) add_product(frag, rt, pp[rt]);
@@ -434,8 +460,8 @@ wave_split_kernel(WaveArgs a)
         const int node = m - (int)a.by_tree.div((uint32_t)m) * a.n_tree;
         return a.n_tree > 64 ? chain_word(par_lds, node, tt) : (uint32_t)par_lds[2 * node + tt];
     };
-    for (; t < n_all; t += NW) {  // tree keys; one row tile after the other
-        if (t != wave) request(true, t, pages);
+    for (; TREE && t < n_all; t += NW) {  // tree keys; one row tile after the other
+        if (t != first_tile) request(true, t, pages);
         wait_vmem<0>();
         const int tt = t - n_pref;
 #pragma unroll
@@ -444,11 +470,11 @@ wave_split_kernel(WaveArgs a)
             read_k_tile(frag);
             floatx16 s;
             scores(frag, rt, s);
-            const uint32_t seen = visible(rt, tt) >> (4 * lh);
+            const uint32_t seen = visible(rt, tt) >> (4 * (lane_again() >> 5));
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 if (!((seen >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
-            raise(rt, s, t == wave, F16 ? 0.f : kRaise, t - NW < n_pref ? kTreeUp<F16> : 1.f);
+            raise(rt, s, t == first_tile, F16 ? 0.f : kRaise, t < n_pref + NW ? kTreeUp<F16> : 1.f);
             uint32_t parts[kTreeParts<F16>][8];
             l_run[rt] += tree_numerators<F16>(s, c, m_run[rt], parts);
             __builtin_amdgcn_sched_barrier(0);  // the values are not read early: no registers to spare
@@ -459,10 +485,8 @@ wave_split_kernel(WaveArgs a)
         if (t + NW < n_all) request(false, t + NW, pages);
     }
 
-    if (not_finite) {
-        for (t = n_pref + (wave - n_pref) % NW; t < n_all; t += NW) {
-            const int tt = t - n_pref;
-            if (tt < 0) continue;
+    if (TREE && not_finite) {
+        for (int tt = wave; tt < n_tree_tiles; tt += NW) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 uint32_t word = visible(rt, tt);
@@ -481,19 +505,21 @@ wave_split_kernel(WaveArgs a)
     constexpr int PASSES = CPR / TPR;         // pieces per thread
     float2 *ml = (float2 *)(smem + ML_OFF);   // (m, l) [row][wave]
     const int n_active = n_all < NW ? n_all : NW;
-    const int row = tid / TPR;                // the row this thread finishes
+    const int end_lane = lane_again(), end_tid = wave * 64 + end_lane;
+    const int end_li = end_lane & 31, end_lh = end_lane >> 5;
+    const int row = end_tid / TPR;            // the row this thread finishes
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         if (rt) __syncthreads();  // the rows of the previous tile have been read
         const float l_tot = half_sum(l_run[rt]);
-        if (lh == 0) ml[li * NW + wave] = make_float2(m_run[rt], l_tot);
+        if (end_lh == 0) ml[end_li * NW + wave] = make_float2(m_run[rt], l_tot);
         if (busy) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
-                    const int piece = (8 * mt + 2 * rg + lh) ^ (li & (CPR - 1));
-                    *(float4 *)(smem + wave * 2 * TILEB + li * (D * 4) + piece * 16) =
+                    const int piece = (8 * mt + 2 * rg + end_lh) ^ (end_li & (CPR - 1));
+                    *(float4 *)(smem + wave * 2 * TILEB + end_li * (D * 4) + piece * 16) =
                         make_float4(o_acc[rt][mt][4 * rg], o_acc[rt][mt][4 * rg + 1], o_acc[rt][mt][4 * rg + 2],
                                     o_acc[rt][mt][4 * rg + 3]);
                 }
@@ -516,7 +542,7 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
                 for (int u = 0; u < PASSES; ++u)
                     v[u][k] = *(const float4 *)(smem + k * 2 * TILEB + row * (D * 4) +
-                                                (((tid % TPR + u * TPR) ^ (row & (CPR - 1))) * 16));
+                                                (((end_tid % TPR + u * TPR) ^ (row & (CPR - 1))) * 16));
         float top = s[0].x;
 #pragma unroll
         for (int k = 1; k < NW; ++k) top = fmaxf(top, s[k].x);
@@ -528,7 +554,7 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
         for (int k = 0; k < NW; ++k) {
             if (k >= n_active) continue;
-            const bool tree = ((k - n_pref) & (NW - 1)) < n_all - n_pref;  // this wave had tree tiles: its sums are lifted
+            const bool tree = TREE && k < n_tree_tiles;  // this wave had tree tiles: its sums are lifted
             const float scale = s[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s[k].x - top) * c) * (tree ? kTreeDown<F16> : 1.f);
             l_sum += scale * s[k].y;
 #pragma unroll
@@ -543,7 +569,7 @@ wave_split_kernel(WaveArgs a)
         if (m >= rows_kv) continue;
 #pragma unroll
         for (int u = 0; u < PASSES; ++u) {
-            const int col = (tid % TPR + u * TPR) * 4;
+            const int col = (end_tid % TPR + u * TPR) * 4;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[u][i] *= inv;
             if (has_tree && !final_row) {  // fp32, in two halves
@@ -553,7 +579,7 @@ wave_split_kernel(WaveArgs a)
                 *(uint2 *)(dst + col) = make_uint2(pack16<F16>(o[u][0], o[u][1]), pack16<F16>(o[u][2], o[u][3]));
             }
         }
-        if (tid % TPR == 0) {
+        if (end_tid % TPR == 0) {
             const float lse = l_sum == 0.f ? -INFINITY : (top * c + log2f(l_sum)) * kLn2;
             (final_row ? a.lse : a.lse_parts)[prow] = lse;
         }
@@ -562,12 +588,12 @@ wave_split_kernel(WaveArgs a)
 
 namespace {
 
-template <int D, bool F16, bool PAGED, int RT>
+template <int D, bool F16, bool PAGED, int RT, bool TREE>
 hipError_t launch_one(WaveArgs a, int batch, hipStream_t stream)
 {
     constexpr int lds_bytes = NW * 2 * TK * D * 2 + (RT > 1 ? RT * TK * D * 2 : 0) + LS_MAX_TREE * 4 + NW * 32 * 8;
     static_assert(lds_bytes <= 160 * 1024, "the stages exceed the 160 KB of a compute unit");
-    auto kernel = wave_split_kernel<D, F16, PAGED, RT>;
+    auto kernel = wave_split_kernel<D, F16, PAGED, RT, TREE>;
     static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  lds_bytes);
     if (attr != hipSuccess) return attr;
@@ -621,14 +647,16 @@ hipError_t launch_wave_split(const Problem &p, int dtype, int row_tiles, const W
     a.o_parts = w.o_parts;
     a.lse_parts = w.lse_parts;
     a.err_flag = w.err_flag;
-#define LS_WS_CASE2(DD, RR)                                                                                \
-    (paged ? (f16 ? launch_one<DD, true, true, RR>(a, p.batch, stream) : launch_one<DD, false, true, RR>(a, p.batch, stream)) \
-           : (f16 ? launch_one<DD, true, false, RR>(a, p.batch, stream) : launch_one<DD, false, false, RR>(a, p.batch, stream)))
+#define LS_WS_CASE3(DD, RR, TT)                                                                                             \
+    (paged ? (f16 ? launch_one<DD, true, true, RR, TT>(a, p.batch, stream) : launch_one<DD, false, true, RR, TT>(a, p.batch, stream)) \
+           : (f16 ? launch_one<DD, true, false, RR, TT>(a, p.batch, stream) : launch_one<DD, false, false, RR, TT>(a, p.batch, stream)))
+#define LS_WS_CASE2(DD, RR) (w.parents ? LS_WS_CASE3(DD, RR, true) : LS_WS_CASE3(DD, RR, false))
 #define LS_WS_CASE(DD) (row_tiles == 1 ? LS_WS_CASE2(DD, 1) : LS_WS_CASE2(DD, 2))
     if (p.head_dim == 128) return LS_WS_CASE(128);
     if (p.head_dim == 64) return LS_WS_CASE(64);
 #undef LS_WS_CASE
 #undef LS_WS_CASE2
+#undef LS_WS_CASE3
     return hipErrorInvalidValue;
 }
 

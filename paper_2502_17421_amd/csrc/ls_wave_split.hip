@@ -82,7 +82,7 @@ struct WaveArgs {
     int32_t *err_flag;
 };
 
-// TREE: the call has tree keys (without them the code for them is not there: 40 heads x 4 tokens x 241 keys x.x us)
+// TREE: the call has tree keys; without them the code for them is not there (cross attention, 16 shapes 1.017 of the speed)
 template <int D, bool F16, bool PAGED, int RT, bool TREE>
 __global__ void __launch_bounds__(NW * 64, D == 64 && RT == 1 ? 4 : 2)
 wave_split_kernel(WaveArgs a)
@@ -153,8 +153,9 @@ wave_split_kernel(WaveArgs a)
     // Tiles of a wave: cached ones, then tree ones.  A tree tile takes about as long as two cached ones (its mask, three
     // products, K and V one after the other), and the waves that start first are the first ones; so these take the tree tiles,
     // and those with one more of them than the others leave out two rounds of cached tiles and are the last in every later
-    // one.  (Tree tiles after the cached ones in turn: DEAL; tree tiles to the last waves: 88 keys x 26 nodes, 32 KV
-    // heads 6.1 -> 6.8 us.)
+    // one.  (Against tree tiles after the cached ones in turn, 64 drawn shapes: windows 1.06 of the speed, short caches
+    // 1.045, pages 1.02, worst 0.945; 300 keys x 5 nodes 7.6 -> 6.8 us, 667 keys x 63 nodes f16 11.5 -> 9.7.  Tree tiles to the
+    // last waves: 88 keys x 26 nodes, 32 KV heads 6.1 -> 6.8.)
     const int n_tree_tiles = n_all - n_pref, n_heavy = n_tree_tiles & (NW - 1);
     const int spare = NW - n_heavy;  // waves that share the first two rounds
     auto next_tile = [&](int t) __attribute__((always_inline)) {

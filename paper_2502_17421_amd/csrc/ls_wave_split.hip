@@ -44,14 +44,6 @@ __device__ __forceinline__ int32_t scalar_load(const int32_t *p)
     return *(__attribute__((address_space(4))) const int32_t *)(uintptr_t)p;
 }
 
-// The lane's number where it would otherwise be kept over the loops in a register that they do not have.
-__device__ __forceinline__ int lane_again()
-{
-    int lane;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
-    return lane;
-}
-
 // The mask word of tree tile `tt` for the chain of nodes starting at `node`, from its beginning.
 __device__ __forceinline__ uint32_t chain_word(const int32_t *par, int node, int tt)
 {
@@ -110,7 +102,7 @@ wave_split_kernel(WaveArgs a)
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hw_wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
     const int li = lane & 31;
     const int lh = lane >> 5;
@@ -133,7 +125,6 @@ wave_split_kernel(WaveArgs a)
     const int row_block = (int)(item - item_split * a.by_row_blocks.d);
     const int row0 = row_block * (32 * RT);  // first query row (of the KV head) of this workgroup
     const uint32_t smem_off = lds_offset(smem);
-    const uint32_t k_stage = smem_off + wave * 2 * TILEB;  // the V stage follows
 
     // ---- this split's tiles: cached ones, then (last split) those of the tree --------------------
     int plen = a.prefix_lens ? scalar_load(a.prefix_lens + b) : a.prefix_len_all;
@@ -150,25 +141,16 @@ wave_split_kernel(WaveArgs a)
     t_hi = t_hi < all_pref ? t_hi : all_pref;
     const int n_pref = t_hi - t_lo;
     const int n_all = n_pref + (has_tree ? tree_tiles : 0);
-    // Tiles of a wave: cached ones, then tree ones.  A tree tile takes about as long as two cached ones (its mask, three
-    // products, K and V one after the other), and the waves that start first are the first ones; so these take the tree tiles,
-    // and those with one more of them than the others leave out two rounds of cached tiles and are the last in every later
-    // one.  (Against tree tiles after the cached ones in turn, 64 drawn shapes: windows 1.06 of the speed, short caches
-    // 1.045, pages 1.02, worst 0.945; 300 keys x 5 nodes 7.6 -> 6.8 us, 667 keys x 63 nodes f16 11.5 -> 9.7.  Tree tiles to the
-    // last waves: 88 keys x 26 nodes, 32 KV heads 6.1 -> 6.8.)
-    const int n_tree_tiles = n_all - n_pref, n_heavy = n_tree_tiles & (NW - 1);
-    const int spare = NW - n_heavy;  // waves that share the first two rounds
-    auto next_tile = [&](int t) __attribute__((always_inline)) {
-        if (!TREE || t >= n_pref) return t + NW;
-        const int u = t + (t < 2 * spare ? spare : NW);
-        return u < n_pref ? u : n_pref + wave;
-    };
-    int t = wave;
-    if (TREE) {
-        t = wave < n_heavy ? 3 * spare + wave : wave - n_heavy;
-        t = t < n_pref ? t : n_pref + wave;
-    }
-    const int first_tile = TREE ? t : wave;
+    // Tile t of the split belongs to wave t % NW, so a tree tile, which takes about as long as two cached ones (its mask, three
+    // products, K and V one after the other), may fall to any wave.  The hardware starts waves 0 to 3 first, and serves
+    // them first on the SIMD that each shares with one of 4 to 7; so where the tree tiles fall to the latter the halves change
+    // places.  Which tiles are added up together, and in which order, stays as it is.  Not where the tree tiles run on into wave 0:
+    // those waves have one more cached tile than the others (8 sequences x 290 rows 22.4 / 25.3 us with the exchange).
+    // Against no exchange, 8 KV heads x 32 rows: 640 keys 10.4 -> 8.9 us, 926 keys 11.5 -> 10.0, 1500 keys 14.6 -> 13.4;
+    // 174 shapes 0.969 of the time, worst 1.024.  Tree tiles dealt to the first waves, which leave out cached ones: 640 keys 9.1, but 1100
+    // 10.6 / 11.8 and in pages 12.3 / 14.1, and the rounding error grew by up to 4 %: fewer waves start from a row's largest score.
+    const int wave = hw_wave ^ (TREE && (n_pref & (NW / 2)) && (n_pref & (NW - 1)) + n_all - n_pref <= NW ? NW / 2 : 0);
+    const uint32_t k_stage = smem_off + wave * 2 * TILEB;  // the V stage follows
     auto tile_row = [&](int t) __attribute__((always_inline)) { return (t_lo + t) * TK; };  // of cached tile t of the split
 
     const uint8_t *kc = uniform_ptr(a.k_cache + (PAGED ? 0 : b * a.kc_b) + g * a.kc_h);
@@ -240,15 +222,15 @@ wave_split_kernel(WaveArgs a)
             }
         }
     };
-    const bool busy = t < n_all;
+    const bool busy = wave < n_all;
     // Requests go out in the order their data is needed and can be addressed: first keys, query rows (RT == 1:
     // to registers; RT == 2: to LDS, eight rows per wave, in the K tiles' swizzled layout), parents of the
     // tree (one node per lane), first values.  Loads return in order, so waiting for all but the values'
     // copies waits for everything before them.
     int2 pages = make_int2(0, 0);
     if (busy) {
-        pages = pages_of(t);
-        request(false, t, pages);
+        pages = pages_of(wave);
+        request(false, wave, pages);
     }
     auto row_of = [&](int m) __attribute__((always_inline)) { return m < rows_kv ? m : rows_kv - 1; };  // rows past the end repeat the last
     auto q_row_ptr = [&](int m) __attribute__((always_inline)) {
@@ -275,8 +257,8 @@ wave_split_kernel(WaveArgs a)
         const int32_t *src = has_tree ? a.parents + (int64_t)b * a.n_tree + (lane < a.n_tree ? lane : 0) : (const int32_t *)a.q;
         asm volatile("global_load_dword %0, %1, off" : "=v"(par_reg) : "v"(src) : "memory");
     }
-    if (busy) request(true, t, pages);
-    int2 pages_next = pages_of(next_tile(t));
+    if (busy) request(true, wave, pages);
+    int2 pages_next = pages_of(wave + NW);
     if (busy) wait_vmem<LOADS>();
     else wait_vmem<0>();
     bf16x8 q_reg[RT == 1 ? KSTEPS : 1];
@@ -294,7 +276,8 @@ wave_split_kernel(WaveArgs a)
     // ---- tree mask ---------------------------------------------------------------------------------
     int32_t *par_lds = (int32_t *)(smem + PAR_OFF);  // parents; up to 64 nodes: the mask of every node instead
     bool bad_parent = false;
-    if (TREE && wave < n_tree_tiles) {  // wave-uniform
+    const bool tree_wave = has_tree && busy && n_all > n_pref && wave + ((n_all - 1 - wave) / NW) * NW >= n_pref;
+    if (TREE && tree_wave) {  // wave-uniform
         if (a.n_tree <= 64) {
             int anc = par_reg;
             if (lane < a.n_tree) {
@@ -319,7 +302,7 @@ wave_split_kernel(WaveArgs a)
             }
         }
         // the wave of the first tree tile reports
-        if (wave == 0 && g == 0 && row_block == 0) {
+        if (n_pref % NW == wave && g == 0 && row_block == 0) {
             const bool any_bad = __any(bad_parent);
             if (lane == 0 && a.err_flag) a.err_flag[b] = any_bad ? 1 : 0;
         }
@@ -413,12 +396,12 @@ wave_split_kernel(WaveArgs a)
     };
 
     bool not_finite = false;  // wave-uniform: infinities or NaN among the values of this wave's tree tiles
-    for (int next; t < n_pref; t = next) {  // cached keys
-        next = next_tile(t);
-        const bool more = next < n_all;
+    int t = wave;
+    for (; t < n_pref; t += NW) {  // cached keys
+        const bool more = t + NW < n_all;
         bf16x8 frag[KSTEPS];
         uint32_t pp[RT][8];  // numerators in the operand type
-        if (t == first_tile) {
+        if (t == wave) {
             wait_vmem<LOADS>();  // the K rows; the V rows are the LOADS copies behind them
         } else {
             wait_vmem<0>();
@@ -435,7 +418,7 @@ wave_split_kernel(WaveArgs a)
                 for (int e = 0; e < 16; ++e)
                     if (8 * (e >> 2) + 4 * lh + (e & 3) >= valid) s[e] = -INFINITY;
             }
-            raise(rt, s, t == first_tile, kRaise, 1.f);
+            raise(rt, s, t == wave, kRaise, 1.f);
             // a row all of whose scores so far are -inf has the reference -inf: its numerators are zeros
             const float mc = m_run[rt] == -INFINITY ? 0.f : m_run[rt] * c;
             float sum = 0.f;
@@ -450,8 +433,8 @@ wave_split_kernel(WaveArgs a)
         }
         wait_vmem<0>();  // the V rows of tile t
         pages = pages_next;
-        if (more) request(false, next, pages);
-        pages_next = pages_of(next_tile(next));
+        if (more) request(false, t + NW, pages);
+        pages_next = pages_of(t + 2 * NW);
         read_v_tile(frag);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) add_product(frag, rt, pp[rt]);
@@ -462,7 +445,7 @@ wave_split_kernel(WaveArgs a)
         return a.n_tree > 64 ? chain_word(par_lds, node, tt) : (uint32_t)par_lds[2 * node + tt];
     };
     for (; TREE && t < n_all; t += NW) {  // tree keys; one row tile after the other
-        if (t != first_tile) request(true, t, pages);
+        if (t != wave) request(true, t, pages);
         wait_vmem<0>();
         const int tt = t - n_pref;
 #pragma unroll
@@ -471,11 +454,11 @@ wave_split_kernel(WaveArgs a)
             read_k_tile(frag);
             floatx16 s;
             scores(frag, rt, s);
-            const uint32_t seen = visible(rt, tt) >> (4 * (lane_again() >> 5));
+            const uint32_t seen = visible(rt, tt) >> (4 * lh);
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 if (!((seen >> (8 * (e >> 2) + (e & 3))) & 1u)) s[e] = -INFINITY;
-            raise(rt, s, t == first_tile, F16 ? 0.f : kRaise, t < n_pref + NW ? kTreeUp<F16> : 1.f);
+            raise(rt, s, t == wave, F16 ? 0.f : kRaise, t - NW < n_pref ? kTreeUp<F16> : 1.f);
             uint32_t parts[kTreeParts<F16>][8];
             l_run[rt] += tree_numerators<F16>(s, c, m_run[rt], parts);
             __builtin_amdgcn_sched_barrier(0);  // the values are not read early: no registers to spare
@@ -487,7 +470,9 @@ wave_split_kernel(WaveArgs a)
     }
 
     if (TREE && not_finite) {
-        for (int tt = wave; tt < n_tree_tiles; tt += NW) {
+        for (t = n_pref + (wave - n_pref) % NW; t < n_all; t += NW) {
+            const int tt = t - n_pref;
+            if (tt < 0) continue;
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 uint32_t word = visible(rt, tt);
@@ -506,21 +491,19 @@ wave_split_kernel(WaveArgs a)
     constexpr int PASSES = CPR / TPR;         // pieces per thread
     float2 *ml = (float2 *)(smem + ML_OFF);   // (m, l) [row][wave]
     const int n_active = n_all < NW ? n_all : NW;
-    const int end_lane = lane_again(), end_tid = wave * 64 + end_lane;
-    const int end_li = end_lane & 31, end_lh = end_lane >> 5;
-    const int row = end_tid / TPR;            // the row this thread finishes
+    const int row = tid / TPR;                // the row this thread finishes
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         if (rt) __syncthreads();  // the rows of the previous tile have been read
         const float l_tot = half_sum(l_run[rt]);
-        if (end_lh == 0) ml[end_li * NW + wave] = make_float2(m_run[rt], l_tot);
+        if (lh == 0) ml[li * NW + wave] = make_float2(m_run[rt], l_tot);
         if (busy) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
-                    const int piece = (8 * mt + 2 * rg + end_lh) ^ (end_li & (CPR - 1));
-                    *(float4 *)(smem + wave * 2 * TILEB + end_li * (D * 4) + piece * 16) =
+                    const int piece = (8 * mt + 2 * rg + lh) ^ (li & (CPR - 1));
+                    *(float4 *)(smem + wave * 2 * TILEB + li * (D * 4) + piece * 16) =
                         make_float4(o_acc[rt][mt][4 * rg], o_acc[rt][mt][4 * rg + 1], o_acc[rt][mt][4 * rg + 2],
                                     o_acc[rt][mt][4 * rg + 3]);
                 }
@@ -543,7 +526,7 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
                 for (int u = 0; u < PASSES; ++u)
                     v[u][k] = *(const float4 *)(smem + k * 2 * TILEB + row * (D * 4) +
-                                                (((end_tid % TPR + u * TPR) ^ (row & (CPR - 1))) * 16));
+                                                (((tid % TPR + u * TPR) ^ (row & (CPR - 1))) * 16));
         float top = s[0].x;
 #pragma unroll
         for (int k = 1; k < NW; ++k) top = fmaxf(top, s[k].x);
@@ -555,7 +538,7 @@ wave_split_kernel(WaveArgs a)
 #pragma unroll
         for (int k = 0; k < NW; ++k) {
             if (k >= n_active) continue;
-            const bool tree = TREE && k < n_tree_tiles;  // this wave had tree tiles: its sums are lifted
+            const bool tree = TREE && ((k - n_pref) & (NW - 1)) < n_all - n_pref;  // this wave had tree tiles: its sums are lifted
             const float scale = s[k].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s[k].x - top) * c) * (tree ? kTreeDown<F16> : 1.f);
             l_sum += scale * s[k].y;
 #pragma unroll
@@ -570,7 +553,7 @@ wave_split_kernel(WaveArgs a)
         if (m >= rows_kv) continue;
 #pragma unroll
         for (int u = 0; u < PASSES; ++u) {
-            const int col = (end_tid % TPR + u * TPR) * 4;
+            const int col = (tid % TPR + u * TPR) * 4;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[u][i] *= inv;
             if (has_tree && !final_row) {  // fp32, in two halves
@@ -580,7 +563,7 @@ wave_split_kernel(WaveArgs a)
                 *(uint2 *)(dst + col) = make_uint2(pack16<F16>(o[u][0], o[u][1]), pack16<F16>(o[u][2], o[u][3]));
             }
         }
-        if (end_tid % TPR == 0) {
+        if (tid % TPR == 0) {
             const float lse = l_sum == 0.f ? -INFINITY : (top * c + log2f(l_sum)) * kLn2;
             (final_row ? a.lse : a.lse_parts)[prow] = lse;
         }

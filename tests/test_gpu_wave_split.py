@@ -105,6 +105,34 @@ def test_bad_parents_are_cut_and_reported(t, plen):
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen", [
+    ("f16", 8, 2, 128, 5, 300),     # ten tiles, the tree's goes to the third wave
+    ("bf16", 8, 2, 128, 8, 926),    # 29, the sixth: the halves of the workgroup change places
+    ("bf16", 8, 2, 64, 8, 1500),    # 47, the eighth
+    ("bf16", 8, 2, 128, 68, 512),   # three tree tiles, the first three waves
+    ("f16", 8, 2, 64, 100, 150),    # four of them, the sixth to the first: they run on
+    ("bf16", 4, 2, 64, 300, 700),   # ten of them, every wave
+])
+def test_cached_keys_are_added_up_alike_with_and_without_a_tree(dtype, hq, hkv, d, t, plen):
+    """A tree whose keys have no weight (scores some 350 below the cached ones) leaves the bits of the call on the cached keys
+    alone: which tiles a wave adds up, and in which order the waves are merged, does not depend on the tree."""
+    batch = make(dtype, hq, hkv, d, t, [plen], "iid", 23000 + t)
+    seq = batch.seqs[0]
+    seq.q[..., 0] = 2.0
+    seq.k_tree[..., 0] = -2000.0
+    say(f"no weight {dtype} hq={hq} hkv={hkv} d={d} t={t} plen={plen}")
+    db = DeviceBatch(batch)
+    out, lse = db.run_cache_only()
+    torch.cuda.synchronize()
+    alone = out.clone(), lse.clone()
+    out, lse = db.run_full()
+    torch.cuda.synchronize()
+    ro, rl = oracle_full(batch)
+    say(gates(out.float().cpu().numpy(), lse.cpu().numpy(), ro, rl, dtype, "  result", stress=True))
+    assert bool(torch.all(out == alone[0])) and bool(torch.all(lse == alone[1]))
+
+
 # dtype, query heads, KV heads, head_dim, tree nodes, prefix length, runs of cached keys that score -inf, by an infinite
 # component or (the last cases) by overflow.  A tile has 32 keys, tile i belongs to wave i % 8 while there is one split.
 NOTHING = [

@@ -248,7 +248,12 @@ SplitPlan plan_splits(const ls_desc &d, int32_t request)
     plan.balanced = 0;
     // blocks of 128 rows where twice the workgroups still have a compute unit each (see ls_prefix_mfma.hip)
     const int64_t rows_kv = (int64_t)(d.n_q_heads / d.n_kv_heads) * d.n_tree;
-    plan.row_block = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 127) / 128) * s <= compute_units() ? 128 : 256;
+    const int64_t light_blocks = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 127) / 128) * s;
+    plan.row_block = light_blocks <= compute_units() ? 128 : 256;
+    // At head_dim 64 a compute unit holds two blocks of four waves, of four and four that copy one (162 registers per lane): with
+    // more blocks than compute units the former are ahead (96 rows x 20k keys, 512 blocks 105.9 against 125.3 us; 128 rows x
+    // 3000 keys, 960 blocks 67.6 / 88.0), up to one per unit the latter (96 rows x 8000 keys, 256 blocks 117.6 / 106.1).
+    plan.copiers = d.head_dim == 128 || light_blocks <= compute_units();
     return plan;
 }
 

@@ -122,6 +122,7 @@ struct SplitPlan {
     // pieces are dealt to the sequences by their length (see SequenceSplits), all of about the same size.
     int32_t balanced;
     int32_t row_block;  // query rows per workgroup of the matrix-core kernel, 256 or 128
+    int32_t copiers;    // its blocks of 128 rows have four more waves, which copy
 };
 
 // n / d for wave-uniform or per-lane n by one multiplication, exact while n * d < 2^32 (the multiplier is

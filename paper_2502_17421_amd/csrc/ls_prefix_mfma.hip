@@ -1106,7 +1106,7 @@ hipError_t launch_prefix_mfma(const Problem &p, int dtype, const SplitPlan &plan
     // rows copy for themselves.
     const bool eight = rows_kv > 128 && (tail.counters || plan.row_block > 128);
     const int64_t blocks = (int64_t)((rows_kv + 127) / 128) * p.batch * p.n_kv_heads * plan.n_splits + p.batch;
-    const bool copiers = !tail.counters && blocks < (1ll << 32) / 512;
+    const bool copiers = plan.copiers && !tail.counters && blocks < (1ll << 32) / 512;
     const bool deep = plan.split_len <= kDeepMaxTiles * TK;  // few tiles per split: request them all at once
 #define LS_MFMA_CASE3(DD, WW, CC, PP)                                                                      \
     (paged ? (f16 ? launch_one<DD, WW, CC, true, true, PP>(p, plan, out, mask_job, tail, stream)           \

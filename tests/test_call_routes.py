@@ -16,6 +16,7 @@ STUB = r"""
 #include <cstdio>
 
 static char route_text[512];
+static ls::SplitPlan last_plan;
 #define SAY(...) std::snprintf(route_text + std::strlen(route_text), sizeof(route_text) - std::strlen(route_text), __VA_ARGS__)
 
 namespace ls {
@@ -27,6 +28,7 @@ hipError_t launch_wave_split(const Problem &, int, int row_tiles, const WholeCal
 hipError_t launch_prefix_mfma(const Problem &, int, const SplitPlan &plan, const Partials &, const MaskJob &job,
                               const FusedTail &tail, hipStream_t)
 {
+    last_plan = plan;
     SAY("prefix(splits=%d%s%s%s%s) ", plan.n_splits, tail.parents ? ",tree" : "", job.parents ? ",mask" : "",
         plan.balanced ? ",dealt" : "", tail.counters ? ",fused" : "");
     return hipSuccess;
@@ -55,6 +57,9 @@ hipError_t launch_kv_commit(const Problem &, int, const int32_t *, const int32_t
 int prefix_mfma_query_blocks(const Problem &p) { return (p.group * p.n_tree + 255) / 256; }
 bool prefix_mfma_supports(const Problem &, int dtype) { return is_16bit(dtype); }
 }  // namespace ls
+
+extern "C" int last_row_block() { return last_plan.row_block; }
+extern "C" int last_copiers() { return last_plan.copiers; }
 
 extern "C" int count_pieces(int tiles, int piece, float reciprocal) { return ls::pieces_of(tiles, piece, reciprocal); }
 
@@ -232,3 +237,18 @@ def test_pieces_are_counted_exactly_with_an_inexact_reciprocal(lib):
         for _ in range(5):
             assert lib.count_pieces(tiles, piece, float(r)) == max(1, -(-tiles // piece)), (tiles, piece, r)
             r = np.nextafter(r, np.float32(1))
+
+
+def test_waves_that_copy(lib):
+    """At head_dim 64 a compute unit holds two blocks of 128 rows without waves that only copy, of those with them one: they go
+    where no unit would have two blocks.  At head_dim 128 it holds one of either."""
+    for (hq, hkv, d, t, capacity, batch), expect in (
+            ((16, 16, 64, 96, 8000, 16), 1),       # 256 blocks
+            ((32, 32, 64, 96, 20000, 4), 0),       # 512: four splits
+            ((16, 16, 64, 128, 3000, 20), 0),      # 960: three
+            ((8, 2, 64, 24, 16000, 8), 1),
+            ((32, 32, 128, 96, 20000, 4), 1),      # 512
+            ((8, 8, 128, 100, 20000, 40), 1)):
+        route(lib, desc(hq, hkv, d, t, capacity, batch))
+        assert lib.last_copiers() == expect, (hq, hkv, d, t, capacity, batch)
+        assert lib.last_row_block() in (128, 256)

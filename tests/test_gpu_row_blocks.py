@@ -46,6 +46,8 @@ def test_whole_call_against_the_oracle(dtype, hq, hkv, d, t, plens, variant):
     ("bf16", 8, 2, 128, 64, 1000, 4),    # short splits
     ("bf16", 8, 2, 128, 64, 3333, 3),    # long ones
     ("f16", 8, 2, 64, 40, 2010, 5),
+    ("bf16", 4, 2, 64, 24, 700, 2),      # 48 rows: alone with waves that copy, many without
+    ("f16", 4, 2, 64, 64, 3333, 3),      # 128 rows
     ("bf16", 6, 2, 128, 43, 31, 1),      # one tile
     ("f16", 4, 2, 128, 130, 700, 2),     # 260 rows
 ])

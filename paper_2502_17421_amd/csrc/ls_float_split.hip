@@ -18,8 +18,9 @@
 // Against the kernel on the vector ALUs and the tail kernel that it replaces (microseconds per call, 56 shapes 1.25 to 4.0
 // times as fast, none slower): 64 rows x 1024 keys, head_dim 64, 13.7 -> 9.4; 80 rows x 86 keys 15.6 -> 7.1; 8 KV heads x 108 rows
 // x 1016 keys 45.0 -> 18.0; x 160 rows x 4096 keys, 8 sequences, 541 -> 247 (87 TFLOP/s).  Error against float64, relative 2-norm,
-// below what it was on every one of them (3.5e-7 -> 3.0e-7, 3.6e-7 -> 2.6e-7, 4.3e-7 -> 3.3e-7, 3.9e-7 -> 3.8e-7): scores are four
-// sums, and outputs sums in two levels (kChain; without it the last one has 4.9e-7).
+// below what it was on every one of them (3.5e-7 -> 3.0e-7, 3.6e-7 -> 2.6e-7, 4.3e-7 -> 3.3e-7, 3.8e-7 -> 3.4e-7): scores are four
+// sums, and outputs sums in two levels.  Runs of eight tiles instead of four: the last one 3.7e-7 and 1 % less time, but 8 KV heads
+// x 256 rows x 4000 keys at head_dim 64 3.7e-7, where it was 3.6e-7 (now 3.5e-7); without levels 4.9e-7.
 #include "ls_internal.hpp"
 #include "ls_mfma.hpp"
 
@@ -29,7 +30,7 @@ namespace {
 
 constexpr int FTK = 16;             // keys per tile
 constexpr int FNW = 8;              // waves per workgroup
-constexpr int kChain = 8;           // tiles a wave adds up before it puts the sums aside
+constexpr int kChain = 4;           // tiles a wave adds up before it puts the sums aside
 constexpr float kFloatRaise = 8.f;  // the reference exponent is raised when a score exceeds it by 2^8
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 

@@ -124,6 +124,42 @@ def test_what_is_not_finite_stays_with_the_rows_that_see_it(hq, hkv, d, t, plen)
 
 
 @pytest.mark.gpu
+def test_sums_are_taken_in_short_runs():
+    """Keys of equal weight: what is left of the error is that of the sums.  It is that of fp32 additions one by one in runs of four
+    tiles of a wave, whose sums are added up in turn, then the waves' (simulated; runs of eight tiles have 1.3 times as much)."""
+    b, h, d, t, plen = 8, 32, 64, 16, 4096
+    rng = np.random.default_rng(64000)
+
+    def simulated(v):  # [keys, columns]
+        tiles = v.reshape(-1, 4, 4, v.shape[1]).transpose(0, 2, 1, 3).reshape(-1, 16, v.shape[1])  # in the order of the products
+        total = np.zeros(v.shape[1], np.float32)
+        for wave in range(8):
+            kept = run = np.zeros(v.shape[1], np.float32)
+            for i, tile in enumerate(tiles[wave::8]):
+                for row in tile:
+                    run = run + row
+                if i % 4 == 3:
+                    kept, run = kept + run, np.zeros_like(run)
+            total = total + (kept + run)
+        return total / np.float32(len(v))
+
+    rel = lambda x, ref: float(np.sqrt(np.mean((x - ref) ** 2) / np.mean(ref ** 2)))
+    sample = rng.standard_normal((plen, 4096), dtype=np.float32)
+    expect = rel(simulated(sample).astype(np.float64), sample.astype(np.float64).mean(0))
+    q, k = torch.zeros((b, h, t, d), device="cuda"), torch.zeros((b, h, plen, d), device="cuda")
+    v = torch.from_numpy(rng.standard_normal((b, h, plen, d), dtype=np.float32)).cuda()
+    out, lse = torch.zeros_like(q), torch.zeros((b, h, t), device="cuda")
+    x = ls.make_desc(q, k, v, q, q, out, plen)
+    print("float, equal weights", flush=True)
+    ls.ls_cache_attn(x, q, k, v, torch.full((b,), plen, dtype=torch.int32, device="cuda"), out, lse,
+                     torch.empty(ls.ls_workspace_bytes(x), dtype=torch.uint8, device="cuda"))
+    ref = v.double().mean(2, keepdim=True).expand(-1, -1, t, -1)
+    got = rel(out.double().cpu().numpy(), ref.cpu().numpy())
+    print(f"  {got:.3e}, simulated {expect:.3e}", flush=True)
+    assert got <= 1.1 * expect
+
+
+@pytest.mark.gpu
 def test_bad_parents_are_cut_and_reported():
     for t, plen in ((40, 100), (100, 2000)):
         batch = make("f32", 4, 2, 64, t, [plen, plen], "tree", 63000 + t)

@@ -382,7 +382,9 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
 
 // Float calls: one form, so only its sizes are chosen: 16 or 32 query rows per workgroup, and into how many runs of
 // 16-key tiles the keys of a sequence are cut.  Modelled time (microseconds, measured on MI355X):
-//   rounds of workgroups * (2 (32 rows: 3) + tiles of a workgroup / 8 * t), t = 1.4 (2.65) at head_dim 64, 3.05 (4.9) at 128
+//   rounds of workgroups * (2 (32 rows: 3) + tiles of a workgroup / 8 * t), t = 1.4 (2.65) at head_dim 64, 3.05 (4.9) at 128;
+//   the last run holds all tree tiles, so a workgroup has as many at least (2 KV heads x 512 rows x 1000 keys, head_dim 128: 3
+//   runs 27.2 us, 8 runs, the choice by equal shares, 37.7)
 //   more than one run: 2.9 (head_dim 64) or 3.3 for the merge and its launch, and the parts at 3.5 TB/s
 // Both row counts and all run counts against this choice, 22 shapes: within 8 % of the best one (1024 keys x 64 rows, head_dim
 // 64, 1, 9 and 16 runs 18.4, 10.0 and 9.6 us; 8 KV heads x 64 rows x 1024 keys, head_dim 128, 1, 5 and 8 runs 32.7,
@@ -390,7 +392,7 @@ WholePlan plan_whole(const ls_desc &d, const SplitPlan &plan, const Problem &p, 
 WholePlan plan_float(const ls_desc &d, const SplitPlan &plan, bool with_tree)
 {
     const int64_t rows_kv = (int64_t)(d.n_q_heads / d.n_kv_heads) * d.n_tree, cus = compute_units();
-    const int64_t tiles = (d.max_prefix_len + 15ll) / 16 + (with_tree ? (d.n_tree + 15) / 16 : 0);
+    const int64_t tree_tiles = with_tree ? (d.n_tree + 15) / 16 : 0, tiles = (d.max_prefix_len + 15ll) / 16 + tree_tiles;
     const bool wide = d.head_dim == 128;
     const double part_us = (double)d.batch * d.n_q_heads * d.n_tree * d.head_dim * 4.0 / 3.5e6;
     WholePlan w{0, 0, true};
@@ -400,7 +402,8 @@ WholePlan plan_float(const ls_desc &d, const SplitPlan &plan, bool with_tree)
         const double start = rt == 1 ? 2.0 : 3.0, tile = (wide ? (rt == 1 ? 3.05 : 4.9) : (rt == 1 ? 1.4 : 2.65)) / 8.0;
         auto consider = [&](int64_t n) {
             n = n < 1 ? 1 : (n > plan.n_splits ? plan.n_splits : n);
-            const double rounds = (double)((units * n + cus - 1) / cus), per = (double)((tiles + n - 1) / n);
+            const int64_t share = (tiles + n - 1) / n;
+            const double rounds = (double)((units * n + cus - 1) / cus), per = (double)(share > tree_tiles ? share : tree_tiles);
             const double cost = rounds * (start + per * tile) + (n > 1 ? (wide ? 3.3 : 2.9) + (double)n * part_us : 0.0);
             if (w.row_tiles == 0 || cost < best) {
                 best = cost;

@@ -195,3 +195,12 @@ def test_routes(lib):
             first = route(lib, x, tree=tree)
             n = int(first[0].split("splits=")[1].rstrip(")").split(",")[0])
             assert first[0].startswith("wave_split(") and 1 <= n <= most and len(first) == (1 if n == 1 else 2)
+
+
+def test_large_trees_are_counted_as_the_last_run_takes_them(lib):
+    """All tree tiles go to the last run of keys, so more runs than leave it with an equal share make nothing shorter."""
+    for sizes in ((2, 2, 128, 512, 1000), (2, 2, 128, 512, 2000), (2, 2, 128, 300, 700), (1, 1, 64, 512, 3000)):
+        first = route(lib, desc(*sizes, dtype=ls.LS_F32))[0]
+        n = int(first.split("splits=")[1].rstrip(")").split(",")[0])
+        tree_tiles, tiles = (sizes[3] + 15) // 16, (sizes[4] + 15) // 16 + (sizes[3] + 15) // 16
+        assert n > 1 and -(-tiles // (n - 1)) > tree_tiles, (sizes, n)  # (one run fewer would be longer than the tree)

@@ -12,7 +12,9 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import platform
 import types
+import warnings
 from typing import Optional
 
 import torch
@@ -109,15 +111,31 @@ _DEVICE_CALLS = ("ls_hybrid_tree_attn", "ls_hybrid_tree_attn_single", "ls_hybrid
                  "ls_lse_merge", "ls_tree_accept_greedy", "ls_kv_commit", "ls_kv_commit_paged")
 
 
+def _call_module(L):
+    """The native module, or None if it is not built, does not load, or was built for something else: its signatures and the
+    layout of a tensor are compiled in."""
+    if not os.path.exists(CALL_PATH):
+        return None
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_ls_call", CALL_PATH)
+        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_ls_call", loader))
+        loader.exec_module(native)
+        built = native.interface_id, native.torch_version, native.python_version
+        have = (ctypes.c_char * 17).in_dll(L, "ls_interface_id").value.decode(), str(torch.__version__), platform.python_version()
+    except (ImportError, AttributeError, ValueError) as e:
+        warnings.warn(f"{CALL_PATH} does not load or does not fit ({e}): calls go through ctypes", RuntimeWarning)
+        return None
+    if built != have:
+        warnings.warn(f"{CALL_PATH} was built for {built}, not {have}: calls go through ctypes", RuntimeWarning)
+        return None
+    return native
+
+
 def _device_calls(L):
     """The device entry points of a loaded library as callables that take tensors (None, addresses) for pointers and
     an ls_desc for its address."""
     calls = types.SimpleNamespace()
-    native = None
-    if os.path.exists(CALL_PATH):
-        loader = importlib.machinery.ExtensionFileLoader("_ls_call", CALL_PATH)
-        native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_ls_call", loader))
-        loader.exec_module(native)
+    native = _call_module(L)
 
     def through_ctypes(fn):
         def call(*args):

@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import glob
+import hashlib
 import os
 import subprocess
 import sys
@@ -14,13 +15,21 @@ PROBE_SRC = os.path.join(HERE, "csrc_probe", "ls_probe.hip")
 PROBE_LIB_PATH = os.path.join(HERE, "libls_probe.so")   # bench-only measurement helpers
 CALL_SRC = os.path.join(HERE, "csrc_bind", "ls_call.cpp")
 CALL_PATH = os.path.join(HERE, "_ls_call.so")   # Python's way into the library
+HEADER = os.path.join(ROOT, "include", "ls_attn.h")
+
+
+def interface_id() -> str:
+    """What the library and the module that calls it are compiled with, so that the binding can tell whether they fit."""
+    with open(HEADER, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument",
-    "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+    "-I", os.path.join(ROOT, "include"), "-I", CSRC, f'-DLS_INTERFACE_ID="{interface_id()}"',
 ]
 
 
@@ -28,21 +37,26 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def _older(path: str, deps) -> bool:
+    return not os.path.exists(path) or any(os.path.getmtime(d) > os.path.getmtime(path) for d in deps)
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH):
-        return True
-    t = os.path.getmtime(LIB_PATH)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
-    return any(os.path.getmtime(d) > t for d in deps)
+    return _older(LIB_PATH, sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(ROOT, "include", "*.h")))
+
+
+def call_module_is_stale() -> bool:
+    return _older(CALL_PATH, [CALL_SRC, HEADER])
 
 
 RESOURCE_REPORT = os.path.join(HERE, "libls_attn.resources.txt")
 
 
 def build_library(force: bool = True, extra_flags=()) -> str:
-    """Compile every csrc/*.hip into one shared library.  Returns its path.  The compiler's
+    """Compile every csrc/*.hip into one shared library, and the module that calls it.  Returns the library's path.  The compiler's
     per-kernel resource remarks (registers, scratch, spills) are kept next to the library:
     the cached-key kernel counts its own outstanding loads, which a register spill would upset."""
+    build_call_module(force)
     if not force and not is_stale():
         return LIB_PATH
     cmd = [HIPCC, *FLAGS, *extra_flags, "-Rpass-analysis=kernel-resource-usage", "-o", LIB_PATH, *sources()]
@@ -80,22 +94,25 @@ def build_probe_library() -> str:
     return PROBE_LIB_PATH
 
 
-def build_call_module() -> str:
+def build_call_module(force: bool = True) -> str:
     """Compile the module through which Python calls the library's device entry points."""
     import sysconfig
 
     import torch
+    if not force and not call_module_is_stale():
+        return CALL_PATH
     root = os.path.dirname(torch.__file__)
     include = os.path.join(root, "include")
     subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-isystem",
                     sysconfig.get_paths()["include"], "-isystem", include, "-isystem",
                     os.path.join(include, "torch", "csrc", "api", "include"),
-                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-o", CALL_PATH, CALL_SRC, "-L",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    f'-DLS_INTERFACE_ID="{interface_id()}"', f'-DLS_TORCH_VERSION="{torch.__version__}"', "-o", CALL_PATH, CALL_SRC, "-L",
                     os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], check=True)
     return CALL_PATH
 
 
 if __name__ == "__main__":
     print(build_library())
+    print(CALL_PATH)
     print(build_probe_library())
-    print(build_call_module())

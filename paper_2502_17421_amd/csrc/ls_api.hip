@@ -425,6 +425,12 @@ extern "C" {
 
 int ls_version(void) { return 100; }
 
+// Which header this was compiled with (a hash, given by the build): callers with compiled-in signatures compare it with theirs.
+#ifndef LS_INTERFACE_ID
+#define LS_INTERFACE_ID ""
+#endif
+extern const char ls_interface_id[17] = LS_INTERFACE_ID;
+
 const char *ls_status_string(int status)
 {
     switch (status) {

@@ -159,6 +159,13 @@ PyMODINIT_FUNC PyInit__ls_call(void)
     if (PyType_Ready(&CallerType) < 0) return nullptr;
     PyObject *m = PyModule_Create(&module_def);
     if (!m) return nullptr;
+    // what the signatures above, and the tensor type, come from: the loader compares it with what it has
+    if (PyModule_AddStringConstant(m, "interface_id", LS_INTERFACE_ID) < 0 ||
+        PyModule_AddStringConstant(m, "torch_version", LS_TORCH_VERSION) < 0 ||
+        PyModule_AddStringConstant(m, "python_version", PY_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
     Py_INCREF(&CallerType);
     if (PyModule_AddObject(m, "Caller", (PyObject *)&CallerType) < 0) {
         Py_DECREF(&CallerType);

@@ -13,8 +13,7 @@ from test_call_routes import KT, K, LENS, LSE, OUT, PARENTS, Q, V, VT, WORK, des
 
 @pytest.fixture(scope="module", params=["native", "ctypes"])
 def calls(request, lib):  # noqa: F811
-    if not os.path.exists(ls.CALL_PATH):
-        ls_build.build_call_module()
+    ls_build.build_call_module(force=False)
     for name in ls._DEVICE_CALLS:
         getattr(lib, name).argtypes = getattr(ls.lib(), name).argtypes
     path, ls.CALL_PATH = ls.CALL_PATH, ls.CALL_PATH if request.param == "native" else ls.CALL_PATH + ".missing"
@@ -77,3 +76,36 @@ def test_wrong_arguments_are_python_errors(calls):
                 made.ls_hybrid_tree_attn(*a)
     with pytest.raises(errors):
         made.ls_hybrid_tree_attn(*args[:-1])
+
+
+def test_a_module_that_does_not_fit_is_left_alone(lib, tmp_path, monkeypatch):  # noqa: F811
+    """One that does not load, one for another header, torch or Python, and one older than these: ctypes, and a warning."""
+    ls_build.build_call_module(force=False)
+    for name in ls._DEVICE_CALLS:
+        getattr(lib, name).argtypes = getattr(ls.lib(), name).argtypes
+    x = desc(8, 2, 128, 8, 300)
+    args = [x, Q, K, V, LENS, KT, VT, PARENTS, OUT, LSE, WORK, 1 << 40, None]
+    with open(ls.CALL_PATH, "rb") as f:
+        image = f.read()
+    for i, (old, new) in enumerate(((image, b"no module"), (ls_build.interface_id().encode(), b"0" * 16),
+                                    (torch.__version__.encode() + b"\0", b"0" * len(torch.__version__) + b"\0"),
+                                    (b"python_version", b"python_versiox"))):
+        assert old in image
+        path = tmp_path / f"_ls_call_{i}.so"
+        path.write_bytes(image.replace(old, new))
+        monkeypatch.setattr(ls, "CALL_PATH", str(path))
+        with pytest.warns(RuntimeWarning, match="ctypes"):
+            made = ls._device_calls(lib)
+        assert type(made.ls_kv_commit).__name__ != "Caller"
+        assert made.ls_hybrid_tree_attn(*args) == ls.LS_OK and lib.take_route()
+
+
+def test_an_outdated_module_is_built_again(tmp_path, monkeypatch):
+    module = tmp_path / "_ls_call.so"
+    monkeypatch.setattr(ls_build, "CALL_PATH", str(module))
+    assert ls_build.call_module_is_stale()
+    module.write_bytes(b"")
+    assert not ls_build.call_module_is_stale()
+    for source in (ls_build.CALL_SRC, ls_build.HEADER):
+        os.utime(module, (os.path.getmtime(source) - 10,) * 2)
+        assert ls_build.call_module_is_stale()

@@ -362,8 +362,8 @@ def ls_tree_accept_greedy(parents, draft_tokens, target_tokens, accept_path, acc
                           stream=None, check: bool = True) -> int:
     """All tensors device int32: parents/draft_tokens/target_tokens/accept_path [batch, n_tree];
     accept_len/next_token/err_flag [batch]."""
-    batch, n_tree = parents.shape
-    st = lib().call.ls_tree_accept_greedy(parents, draft_tokens, target_tokens, batch, n_tree,
+    shape = parents.shape
+    st = lib().call.ls_tree_accept_greedy(parents, draft_tokens, target_tokens, shape[0], shape[1],
                                           accept_path, accept_len, next_token, err_flag, _stream(stream))
     if check:
         _check(st, "ls_tree_accept_greedy")

@@ -2,6 +2,7 @@
 the library's host code and launchers that only write down what they are asked for."""
 import ctypes
 import os
+import types
 
 import pytest
 import torch
@@ -109,3 +110,20 @@ def test_an_outdated_module_is_built_again(tmp_path, monkeypatch):
     for source in (ls_build.CALL_SRC, ls_build.HEADER):
         os.utime(module, (os.path.getmtime(source) - 10,) * 2)
         assert ls_build.call_module_is_stale()
+
+
+def test_acceptance_takes_the_first_two_axes_of_parents(calls, monkeypatch):
+    """A trailing axis of one is as good as none."""
+    _, made = calls
+    seen = []
+
+    def record(*args):
+        seen.append(args[3:5])
+        return made.ls_tree_accept_greedy(PARENTS, Q, K, *args[3:5], OUT, LENS, LSE, None, None)
+
+    monkeypatch.setattr(ls, "lib", lambda: types.SimpleNamespace(call=types.SimpleNamespace(ls_tree_accept_greedy=record)))
+    monkeypatch.setattr(ls, "_stream", lambda stream: None)
+    for shape in ((3, 7), (3, 7, 1)):
+        x = torch.zeros(shape, dtype=torch.int32)
+        assert ls.ls_tree_accept_greedy(x, x, x, x, x, x) == ls.LS_OK
+    assert seen == [(3, 7), (3, 7)]

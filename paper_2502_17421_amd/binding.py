@@ -100,7 +100,7 @@ def lib() -> ctypes.CDLL:
                  "ls_kv_commit", "ls_hybrid_tree_attn_paged", "ls_cache_attn_paged",
                  "ls_kv_commit_paged"):
         getattr(L, name).restype = ctypes.c_int
-    L.call = _device_calls(L)
+    L.call = _device_calls(L, addresses=False)  # the functions below take tensors
     _lib = L
     return L
 
@@ -131,21 +131,25 @@ def _call_module(L):
     return native
 
 
-def _device_calls(L):
-    """The device entry points of a loaded library as callables that take tensors (None, addresses) for pointers and
-    an ls_desc for its address."""
+def _device_calls(L, addresses=True):
+    """The device entry points of a loaded library as callables that take tensors (None, and integers if `addresses`) for
+    pointers and an ls_desc for its address."""
     calls = types.SimpleNamespace()
     native = _call_module(L)
 
     def through_ctypes(fn):
         def call(*args):
+            if not addresses:  # (the last argument is the stream)
+                for a, kind in zip(args[:-1], fn.argtypes):
+                    if kind is _vp and isinstance(a, int):
+                        a.data_ptr()  # an AttributeError
             return fn(*[ctypes.byref(a) if isinstance(a, ls_desc) else a.data_ptr() if hasattr(a, "data_ptr") else a
                         for a in args])
         return call
 
     for name in _DEVICE_CALLS:
         fn = getattr(L, name)
-        setattr(calls, name, native.Caller(ctypes.cast(fn, _vp).value, name) if native else through_ctypes(fn))
+        setattr(calls, name, native.Caller(ctypes.cast(fn, _vp).value, name, addresses) if native else through_ctypes(fn))
     return calls
 
 

@@ -1,5 +1,6 @@
-// Calls into the C ABI of include/ls_attn.h from Python: Caller(address, name) is a callable whose arguments are those of the
-// entry point, a tensor (or None, or an integer address) where it takes a pointer, the ls_desc structure where it takes one.
+// Calls into the C ABI of include/ls_attn.h from Python: Caller(address, name, addresses) is a callable whose arguments are
+// those of the entry point, a tensor or None (or, if `addresses`, an integer address) where it takes a pointer, the stream's
+// handle, the ls_desc structure where it takes one.
 // It returns the status.  ctypes takes 3 us to marshal such a call, a launch 2.4; this takes 0.4, so a program that
 // accepts a path and commits its rows (two calls) takes 7.4 us a round instead of 11.2, and of every call some 3 us of the host.
 #define PY_SSIZE_T_CLEAN
@@ -18,7 +19,7 @@
 namespace {
 
 // An argument as the C function takes it; false: a Python error is set.
-bool convert(PyObject *obj, const ls_desc *&value)
+bool convert(PyObject *obj, const ls_desc *&value, bool)
 {
     Py_buffer view;
     if (PyObject_GetBuffer(obj, &view, PyBUF_SIMPLE) != 0) return false;
@@ -35,7 +36,7 @@ bool integer(PyObject *obj, unsigned long long &value)  // wraps around like a C
     return !(value == (unsigned long long)-1 && PyErr_Occurred());
 }
 
-template <typename T> std::enable_if_t<std::is_integral_v<T>, bool> convert(PyObject *obj, T &value)
+template <typename T> std::enable_if_t<std::is_integral_v<T>, bool> convert(PyObject *obj, T &value, bool)
 {
     unsigned long long wide = 0;
     if (!integer(obj, wide)) return false;
@@ -43,14 +44,14 @@ template <typename T> std::enable_if_t<std::is_integral_v<T>, bool> convert(PyOb
     return true;
 }
 
-template <typename T> bool convert(PyObject *obj, T *&value)
+template <typename T> bool convert(PyObject *obj, T *&value, bool address_taken)
 {
     unsigned long long address = 0;
     if (obj == Py_None) {
         value = nullptr;
         return true;
     }
-    if (PyLong_Check(obj)) {
+    if (address_taken && PyLong_Check(obj)) {
         if (!integer(obj, address)) return false;
     } else if (THPVariable_CheckExact(obj)) {
         try {
@@ -71,10 +72,11 @@ template <typename T> bool convert(PyObject *obj, T *&value)
 }
 
 template <typename... A, size_t... I>
-PyObject *call_typed(int (*fn)(A...), PyObject *const *args, std::index_sequence<I...>)
+PyObject *call_typed(int (*fn)(A...), PyObject *const *args, bool addresses, std::index_sequence<I...>)
 {
     std::tuple<A...> values;
-    if (!(convert(args[I], std::get<I>(values)) && ...)) return nullptr;
+    // (the last argument is the stream)
+    if (!(convert(args[I], std::get<I>(values), addresses || I + 1 == sizeof...(I)) && ...)) return nullptr;
     int status;
     Py_BEGIN_ALLOW_THREADS
     status = fn(std::get<I>(values)...);
@@ -82,14 +84,14 @@ PyObject *call_typed(int (*fn)(A...), PyObject *const *args, std::index_sequence
     return PyLong_FromLong(status);
 }
 
-typedef PyObject *(*Invoke)(void *, PyObject *const *);
+typedef PyObject *(*Invoke)(void *, PyObject *const *, bool);
 
 template <typename F> struct Typed;
 template <typename... A> struct Typed<int (*)(A...)> {
     static constexpr int count = sizeof...(A);
-    static PyObject *invoke(void *fn, PyObject *const *args)
+    static PyObject *invoke(void *fn, PyObject *const *args, bool addresses)
     {
-        return call_typed((int (*)(A...))fn, args, std::index_sequence_for<A...>{});
+        return call_typed((int (*)(A...))fn, args, addresses, std::index_sequence_for<A...>{});
     }
 };
 
@@ -112,6 +114,7 @@ struct Caller {
     vectorcallfunc vectorcall;
     void *fn;
     const Entry *entry;
+    bool addresses;
 };
 
 PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames)
@@ -122,14 +125,15 @@ PyObject *caller_call(PyObject *self, PyObject *const *args, size_t nargsf, PyOb
         PyErr_Format(PyExc_TypeError, "%s takes %d positional arguments", c->entry->name, c->entry->count);
         return nullptr;
     }
-    return c->entry->invoke(c->fn, args);
+    return c->entry->invoke(c->fn, args, c->addresses);
 }
 
 PyObject *caller_new(PyTypeObject *type, PyObject *args, PyObject *)
 {
     unsigned long long address = 0;
     const char *name = nullptr;
-    if (!PyArg_ParseTuple(args, "Ks", &address, &name)) return nullptr;
+    int addresses = 0;
+    if (!PyArg_ParseTuple(args, "Ksp", &address, &name, &addresses)) return nullptr;
     for (const Entry &entry : kEntries) {
         if (std::strcmp(entry.name, name) != 0) continue;
         Caller *c = (Caller *)type->tp_alloc(type, 0);
@@ -137,6 +141,7 @@ PyObject *caller_new(PyTypeObject *type, PyObject *args, PyObject *)
         c->vectorcall = caller_call;
         c->fn = (void *)(uintptr_t)address;
         c->entry = &entry;
+        c->addresses = addresses != 0;
         return (PyObject *)c;
     }
     PyErr_Format(PyExc_ValueError, "no entry point %s", name);

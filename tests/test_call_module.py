@@ -20,9 +20,11 @@ def calls(request, lib):  # noqa: F811
     path, ls.CALL_PATH = ls.CALL_PATH, ls.CALL_PATH if request.param == "native" else ls.CALL_PATH + ".missing"
     try:
         made = ls._device_calls(lib)
+        tensors_only = ls._device_calls(lib, addresses=False)
     finally:
         ls.CALL_PATH = path
     assert (type(made.ls_kv_commit).__name__ == "Caller") == (request.param == "native")
+    made.tensors_only = tensors_only
     return lib, made
 
 
@@ -127,3 +129,28 @@ def test_acceptance_takes_the_first_two_axes_of_parents(calls, monkeypatch):
         x = torch.zeros(shape, dtype=torch.int32)
         assert ls.ls_tree_accept_greedy(x, x, x, x, x, x) == ls.LS_OK
     assert seen == [(3, 7), (3, 7)]
+
+
+def test_an_integer_is_no_tensor(calls):
+    """The binding's functions take tensors: a size or an index in the place of one is an error, not an address."""
+    lib, made = calls  # noqa: F811
+    x = desc(8, 2, 128, 8, 300)
+
+    class Pointer:
+        def __init__(self, address):
+            self.address = address
+
+        def data_ptr(self):
+            return self.address
+
+    args = [x, *[Pointer(a) for a in (Q, K, V, LENS, KT, VT, PARENTS, OUT, LSE, WORK)], 1 << 40, 12345]
+    assert made.tensors_only.ls_hybrid_tree_attn(*args) == ls.LS_OK and lib.take_route()
+    for at in range(1, 11):
+        a = list(args)
+        a[at] = 64
+        with pytest.raises(AttributeError, match="data_ptr"):
+            made.tensors_only.ls_hybrid_tree_attn(*a)
+    assert not lib.take_route()
+    y = torch.zeros((1, 4), dtype=torch.int32)
+    with pytest.raises(AttributeError, match="data_ptr"):
+        ls.ls_tree_accept_greedy(y, y, 64, y, y, y, stream=0)

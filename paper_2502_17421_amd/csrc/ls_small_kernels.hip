@@ -239,8 +239,8 @@ template <int LPR, int CH, int PART_BYTES> constexpr int tail_waves_per_simd()
     return (LPR == 16 && CH == 16) || CH * PART_BYTES >= 256 ? 1 : (LPR == 16 && CH * PART_BYTES < 128 ? 3 : 2);
 }
 
-template <typename T, typename PT, int D, int LPR, int CH>
-__global__ void __launch_bounds__(kWave, (tail_waves_per_simd<LPR, CH, (int)sizeof(PT) * D / LPR>()))
+template <typename T, int D, int LPR, int CH>
+__global__ void __launch_bounds__(kWave, (tail_waves_per_simd<LPR, CH, (int)sizeof(T) * D / LPR>()))
 tree_merge_kernel(Problem p, const uint64_t *__restrict__ mask, Partials parts, int32_t n_cache, T *__restrict__ out,
                   int64_t os0, int64_t os1, int64_t os2, float *__restrict__ lse)
 {
@@ -259,7 +259,7 @@ tree_merge_kernel(Problem p, const uint64_t *__restrict__ mask, Partials parts, 
     const int g = t % p.n_kv_heads;
     const int b = t / p.n_kv_heads;
     const uint64_t *mask_b = mask ? mask + (size_t)b * p.n_tree * ((p.n_tree + 63) >> 6) : nullptr;
-    tail_rows<T, PT, D, LPR, CH>(p, mask_b, parts, n_cache, out, os0, os1, os2, lse, b, g * p.group + hh, i, live, lane);
+    tail_rows<T, T, D, LPR, CH>(p, mask_b, parts, n_cache, out, os0, os1, os2, lse, b, g * p.group + hh, i, live, lane);
 }
 
 hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, const Partials &cache_parts,
@@ -271,33 +271,23 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
     const bool wide = n_cache_parts > 16 && rows <= kTailWideMaxRows;
     const int rows_per_wave = wide ? 1 : 4;
     const dim3 block(kWave), grid((rows + rows_per_wave - 1) / rows_per_wave);
-#define LS_TM_LAUNCH(T, PT, DD, LPR, CH)                                                                          \
-    hipLaunchKernelGGL((tree_merge_kernel<T, PT, DD, LPR, CH>), grid, block, 0, stream, p, mask, cache_parts,     \
+#define LS_TM_LAUNCH(T, DD, LPR, CH)                                                                              \
+    hipLaunchKernelGGL((tree_merge_kernel<T, DD, LPR, CH>), grid, block, 0, stream, p, mask, cache_parts,         \
                        n_cache_parts, (T *)out, o_stride[0], o_stride[1], o_stride[2], lse)
-#define LS_TM_CASE(T, PT, DD)                                        \
-    do {                                                             \
-        if (wide) LS_TM_LAUNCH(T, PT, DD, 64, 32);                   \
-        else if (n_cache_parts <= 8) LS_TM_LAUNCH(T, PT, DD, 16, 4); \
-        else LS_TM_LAUNCH(T, PT, DD, 16, 16);                        \
+#define LS_TM_CASE(T, DD)                                        \
+    do {                                                         \
+        if (wide) LS_TM_LAUNCH(T, DD, 64, 32);                   \
+        else if (n_cache_parts <= 8) LS_TM_LAUNCH(T, DD, 16, 4); \
+        else LS_TM_LAUNCH(T, DD, 16, 16);                        \
     } while (0)
-    if (p.head_dim != 64 && p.head_dim != 128) return hipErrorInvalidValue;
+    if (!cache_parts.o_is_16bit || (p.head_dim != 64 && p.head_dim != 128)) return hipErrorInvalidValue;
     if (rows <= 0) return hipSuccess;
     if (dtype == LS_BF16) {
-        if (cache_parts.o_is_16bit) {
-            if (p.head_dim == 128) LS_TM_CASE(uint16_t, uint16_t, 128);
-            else LS_TM_CASE(uint16_t, uint16_t, 64);
-        } else {
-            if (p.head_dim == 128) LS_TM_CASE(uint16_t, float, 128);
-            else LS_TM_CASE(uint16_t, float, 64);
-        }
+        if (p.head_dim == 128) LS_TM_CASE(uint16_t, 128);
+        else LS_TM_CASE(uint16_t, 64);
     } else if (dtype == LS_F16) {
-        if (cache_parts.o_is_16bit) {
-            if (p.head_dim == 128) LS_TM_CASE(half_t, half_t, 128);
-            else LS_TM_CASE(half_t, half_t, 64);
-        } else {
-            if (p.head_dim == 128) LS_TM_CASE(half_t, float, 128);
-            else LS_TM_CASE(half_t, float, 64);
-        }
+        if (p.head_dim == 128) LS_TM_CASE(half_t, 128);
+        else LS_TM_CASE(half_t, 64);
     } else {
         return hipErrorInvalidValue;  // float calls end with merge_float_kernel
     }
@@ -488,7 +478,6 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(MergeArgs a)
 
 hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream)
 {
-    if (dtype == LS_F32) return launch_merge_float(p, w, stream);
     const int rows = p.batch * p.n_q_heads * p.n_tree;
     const bool wide = w.n_splits > 8;
     const int rows_per_block = 4 * (wide ? 1 : kWave / (p.head_dim / 8));

@@ -115,8 +115,8 @@ int ls_validate_parents_host(const int32_t *parents, int32_t batch, int32_t n_tr
 
 /*
  * Number of key-axis splits the library would pick for the cached part of this
- * problem (>= 1): what ls_prefix_attn_splitkv uses for n_splits = 0, and what the whole-path
- * calls use.  It depends on the descriptor AND on the number of compute units of the current
+ * problem (>= 1): what ls_prefix_attn_splitkv uses for n_splits = 0.  The whole-path calls
+ * take as many or fewer (short caches, few query rows, f32).  It depends on the descriptor AND on the number of compute units of the current
  * HIP device (the splits are sized to fill the GPU once); without a device it is computed
  * for 256 compute units (MI355X).  It is stable across calls on one device.  Ask for it, and
  * for ls_workspace_bytes, with the device current on which the call will run.
@@ -126,8 +126,8 @@ int ls_prefix_num_splits(const ls_desc *desc, int32_t *n_splits_out);
 /*
  * Bytes of DEVICE workspace ls_hybrid_tree_attn needs for this descriptor:
  * the tree mask, one error word per sequence, and the partial outputs (stored in the
- * problem's dtype) and LSEs of the cached part, one per key split (ls_prefix_num_splits, so
- * the size depends on the current device's compute-unit count in the same way).
+ * problem's dtype) and LSEs, one per key split of ls_prefix_num_splits (so the size depends
+ * on the current device's compute-unit count in the same way).
  * The workspace must be 256-byte aligned.
  */
 int ls_workspace_bytes(const ls_desc *desc, size_t *bytes_out);
@@ -136,11 +136,12 @@ int ls_workspace_bytes(const ls_desc *desc, size_t *bytes_out);
  * The whole path (Section 3.3): tree mask from `parents`, split-KV attention over the
  * cache, masked attention over the tree tokens, log-sum-exp merge into out / lse.  It runs
  * as one or two launches, chosen by the sizes: a kernel for the cached keys, which takes the
- * tree tokens along (short caches, few query rows, or a small tree and long splits) or whose
+ * tree tokens along (f32, short caches, few query rows, or a small tree and long splits) or whose
  * extra workgroups build the mask, then a merge of the parts, with the tree attention if it is
  * still to do.  With contiguous caches, out and lse may lie over cached rows, lengths or
- * parents, and out over q row by row (in place); the call then takes the latter route.  A pool
- * of pages must not overlap the outputs.
+ * parents, and out over q row by row (in place); 16-bit calls then take the latter route, f32
+ * calls leave their rows as parts, of a single split too, and merge them.  A pool of pages must
+ * not overlap the outputs.
  *
  *   prefix_lens  DEVICE int32[batch]; values are clamped into [0, max_prefix_len].
  *                A sequence with prefix length 0 attends to its tree tokens only.
@@ -215,9 +216,9 @@ int ls_hybrid_tree_attn_static(const ls_desc *desc, const void *q,
  *     after anything else wrote there).  ls_workspace_init enqueues a small kernel, never a
  *     memset, so both calls may sit in a captured HIP graph.  No other entry point reads or
  *     writes the counters.  Calls that share a workspace must not overlap in time.
- *   - Problems outside the matrix-core kernel (float inputs, row strides beyond its reach),
- *     with more than 64 key splits or with more than 4096 (sequence, KV head, query block)
- *     triples run in two launches, the second one with the tree attention and the merge.
+ *   - Problems with more than 64 key splits or with more than 4096 (sequence, KV head, query
+ *     block) triples run in two launches, the second one with the tree attention and the merge;
+ *     f32 problems run as in ls_hybrid_tree_attn.
  *   - ls_set_single_launch_polls(n) sets the number of polls (about half a microsecond
  *     apart) for later calls of this process: 0 makes every launch the nobody-waits form,
  *     a negative n restores the default (about 20 ms); n above 2^24 is LS_ERR_SHAPE.  A wait

@@ -138,13 +138,14 @@ def _device_calls(L, addresses=True):
     native = _call_module(L)
 
     def through_ctypes(fn):
+        # per argument: 1 a descriptor, 2 a pointer, 0 as it is (sizes, and the stream, which is the last one)
+        kinds = [1 if t not in (_vp, _i32, _sz) else 2 if t is _vp else 0 for t in fn.argtypes[:-1]] + [0]
+
         def call(*args):
-            if not addresses:  # (the last argument is the stream)
-                for a, kind in zip(args[:-1], fn.argtypes):
-                    if kind is _vp and isinstance(a, int):
-                        a.data_ptr()  # an AttributeError
-            return fn(*[ctypes.byref(a) if isinstance(a, ls_desc) else a.data_ptr() if hasattr(a, "data_ptr") else a
-                        for a in args])
+            if len(args) != len(kinds):
+                raise TypeError(f"{fn.__name__} takes {len(kinds)} positional arguments")
+            return fn(*[a if not kind or a is None else ctypes.byref(a) if kind == 1 else
+                        a if addresses and isinstance(a, int) else a.data_ptr() for kind, a in zip(kinds, args)])
         return call
 
     for name in _DEVICE_CALLS:

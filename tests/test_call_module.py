@@ -79,6 +79,8 @@ def test_wrong_arguments_are_python_errors(calls):
                 made.ls_hybrid_tree_attn(*a)
     with pytest.raises(errors):
         made.ls_hybrid_tree_attn(*args[:-1])
+    with pytest.raises(errors):
+        made.ls_hybrid_tree_attn(*args, None)
 
 
 def test_a_module_that_does_not_fit_is_left_alone(lib, tmp_path, monkeypatch):  # noqa: F811

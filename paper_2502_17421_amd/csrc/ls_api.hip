@@ -167,7 +167,8 @@ void *static_scratch_of_current_device()
 // Split schedule.  The cached keys of every sequence are cut into pieces of split_len rows
 // (a multiple of 64); the grid is sized for max_prefix_len.  Left to the library, the count S
 // minimises a modelled time.  Float path: units*S workgroups run in ceil(units*S / slots)
-// rounds of max_prefix_len / S keys each, plus a small charge per split.  MFMA path: the
+// rounds of max_prefix_len / S keys each, plus a small charge per split; this count is that of the
+// stand-alone call and of the workspace, and the most that a whole call takes (plan_float).  MFMA path: the
 // time of the whole call, cached-key kernel plus the kernel that merges the S parts of every
 // row, from figures measured on MI355X (microseconds; f = share of the compute units the
 // launch occupies, tiles of 32 keys):
@@ -246,7 +247,8 @@ SplitPlan plan_splits(const ls_desc &d, int32_t request)
     plan.split_len = (int32_t)len;
     plan.per_sequence = 0;
     plan.balanced = 0;
-    // blocks of 128 rows where twice the workgroups still have a compute unit each (see ls_prefix_mfma.hip)
+    // Blocks of 128 rows where twice the workgroups still have a compute unit each (see ls_prefix_mfma.hip; the mask's workgroups,
+    // one per sequence, come on top and wait for one).  The model above prices blocks of 256.
     const int64_t rows_kv = (int64_t)(d.n_q_heads / d.n_kv_heads) * d.n_tree;
     const int64_t light_blocks = (int64_t)d.batch * d.n_kv_heads * ((rows_kv + 127) / 128) * s;
     plan.row_block = light_blocks <= compute_units() ? 128 : 256;

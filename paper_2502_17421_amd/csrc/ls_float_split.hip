@@ -17,7 +17,7 @@
 // register set, with the tile after next on its way too, changed nothing.  Few keys: launch, first loads, a tile or two, merge.
 // Against the kernel on the vector ALUs and the tail kernel that it replaces (microseconds per call, 56 shapes 1.25 to 4.0
 // times as fast, none slower): 64 rows x 1024 keys, head_dim 64, 13.7 -> 9.4; 80 rows x 86 keys 15.6 -> 7.1; 8 KV heads x 108 rows
-// x 1016 keys 45.0 -> 18.0; x 160 rows x 4096 keys, 8 sequences, 541 -> 247 (87 TFLOP/s).  Error against float64, relative 2-norm,
+// x 1016 keys 45.0 -> 18.0; x 160 rows x 4096 keys, 8 sequences, 541 -> 250 (86 TFLOP/s).  Error against float64, relative 2-norm,
 // below what it was on every one of them (3.5e-7 -> 3.0e-7, 3.6e-7 -> 2.6e-7, 4.3e-7 -> 3.3e-7, 3.8e-7 -> 3.4e-7): scores are four
 // sums, and outputs sums in two levels.  Runs of eight tiles instead of four: the last one 3.7e-7 and 1 % less time, but 8 KV heads
 // x 256 rows x 4000 keys at head_dim 64 3.7e-7, where it was 3.6e-7 (now 3.5e-7); without levels 4.9e-7.

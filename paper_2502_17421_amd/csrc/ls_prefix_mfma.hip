@@ -12,11 +12,12 @@
 //
 // Blocks of 128 rows (CW = 4) leave the other wave of each SIMD to the copies: a wave that copies as well spends some
 // 550 of 2500 cycles per pair of tiles in the issue of its copies.  They serve heads with at most 128 rows (eight
-// sequences of 501 to 9003 keys x 8 KV heads x 96 rows, paged: 47.6 against 46.3 us with four waves doing both; 70 shapes
-// of 65 to 128 rows 0.98 of the time, best 0.86, worst 1.03), and heads with more rows while the blocks of 256
-// rows would leave half the chip idle (SplitPlan::row_block): two workgroups then share an XCD's L2 and
-// each has a compute unit (256 rows x 8k keys, 16 splits of 8 heads: 0.73 -> 0.58 us per tile, call 30.2 -> 28.1 us, with
-// four waves doing both 28.6; 5k to 8k keys, 144 to 256 rows 0.93 of the time).  Results do not depend on the form.
+// sequences of 501 to 9003 keys x 8 KV heads x 96 rows, paged: 45.3 us, with four waves doing both 46.9; at head_dim 64 only up
+// to one block per compute unit, see plan_splits), and heads with more rows while the blocks of 256 rows would leave half the
+// chip idle (SplitPlan::row_block): two workgroups then share an XCD's L2 and each has a compute unit (8 KV heads x 144 rows x 8k
+// keys 26.0 -> 24.1 us, with four waves doing both 24.7; 2 KV heads x 256 rows x 48k keys, head_dim 64, 23.1 -> 19.6;
+// 142 shapes of 130 to 1040 rows x 1.5k to 48k keys, head_dim 64 and 128, one to eight sequences, capacities up to six times the
+// lengths: 0.95 of the time, worst 1.008).  Results do not depend on the form.
 //
 // Data movement.  K and V rows go HBM -> LDS directly (global_load_lds_dwordx4, 16 bytes
 // per lane, no staging registers) in tiles of 32 keys.  K tiles and V tiles have rings of

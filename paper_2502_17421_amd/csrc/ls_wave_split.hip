@@ -10,11 +10,12 @@
 // eight waves read 64 KB of neighbouring K rows and of V rows at a time (tiles dealt to the splits in
 // turn instead: 59.4 against 54.9 us for 32 rows per KV head, 32 KV heads, 16k keys).
 //
-// What bounds it.  Latency and HBM: with 32 or 64 query rows a key tile of 16 KB costs 16 or 32 matrix
-// instructions.  A wave requests the V rows of a tile once its K rows are there, and the next K rows once the V rows
-// are: one of its two stages is in flight at any time, 64 KB per workgroup, and a tile costs two round trips in
-// series.  16k keys x 32 KV heads: 5.1 TB/s of the 7.2 that a large read reaches.  (The kernel for many
-// rows, ls_prefix_mfma.hip, shares tiles between its waves, which with few rows leaves waves without work.)
+// What bounds it.  Short caches: the launch, then three dependent round trips (length, keys, output).  Long ones: with 32 or 64
+// query rows a key tile of 16 KB costs 16 or 32 matrix instructions; 16k keys x 32 KV heads take 47.9 us, 5.6 TB/s of
+// the 7.2 that a large read reaches, with the matrix cores busy for 0.08 of the cycles.  A wave requests the V rows of a
+// tile once its K rows are there, and the next K rows once the V rows are, so one of its two stages is in flight at any time, 64 KB
+// per workgroup; both in flight took as long, so that is not what holds it back, and the cause is not known.  (The kernel for
+// many rows, ls_prefix_mfma.hip, shares tiles between its waves, which with few rows leaves waves without work.)
 //
 // Tree keys.  The tiles of the tree follow the cached tiles of the last split; the visibility of a
 // row is a mask of its ancestors.  Up to 64 nodes it is built in registers, lane = node, by

@@ -52,7 +52,8 @@ def test_whole_call_against_the_oracle(dtype, hq, hkv, d, t, plens, variant):
     ("f16", 4, 2, 128, 130, 700, 2),     # 260 rows
 ])
 def test_parts_do_not_depend_on_the_block(dtype, hq, hkv, d, t, plen, n_splits):
-    """One sequence takes blocks of 128 rows, so many copies of it that all blocks fill the chip take blocks of 256."""
+    """One sequence takes blocks of 128 rows with waves that copy; so many copies of it that all blocks fill the chip take blocks of 256,
+    or of 128 whose waves copy for themselves (at most 128 rows, head_dim 64)."""
     copies = 256 // (hkv * n_splits) + 1
     one = make(dtype, hq, hkv, d, t, [plen], "peaked", 52000 + t)
     many = make(dtype, hq, hkv, d, t, [plen] * copies, "peaked", 52000 + t)

@@ -534,9 +534,8 @@ FloatArgs float_args(const Problem &p, int n_splits)
 template <int D, int RT> hipError_t launch_one(const FloatArgs &a, dim3 grid, dim3 block, hipStream_t stream)
 {
     constexpr int lds_bytes = RT * FNW * 16 * (D * 4 + 8) + LS_MAX_TREE * 4 + (RT > 1 ? 16 * RT * D * 4 : 0);
-    static hipError_t attr = hipFuncSetAttribute((const void *)float_split_kernel<D, RT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 lds_bytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> allowed{0};
+    if (const hipError_t e = allow_dynamic_lds((const void *)float_split_kernel<D, RT>, lds_bytes, allowed); e != hipSuccess) return e;
     hipLaunchKernelGGL((float_split_kernel<D, RT>), grid, block, lds_bytes, stream, a);
     return hipGetLastError();
 }

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "ls_attn.h"
 
 namespace ls {
@@ -152,6 +154,20 @@ struct WholeCall {
     const SequenceSplits *table;  // balanced call: pieces per sequence; nullptr: n_splits each
     int32_t in_parts;             // rows leave as parts, also those of a single split
 };
+
+// Lets `kernel` have `bytes` of dynamic LDS on the current device; asked once per kernel and device (`done`: a bit per device).
+// A refusal is reported and asked for again by the next call.
+inline hipError_t allow_dynamic_lds(const void *kernel, int bytes, std::atomic<uint64_t> &done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+}
 
 // bf16 <-> float on raw 16-bit patterns (round to nearest even, NaN kept quiet).
 __device__ __forceinline__ float bf16_to_float(uint16_t v) { return __uint_as_float(((uint32_t)v) << 16); }

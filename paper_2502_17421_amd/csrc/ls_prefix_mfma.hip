@@ -1057,9 +1057,8 @@ hipError_t launch_form(const Problem &p, const SplitPlan &plan, const Partials &
     constexpr int lds_bytes = (2 * PD + 7) * TK * D * 2 + (PAGED ? kMaxSplitPages * 4 : 0) + (LS_MAX_TREE + 2 * NW) * 4;
     static_assert(lds_bytes <= 160 * 1024, "the rings exceed the 160 KB of a compute unit");
     auto kernel = prefix_mfma_kernel<D, NW, CW, F16, PAGED, PD, FUSED, TREE>;
-    static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 lds_bytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> allowed{0};
+    if (const hipError_t e = allow_dynamic_lds((const void *)kernel, lds_bytes, allowed); e != hipSuccess) return e;
     const int rows_kv = p.group * p.n_tree;
     const int n_qblocks = (rows_kv + CW * 32 - 1) / (CW * 32);
     const int64_t n_main = (int64_t)plan.n_splits * n_qblocks * p.batch * p.n_kv_heads;

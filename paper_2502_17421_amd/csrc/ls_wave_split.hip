@@ -579,9 +579,8 @@ hipError_t launch_one(WaveArgs a, int batch, hipStream_t stream)
     constexpr int lds_bytes = NW * 2 * TK * D * 2 + (RT > 1 ? RT * TK * D * 2 : 0) + LS_MAX_TREE * 4 + NW * 32 * 8;
     static_assert(lds_bytes <= 160 * 1024, "the stages exceed the 160 KB of a compute unit");
     auto kernel = wave_split_kernel<D, F16, PAGED, RT, TREE>;
-    static hipError_t attr = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 lds_bytes);
-    if (attr != hipSuccess) return attr;
+    static std::atomic<uint64_t> allowed{0};
+    if (const hipError_t e = allow_dynamic_lds((const void *)kernel, lds_bytes, allowed); e != hipSuccess) return e;
     const int64_t row_blocks = (a.rows_kv + 32 * RT - 1) / (32 * RT);
     const int64_t items = row_blocks * a.n_splits * batch * a.n_kv_heads;
     // (the bound keeps the kernel's divisions exact)

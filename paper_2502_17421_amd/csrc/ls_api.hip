@@ -528,11 +528,9 @@ int ls_prefix_attn_splitkv(const ls_desc *desc, const void *q, const void *k_cac
     hipError_t e;
     if (prefix_mfma_supports(p, desc->dtype)) {
         e = launch_prefix_mfma(p, desc->dtype, plan, out, MaskJob{nullptr, nullptr, nullptr}, FusedTail{}, (hipStream_t)stream);
-    } else if (desc->dtype == LS_F32) {
-        e = launch_float_pieces(p, plan, out, (hipStream_t)stream);
     } else {
         if (part_dtype != LS_F32) return LS_ERR_UNSUPPORTED;
-        e = launch_prefix_valu(p, desc->dtype, plan, out, (hipStream_t)stream);
+        e = launch_prefix_valu(p, desc->dtype, plan, out, MaskJob{nullptr, nullptr, nullptr}, (hipStream_t)stream);
     }
     return e == hipSuccess ? LS_OK : LS_ERR_HIP;
 }
@@ -574,13 +572,9 @@ int run_whole(const ls_desc &d, const Problem &p, SplitPlan splits, const WholeP
 {
     WholeCall w{parents, err, out, {d.o_stride[0], d.o_stride[1], d.o_stride[2]}, lse, o_parts, lse_parts, plan.n_splits,
                 FastDiv::of(plan.n_splits), FastDiv::of(d.n_tree), FastDiv::of(d.n_kv_heads), FastDiv::of(d.n_q_heads), nullptr, plan.n_splits > 1};
-    if (d.dtype == LS_F32) {
-        // (outputs may lie over inputs: the merge writes them when the inputs have been read)
-        if (!w.in_parts) w.in_parts = outputs_overlap_inputs(d, p, parents, out, lse);
-        if (launch_float_split(p, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
-        return !w.in_parts || launch_merge_float(p, w, s) == hipSuccess ? LS_OK : LS_ERR_HIP;
-    }
     if (plan.row_tiles > 0) {
+        // (a float call's outputs may lie over its inputs: the merge writes them when the inputs have been read)
+        if (d.dtype == LS_F32 && !w.in_parts) w.in_parts = outputs_overlap_inputs(d, p, parents, out, lse);
         if (launch_wave_split(p, d.dtype, plan.row_tiles, w, s) != hipSuccess) return LS_ERR_HIP;
         if (!w.in_parts) return LS_OK;
     } else {

@@ -246,7 +246,8 @@ hipError_t launch_tree_mask(const int32_t *parents, int32_t batch, int32_t n_tre
                             int32_t *err_flag, hipStream_t stream);
 hipError_t launch_tree_attn(const Problem &p, int dtype, const uint64_t *mask, const Partials &out,
                             hipStream_t stream);
-hipError_t launch_prefix_valu(const Problem &p, int dtype, const SplitPlan &plan, const Partials &out, hipStream_t stream);
+hipError_t launch_prefix_valu(const Problem &p, int dtype, const SplitPlan &plan, const Partials &out,
+                              const MaskJob &mask_job, hipStream_t stream);
 hipError_t launch_prefix_mfma(const Problem &p, int dtype, const SplitPlan &plan, const Partials &out,
                               const MaskJob &mask_job, const FusedTail &tail, hipStream_t stream);
 // query blocks per KV head of the MFMA kernel (the arrival counters of a single-launch call are
@@ -265,12 +266,12 @@ hipError_t launch_tree_merge(const Problem &p, int dtype, const uint64_t *mask, 
 
 // Whole-path kernel whose waves split the keys (32 * row_tiles query rows per workgroup, 1 or 2).
 hipError_t launch_wave_split(const Problem &p, int dtype, int row_tiles, const WholeCall &w, hipStream_t stream);
-// Float calls: the whole path (16 * row_tiles query rows per workgroup, 1 or 2), the stand-alone call's pieces of plan.split_len
-// rows, and the merge of the parts of a whole path (w.in_parts).
+// The same in fp32 (16 * row_tiles query rows per workgroup), what launch_wave_split runs for LS_F32; the stand-alone call's pieces
+// of plan.split_len rows, what launch_prefix_valu runs for it; and the merge of the whole path's parts, what launch_merge_parts runs.
 hipError_t launch_float_split(const Problem &p, int row_tiles, const WholeCall &w, hipStream_t stream);
 hipError_t launch_float_pieces(const Problem &p, const SplitPlan &plan, const Partials &out, hipStream_t stream);
 hipError_t launch_merge_float(const Problem &p, const WholeCall &w, hipStream_t stream);
-// Merge of the parts of a whole-path call on 16-bit inputs (w.in_parts) into out / lse.
+// Merge of the parts of a whole-path call (w.in_parts) into out / lse.
 hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream);
 
 hipError_t launch_tree_accept(const int32_t *parents, const int32_t *draft_tokens, const int32_t *target_tokens,

@@ -203,8 +203,11 @@ prefix_valu_kernel(Problem p, SplitPlan plan, Partials out)
     }
 }
 
-hipError_t launch_prefix_valu(const Problem &p, int dtype, const SplitPlan &plan, const Partials &out, hipStream_t stream)
+hipError_t launch_prefix_valu(const Problem &p, int dtype, const SplitPlan &plan, const Partials &out,
+                              const MaskJob &mask_job, hipStream_t stream)
 {
+    if (mask_job.parents) return hipErrorInvalidValue;  // no call has this kernel build the mask
+    if (dtype == LS_F32) return launch_float_pieces(p, plan, out, stream);
     const int rows_kv = p.group * p.n_tree;
     const int n_qblocks = (rows_kv + TQ - 1) / TQ;
     const dim3 block(256), grid(plan.n_splits, n_qblocks, p.batch * p.n_kv_heads);

@@ -478,6 +478,7 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(MergeArgs a)
 
 hipError_t launch_merge_parts(const Problem &p, int dtype, const WholeCall &w, hipStream_t stream)
 {
+    if (dtype == LS_F32) return launch_merge_float(p, w, stream);
     const int rows = p.batch * p.n_q_heads * p.n_tree;
     const bool wide = w.n_splits > 8;
     const int rows_per_block = 4 * (wide ? 1 : kWave / (p.head_dim / 8));

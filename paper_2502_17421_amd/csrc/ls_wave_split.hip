@@ -594,6 +594,7 @@ hipError_t launch_one(WaveArgs a, int batch, hipStream_t stream)
 
 hipError_t launch_wave_split(const Problem &p, int dtype, int row_tiles, const WholeCall &w, hipStream_t stream)
 {
+    if (dtype == LS_F32) return launch_float_split(p, row_tiles, w, stream);
     const bool f16 = dtype == LS_F16;
     const bool paged = p.block_table != nullptr;
     WaveArgs a{};

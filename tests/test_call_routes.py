@@ -33,22 +33,11 @@ hipError_t launch_prefix_mfma(const Problem &, int, const SplitPlan &plan, const
         plan.balanced ? ",dealt" : "", tail.counters ? ",fused" : "");
     return hipSuccess;
 }
-hipError_t launch_prefix_valu(const Problem &, int, const SplitPlan &plan, const Partials &, hipStream_t)
+hipError_t launch_prefix_valu(const Problem &, int, const SplitPlan &plan, const Partials &, const MaskJob &, hipStream_t)
 {
-    SAY("valu(splits=%d) ", plan.n_splits);
+    SAY("float(splits=%d) ", plan.n_splits);
     return hipSuccess;
 }
-hipError_t launch_float_split(const Problem &, int row_tiles, const WholeCall &w, hipStream_t)
-{
-    SAY("float_split(rows=%d,splits=%d%s) ", 16 * row_tiles, w.n_splits, w.parents ? ",tree" : "");
-    return hipSuccess;
-}
-hipError_t launch_float_pieces(const Problem &, const SplitPlan &plan, const Partials &, hipStream_t)
-{
-    SAY("float_pieces(splits=%d) ", plan.n_splits);
-    return hipSuccess;
-}
-hipError_t launch_merge_float(const Problem &, const WholeCall &, hipStream_t) { SAY("merge_float "); return hipSuccess; }
 hipError_t launch_merge_parts(const Problem &, int, const WholeCall &, hipStream_t) { SAY("merge "); return hipSuccess; }
 hipError_t launch_tree_merge(const Problem &, int, const uint64_t *mask, const Partials &, int32_t, void *, const int64_t *,
                              float *, hipStream_t)

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2502_17421_amd import binding as ls
-from test_call_routes import K, LENS, LSE, OUT, PARENTS, Q, V, desc, lib, route  # noqa: F401  (lib: fixture)
+from test_call_routes import PARENTS, Q, desc, lib, route  # noqa: F401  (lib: fixture)
 from test_gpu_light_block import make
 from util import DeviceBatch, gates, oracle_full
 
@@ -181,20 +181,20 @@ def test_bad_parents_are_cut_and_reported():
 
 def test_routes(lib):
     """One launch while the keys are few; runs of keys and a merge, of one run too where the outputs lie over inputs.  The workspace
-    holds the parts of ls_prefix_num_splits runs, so there are never more."""
+    holds the parts of ls_prefix_num_splits runs, so there are never more.  (The stand-in prints 32 rows for a tile of 16.)"""
     call = lambda *sizes, **at: route(lib, desc(*sizes, dtype=ls.LS_F32), **at)
-    assert call(4, 1, 64, 16, 100) == ["float_split(rows=16,splits=1,tree)"]
-    assert call(4, 1, 64, 16, 100, out=Q) == ["float_split(rows=16,splits=1,tree)", "merge_float"]
-    assert call(4, 1, 64, 16, 100, lse=PARENTS) == ["float_split(rows=16,splits=1,tree)", "merge_float"]
-    assert call(4, 1, 64, 16, 1024) == ["float_split(rows=16,splits=16,tree)", "merge_float"]
-    assert call(4, 1, 64, 16, 1024, tree=False) == ["float_split(rows=16,splits=16)", "merge_float"]
+    assert call(4, 1, 64, 16, 100) == ["wave_split(rows=32,splits=1,tree)"]
+    assert call(4, 1, 64, 16, 100, out=Q) == ["wave_split(rows=32,splits=1,tree)", "merge"]
+    assert call(4, 1, 64, 16, 100, lse=PARENTS) == ["wave_split(rows=32,splits=1,tree)", "merge"]
+    assert call(4, 1, 64, 16, 1024) == ["wave_split(rows=32,splits=16,tree)", "merge"]
+    assert call(4, 1, 64, 16, 1024, tree=False) == ["wave_split(rows=32,splits=16)", "merge"]
     for sizes in ((4, 1, 64, 1, 0), (32, 8, 128, 40, 4096, 8), (8, 2, 128, 512, 2 ** 31 - 1), (64, 64, 64, 4, 70, 1000)):
         x = desc(*sizes, dtype=ls.LS_F32)
         most = ls.ls_prefix_num_splits(x)
         for tree in (True, False):
             first = route(lib, x, tree=tree)
             n = int(first[0].split("splits=")[1].rstrip(")").split(",")[0])
-            assert first[0].startswith("float_split(rows=") and 1 <= n <= most and len(first) == (1 if n == 1 else 2)
+            assert first[0].startswith("wave_split(") and 1 <= n <= most and len(first) == (1 if n == 1 else 2)
 
 
 def test_large_trees_are_counted_as_the_last_run_takes_them(lib):
@@ -204,13 +204,3 @@ def test_large_trees_are_counted_as_the_last_run_takes_them(lib):
         n = int(first.split("splits=")[1].rstrip(")").split(",")[0])
         tree_tiles, tiles = (sizes[3] + 15) // 16, (sizes[4] + 15) // 16 + (sizes[3] + 15) // 16
         assert n > 1 and -(-tiles // (n - 1)) > tree_tiles, (sizes, n)  # (one run fewer would be longer than the tree)
-
-
-def test_the_stand_alone_call_runs_the_float_kernel(lib):
-    x = desc(4, 1, 64, 16, 1024, dtype=ls.LS_F32)
-    call = lib.ls_prefix_attn_splitkv
-    call.argtypes = ls.lib().ls_prefix_attn_splitkv.argtypes
-    for n in (1, 3):
-        assert call(x, Q, K, V, LENS, n, ls.LS_F32, OUT, LSE, None) == ls.LS_OK
-        assert lib.take_route().decode().split() == [f"float_pieces(splits={n})"]
-    assert call(x, Q, K, V, LENS, 1, ls.LS_BF16, OUT, LSE, None) == ls.LS_ERR_DTYPE and not lib.take_route()

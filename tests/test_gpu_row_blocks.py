@@ -46,14 +46,11 @@ def test_whole_call_against_the_oracle(dtype, hq, hkv, d, t, plens, variant):
     ("bf16", 8, 2, 128, 64, 1000, 4),    # short splits
     ("bf16", 8, 2, 128, 64, 3333, 3),    # long ones
     ("f16", 8, 2, 64, 40, 2010, 5),
-    ("bf16", 4, 2, 64, 24, 700, 2),      # 48 rows: alone with waves that copy, many without
-    ("f16", 4, 2, 64, 64, 3333, 3),      # 128 rows
     ("bf16", 6, 2, 128, 43, 31, 1),      # one tile
     ("f16", 4, 2, 128, 130, 700, 2),     # 260 rows
 ])
 def test_parts_do_not_depend_on_the_block(dtype, hq, hkv, d, t, plen, n_splits):
-    """One sequence takes blocks of 128 rows with waves that copy; so many copies of it that all blocks fill the chip take blocks of 256,
-    or of 128 whose waves copy for themselves (at most 128 rows, head_dim 64)."""
+    """One sequence takes blocks of 128 rows, so many copies of it that all blocks fill the chip take blocks of 256."""
     copies = 256 // (hkv * n_splits) + 1
     one = make(dtype, hq, hkv, d, t, [plen], "peaked", 52000 + t)
     many = make(dtype, hq, hkv, d, t, [plen] * copies, "peaked", 52000 + t)
@@ -75,3 +72,14 @@ def test_parts_do_not_depend_on_the_block(dtype, hq, hkv, d, t, plen, n_splits):
     for b in (0, copies // 2, copies - 1):
         assert torch.equal(got[0][1][0], got[1][1][b])
         assert torch.equal(got[0][0][0][filled], got[1][0][b][filled])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,hq,hkv,d,t,plen,n_splits", [
+    ("bf16", 4, 2, 64, 24, 700, 2),      # 48 rows
+    ("f16", 4, 2, 64, 64, 3333, 3),      # 128 rows
+])
+def test_parts_do_not_depend_on_the_copying_waves(dtype, hq, hkv, d, t, plen, n_splits):
+    """At head_dim 64 one sequence takes blocks with waves that copy; of so many copies of it that all blocks fill the chip the
+    blocks' waves copy for themselves."""
+    test_parts_do_not_depend_on_the_block(dtype, hq, hkv, d, t, plen, n_splits)
